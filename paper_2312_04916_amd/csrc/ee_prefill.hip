@@ -600,7 +600,10 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_swiglu_kern
     constexpr int MW = MTL / 2;
     float* rs = pf_rs_ptr<MTL, NWAVE, true>(pf_lds);
     f32x4 acc[WNF][MW];
-    pf_mainloop<MTL, NWAVE, true>(a, t, pf_lds, rs, acc);
+    // One operand set for both tiles: with two, the 64-row tile's epilogue put 24 registers of the main loop into scratch
+    // at the 128 that two workgroups per CU leave (2422 us at 2048 rows of the 7B widths; 76 registers now.  Prompts, 7B
+    // widths: 5000 tokens through 4 layers 30.6 -> 16.3 ms, 99 tokens through 8 layers 4.79 -> 3.03 ms).
+    pf_mainloop<MTL, NWAVE, true, false>(a, t, pf_lds, rs, acc);
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     const int KTf = F / 32;
 #pragma unroll
