@@ -439,8 +439,8 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
     const int d = cf.d_model, F = cf.d_ff, dt = cf.dtype;
     SegDesc* dd = m->dev_desc(di);
     const int32_t* xrow = (const int32_t*)((char*)dd + offsetof(SegDesc, xrow));
-    const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d);
-    const bool pk_F = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, F);
+    const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d, 3 * d);
+    const bool pk_F = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, F, d);
     char* xg_pk = m->ws + m->wsl.xg_pk;
     GemmCommon g{};
     g.dtype = dt;
@@ -473,7 +473,7 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
         HIPCHK(launch_attention(dt, m->ws + m->wsl.q, m->ws + m->wsl.attn, m->lo_rows(d), dd, g.desc_host, T, n_qt, m->dev_btab(), c->geom,
                                 kv_layer, d,
                                 (float*)(m->ws + m->wsl.attn_part), (int32_t*)(m->ws + m->wsl.counters) + 64, max_ctx,
-                                gemm_rows_fit_lds(dt, T, d) ? &att_ns : nullptr, pk_d, st));
+                                gemm_rows_fit_lds(dt, T, d, 3 * d) ? &att_ns : nullptr, pk_d, st));
     }
     if (phase == BLOCK_FRONT) {
         *att_ns_io = att_ns;
@@ -516,7 +516,7 @@ int run_layers(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int l0, int
     // More rows than a workgroup can stage in LDS: the GEMMs then take their row operands from packed arrays
     // (dense rows of this launch in MFMA operand order) that the producing epilogues write, and the segment
     // starts by packing the rows' x.g operands out of the residual store.
-    const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d);
+    const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d, 3 * d);
     if (pk_d && l0 < l1 && first_phase != BLOCK_REST)
         HIPCHK(launch_pack_rows(c->xg(), c->xs_lo, d, xrow, T, d, m->ws + m->wsl.xg_pk, m->lo_rows(d), st));
     for (int l = l0; l < l1; ++l) {
@@ -581,7 +581,7 @@ int run_exit_layer(ee_model* m, ee_kv_cache* c, int seg, const int32_t* src, boo
     if (T <= 0) return EE_OK;
     const int32_t* dst = (const int32_t*)((char*)m->dev_desc(me) + offsetof(SegDesc, xrow));
     HIPCHK(launch_copy_slots(dt, src, dst, T, d, c->x(), c->xgh(), c->xs_lo, c->ssq(), c->ssq_stride, st));
-    if (dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d))
+    if (dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d, 3 * d))
         HIPCHK(launch_pack_rows(c->xgh(), c->xs_lo, d, dst, T, d, m->ws + m->wsl.xg_pk, m->lo_rows(d), st));
     const BlockW w{m->wbase + m->wl.eqkv[seg], m->wbase + m->wl.ewo[seg], m->wbase + m->wl.egu[seg], m->wbase + m->wl.ewd[seg],
                    m->gain(m->wl.gm[seg])};
@@ -620,8 +620,8 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
         const int32_t* src = (const int32_t*)((char*)dd + offsetof(SegDesc, head_xrow));
         const int32_t* dst = (const int32_t*)((char*)ed + offsetof(SegDesc, xrow));
         HIPCHK(launch_copy_slots(dt, src, dst, n_head, d, c->x(), c->xgh(), c->xs_lo, c->ssq(), c->ssq_stride, st));
-        const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, d);
-        const bool pk_F = dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, cf.d_ff);
+        const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, d, 3 * d);
+        const bool pk_F = dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, cf.d_ff, d);
         if (pk_d) HIPCHK(launch_pack_rows(c->xgh(), c->xs_lo, d, dst, n_head, d, m->ws + m->wsl.xg_pk, m->lo_rows(d), st));
         g.desc = ed;
         g.desc_host = eh;
@@ -641,7 +641,7 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
     g.a_packed = 0;
     g.lda = d;
     g.arow = (const int32_t*)((char*)dd + offsetof(SegDesc, head_xrow));
-    if (dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, d)) {  // many rows: packed operands
+    if (dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, d, 3 * d)) {  // many rows: packed operands
         char* hp = m->ws + m->wsl.head_pk;
         HIPCHK(launch_pack_rows(g.A, g.a_lo, d, g.arow, n_head, d, hp, (size_t)64 * d, st));
         g.A = hp;
@@ -852,12 +852,14 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
             // layer's KV write and attention are enqueued before the host knows which, so that the GPU does not stand
             // idle while the result travels and the launches follow.  They change nothing a token that leaves depends
             // on: K and V of rows whose watermark for that segment stays where it was (the pass that does advance it
-            // writes them again), and the q, attention and partial buffers of the workspace.  The residual stream is
+            // writes them again), and the q, attention, packed-operand and partial buffers of the workspace (a segment
+            // that starts packs its operands itself).  The residual stream is
             // first touched by the O projection, which waits for the decision.
             if (!is_final && ss.size() == 1 && !pp.on) {
                 const SegDesc* nd = m->host_desc(s + 1);
-                const int dt = m->cfg.dtype;
-                if (nd->T > 0 && (dt != EE_BF16 || gemm_rows_fit_lds(dt, nd->T, m->cfg.d_model))) {
+                // (For long deferred lists the work that a leaving token throws away outweighs the idle time: 31 deferred
+                // rows at the 7B width, 10.3 against 9.8 ms for a list filled and worked off.)
+                if (nd->T > 0 && (m->cfg.dtype != EE_BF16 || (nd->T <= 16 && nd->T * m->cfg.d_model <= 17408))) {
                     EECHK(run_layers(m, c, s + 1, nd->T, nd->n_qt, m->seg_begin(s + 1), m->seg_end(s + 1), max_ctx, st, BLOCK_FRONT, &spec_ns));
                     spec_seg = s + 1;
                     HIPCHK(hipEventRecord(m->spec_ev, st));

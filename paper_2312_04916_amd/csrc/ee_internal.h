@@ -119,7 +119,8 @@ hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, c
                             bool out_packed, hipStream_t s);
 // defer_ns != NULL: when the KV range was split, leave the partials unmerged and report the number of splits
 // (the O projection then merges them, see GemmCommon::att_part); 0 is reported when `out` is complete.
-bool gemm_rows_fit_lds(int dtype, int T, int K);  // true when the GEMMs stage this many rows in LDS
+// true when GEMMs of T rows with K inputs and N outputs stage their rows in LDS; the rows are packed (a_packed) otherwise
+bool gemm_rows_fit_lds(int dtype, int T, int K, int N);
 
 hipError_t launch_kv_gather(int dtype, const KvGeom& kv, int layer, const int32_t* btab_seq, int pos0, int n,
                             float* k_out, float* v_out, hipStream_t s);

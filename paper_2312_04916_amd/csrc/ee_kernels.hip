@@ -436,13 +436,10 @@ struct GemmArgs {
     int att_ns, att_H, att_hd;
 };
 
-// G = 16-column tiles a workgroup owns (1 for few rows; more when there are many rows, so that the
-// activation operands a wave has loaded serve several weight tiles and the L2 traffic of the rows,
-// which every workgroup re-reads in full, shrinks accordingly)
-template <int KS, int MT, int G = 1>
+template <int KS, int MT>
 struct GemmSmem {
     float red[KS][MT][256];
-    float out[G][MT * 16][16];
+    float out[MT * 16][16];
     float rs[MT * 16];
 };
 
@@ -469,227 +466,10 @@ __device__ __forceinline__ void rms_scales(const GemmArgs& a, float* rs) {
     }
 }
 
-template <int KS, int MT, typename Pre>
-__device__ __forceinline__ void gemm_mainloop_bf16(const GemmArgs& a, int tile, GemmSmem<KS, MT>& sm, Pre pre) {
-    const int ks = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int li = lane & 15, lg = lane >> 4;
-    const int KT = a.KT;
-    const int kt0 = (int)(((long)ks * KT) / KS), kt1 = (int)(((long)(ks + 1) * KT) / KS);
-    const u32x4* wp = (const u32x4*)a.W + ((size_t)tile * KT + kt0) * 64 + lane;
-    f32x4 acc[MT];
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) acc[mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // Ring of D tiles (1 KB of weights each) per wave: a slot is refilled with the tile D ahead as soon
-    // as its MFMAs are issued.  The first D weight loads go out before anything that depends on another
-    // load (row indirection, RMS partial sums, epilogue operands), so the stream starts at once.
-    constexpr int D = MT == 1 ? 7 : 4;
-    u32x4 w[D], ah[MT][D], al[MT][D];
-    const int n = kt1 - kt0;
-    auto fill_w = [&](int u, int t) { w[u] = __builtin_nontemporal_load(wp + (size_t)t * 64); };
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < n) fill_w(u, u);
-    // Rows beyond T read row 0 again (always a valid address): their products are never looked at,
-    // and an unpredicated load keeps the loop free of branches.
-    // A operands: row-major rows (a load gathers 16 rows x 64 bytes), or already in operand order
-    // (packed: one contiguous KB per load)
-    const __bf16* ap[MT];
-    const int astep = a.a_packed ? 512 : 32;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        if (a.a_packed) {
-            ap[mt] = (const __bf16*)a.A + ((size_t)mt * KT + kt0) * 512 + lane * 8;
-        } else {
-            int row = mt * 16 + li;
-            if (row >= a.T) row = 0;
-            int idx = a.arow ? a.arow[row] : row;
-            ap[mt] = (const __bf16*)a.A + (size_t)idx * a.lda + (size_t)kt0 * 32 + lg * 8;
-        }
-    }
-    auto fill_a = [&](int u, int t) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            ah[mt][u] = *(const u32x4*)(ap[mt] + (size_t)t * astep);
-            al[mt][u] = *(const u32x4*)(ap[mt] + a.a_lo + (size_t)t * astep);
-        }
-    };
-    auto fill = [&](int u, int t) {  // slot u <- tile t (relative to kt0)
-        fill_w(u, t);
-        fill_a(u, t);
-    };
-    auto use = [&](int u) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, al[mt][u]),
-                                                              __builtin_bit_cast(bf16x8, w[u]), acc[mt], 0, 0, 0);
-            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ah[mt][u]),
-                                                              __builtin_bit_cast(bf16x8, w[u]), acc[mt], 0, 0, 0);
-        }
-    };
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < n) fill_a(u, u);
-    rms_scales<MT>(a, sm.rs);
-    pre(std::false_type{});
-    const int full = n / D, rem = n - full * D;
-    for (int gI = 0; gI + 1 < full; ++gI) {  // steady state: every refill is in range
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            use(u);
-            fill(u, (gI + 1) * D + u);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    if (full > 0) {  // last full group: refill only the slots the remainder needs
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            use(u);
-            if (u < rem) fill(u, full * D + u);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < rem) use(u);
-    // accumulator layout: lane (lg, li) holds D[row = lg*4 + r][col = li]
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) sm.red[ks][mt][(lg * 4 + r) * 16 + li] = acc[mt][r];
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
-        int e = idx & 255, mt = idx >> 8;
-        float s = 0.f;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) s += sm.red[k][mt][e];
-        int m = mt * 16 + (e >> 4);
-        sm.out[0][m][e & 15] = s * sm.rs[m];
-    }
-    __syncthreads();
-}
-
-// Register path with G tiles per workgroup: every ring slot holds one k-step of G weight tiles and of the
-// MT row tiles (both terms); the G*MT products of a slot share its activation registers.
-template <int KS, int MT, int G, typename Pre>
-__device__ __forceinline__ void gemm_mainloop_bf16_multi(const GemmArgs& a, int tile0, GemmSmem<KS, MT, G>& sm, Pre pre) {
-    const int ks = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int li = lane & 15, lg = lane >> 4;
-    const int KT = a.KT;
-    const int kt0 = (int)(((long)ks * KT) / KS), kt1 = (int)(((long)(ks + 1) * KT) / KS);
-    const u32x4* wp[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        int t = tile0 + g;
-        if (t >= a.n_tiles) t = a.n_tiles - 1;  // (a surplus tile repeats the last one; its result is dropped)
-        wp[g] = (const u32x4*)a.W + ((size_t)t * KT + kt0) * 64 + lane;
-    }
-    f32x4 acc[G][MT];
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) acc[g][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    constexpr int D = (MT == 4 || MT * G >= 12) ? 2 : 4;  // ring slots: fewer where a slot already holds many KB
-    u32x4 w[G][D], ah[MT][D], al[MT][D];
-    const int n = kt1 - kt0;
-    auto fill_w = [&](int u, int t) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) w[g][u] = __builtin_nontemporal_load(wp[g] + (size_t)t * 64);
-    };
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < n) fill_w(u, u);
-    // A operands: row-major rows (a load gathers 16 rows x 64 bytes), or already in operand order
-    // (packed: one contiguous KB per load)
-    const __bf16* ap[MT];
-    const int astep = a.a_packed ? 512 : 32;
-#pragma unroll
-    for (int mt = 0; mt < MT; ++mt) {
-        if (a.a_packed) {
-            ap[mt] = (const __bf16*)a.A + ((size_t)mt * KT + kt0) * 512 + lane * 8;
-        } else {
-            int row = mt * 16 + li;
-            if (row >= a.T) row = 0;
-            int idx = a.arow ? a.arow[row] : row;
-            ap[mt] = (const __bf16*)a.A + (size_t)idx * a.lda + (size_t)kt0 * 32 + lg * 8;
-        }
-    }
-    auto fill_a = [&](int u, int t) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            ah[mt][u] = *(const u32x4*)(ap[mt] + (size_t)t * astep);
-            al[mt][u] = *(const u32x4*)(ap[mt] + a.a_lo + (size_t)t * astep);
-        }
-    };
-    auto use = [&](int u) {
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int mt = 0; mt < MT; ++mt) {
-                acc[g][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, al[mt][u]),
-                                                                     __builtin_bit_cast(bf16x8, w[g][u]), acc[g][mt], 0, 0, 0);
-                acc[g][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, ah[mt][u]),
-                                                                     __builtin_bit_cast(bf16x8, w[g][u]), acc[g][mt], 0, 0, 0);
-            }
-    };
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < n) fill_a(u, u);
-    rms_scales<MT>(a, sm.rs);
-    pre(std::false_type{});
-    const int full = n / D, rem = n - full * D;
-    for (int gI = 0; gI + 1 < full; ++gI) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            use(u);
-            fill_w(u, (gI + 1) * D + u);
-            fill_a(u, (gI + 1) * D + u);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    }
-    if (full > 0) {
-#pragma unroll
-        for (int u = 0; u < D; ++u) {
-            use(u);
-            if (u < rem) {
-                fill_w(u, full * D + u);
-                fill_a(u, full * D + u);
-            }
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < rem) use(u);
-    // cross-wave reduction, one tile after the other through the same buffer
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) sm.red[ks][mt][(lg * 4 + r) * 16 + li] = acc[g][mt][r];
-        __syncthreads();
-        for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
-            int e = idx & 255, mt = idx >> 8;
-            float s = 0.f;
-#pragma unroll
-            for (int k = 0; k < KS; ++k) s += sm.red[k][mt][e];
-            int m = mt * 16 + (e >> 4);
-            sm.out[g][m][e & 15] = s * sm.rs[m];
-        }
-        __syncthreads();
-    }
-}
-
 // Variant for few rows (T*K small enough for LDS): the workgroup first copies its T activation rows
 // (hi and lo terms) into LDS, and the loop takes its A operands from there.  The vector-memory queue
 // then carries weight loads only (deeper ring, no registers spent on A look-ahead), and the lower
-// register count lets more workgroups share a CU.  Up to 72 KB of rows (two workgroups per CU still fit: 4 rows at
-// K = 4096); with 112 KB (one workgroup per CU) the 30B-shaped steps of 4 rows were 5 % slower than on the register
-// path, while 2-4 rows at the 7B width gained 2-4 % over it.
-constexpr int A_LDS_MAX_BYTES = 72 * 1024;
-// The 16-wave variants (K beyond 4096) have the CU to themselves whatever their LDS use, so two or three of their
-// rows may take up to 140 KB (the down projection at the 7B width: 88 and 132 KB; 23.1 us on the register path,
-// which steps carrying a deferred row or two took until then, against 18 us; C3 at threshold 0.2: 2.262 -> 2.240 ms
-// per step).  Four rows stay on the register path: see the 30B-shaped steps above.
-constexpr int A_LDS_MAX_BYTES_16 = 140 * 1024;
+// register count lets more workgroups share a CU.
 __host__ __device__ inline int a_lds_row_stride(int K) { return 2 * K + 32; }  // elements; +64 B staggers the banks of two rows
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding global load of
@@ -980,7 +760,7 @@ __device__ __forceinline__ void gemm_mainloop_bf16_lds(const GemmArgs& a, int ti
 #pragma unroll
         for (int k = 0; k < KS; ++k) s += sm.red[k][0][idx];
         int m = idx >> 4;
-        sm.out[0][m][idx & 15] = s * sm.rs[m];
+        sm.out[m][idx & 15] = s * sm.rs[m];
     }
     __syncthreads();
 }
@@ -1000,24 +780,20 @@ __device__ __forceinline__ void gemm_mainloop_f32(const GemmArgs& a, int tile, G
             const float* wr = (const float*)a.W + ((size_t)tile * 16 + c) * a.K;
             for (int k = 0; k < a.K; ++k) s = fmaf(ar[k], wr[k], s);
         }
-        sm.out[0][m][c] = s * sm.rs[m];
+        sm.out[m][c] = s * sm.rs[m];
     }
     __syncthreads();
 }
 
 // `pre` runs once the first weight loads are in flight: the place to fetch what the epilogue needs.
-// Leaves tile g of the workgroup (g < G, tile index tile0 + g) in sm.out[g].
-template <typename ST, int KS, int MT, bool ALDS, int G, typename Pre, int ATT = 0>
-__device__ __forceinline__ void gemm_mainloop(const GemmArgs& a, int tile0, GemmSmem<KS, MT, G>& sm, Pre pre) {
-    if constexpr (G > 1) {
-        static_assert(sizeof(ST) == 2 && !ALDS, "several tiles per workgroup: bf16 register path only");
-        gemm_mainloop_bf16_multi<KS, MT, G>(a, tile0, sm, pre);
-    } else if constexpr (sizeof(ST) == 2 && ALDS)
-        gemm_mainloop_bf16_lds<KS, ATT>(a, tile0, sm, pre);
-    else if constexpr (sizeof(ST) == 2)
-        gemm_mainloop_bf16<KS, MT>(a, tile0, sm, pre);  // (its first __syncthreads orders rs before use)
+// Leaves the tile in sm.out.
+template <typename ST, int KS, int MT, bool ALDS, typename Pre, int ATT = 0>
+__device__ __forceinline__ void gemm_mainloop(const GemmArgs& a, int tile, GemmSmem<KS, MT>& sm, Pre pre) {
+    static_assert(sizeof(ST) == 4 || ALDS, "many rows of the bf16 model: rows_kernel");
+    if constexpr (sizeof(ST) == 2)
+        gemm_mainloop_bf16_lds<KS, ATT>(a, tile, sm, pre);
     else
-        gemm_mainloop_f32<KS, MT>(a, tile0, sm, pre);
+        gemm_mainloop_f32<KS, MT>(a, tile, sm, pre);
 }
 
 // (Launch bounds of the few-rows variants: 6 waves per SIMD, i.e. at most 80 registers per lane, so that three
@@ -1038,17 +814,17 @@ struct QkvArgs {
     int32_t pos_v0, blk_v0;  // those of row 0 (a launch of one row reads them here)
 };
 
-template <typename ST, int KS, int MT, bool ALDS, int G = 1>
+template <typename ST, int KS, int MT, bool ALDS>
 __global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_qkv_kernel(GemmArgs a, QkvArgs<ST> e) {
-    __shared__ GemmSmem<KS, MT, G> sm;
+    __shared__ GemmSmem<KS, MT> sm;
     const int per_head = e.hd / 16, per_part = e.H * per_head;
     const int half = e.hd / 2;
-    const int tile0 = blockIdx.x * G;
+    const int tile = blockIdx.x;
     // epilogue operands of this thread's first (row, column pair) of the first tile, fetched while the weights stream
     const int m0 = threadIdx.x >> 3, i0 = threadIdx.x & 7;
     int pos0 = 0, blk0 = 0;
     float2 cs0 = make_float2(1.f, 0.f);
-    gemm_mainloop<ST, KS, MT, ALDS, G>(a, tile0, sm, [&](auto one_row) {
+    gemm_mainloop<ST, KS, MT, ALDS>(a, tile, sm, [&](auto one_row) {
         if (m0 < a.T) {
             if constexpr (decltype(one_row)::value) {  // (the row's position and block sit in the kernel arguments)
                 pos0 = e.pos_v0;
@@ -1057,50 +833,45 @@ __global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_q
                 pos0 = e.pos[m0];
                 blk0 = e.kvblk[m0];
             }
-            if (tile0 / per_part < 2) cs0 = e.rope_cs[(size_t)pos0 * half + (tile0 % per_head) * 8 + i0];
+            if (tile / per_part < 2) cs0 = e.rope_cs[(size_t)pos0 * half + (tile % per_head) * 8 + i0];
         }
     });
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int tile = tile0 + g;
-        if (tile >= a.n_tiles) break;
-        const float(*out)[16] = sm.out[g];
-        const int part = tile / per_part;  // 0 q, 1 k, 2 v
-        const int rem = tile % per_part;
-        const int h = rem / per_head, c = rem % per_head;
-        for (int idx = threadIdx.x; idx < MT * 128; idx += blockDim.x) {
-            int m = idx >> 3, i = idx & 7;
-            if (m >= a.T) continue;
-            float lo = out[m][i], hi = out[m][8 + i];
-            int pos = pos0, blk = blk0;
-            float2 cs = cs0;
-            if (g != 0 || idx != (int)threadIdx.x) {
-                pos = e.pos[m];
-                blk = e.kvblk[m];
-                if (part < 2) cs = e.rope_cs[(size_t)pos * half + c * 8 + i];
-            }
-            if (part < 2) {
-                float nlo = lo * cs.x - hi * cs.y;
-                float nhi = hi * cs.x + lo * cs.y;
-                lo = nlo;
-                hi = nhi;
-            }
-            if (part == 0) {
-                ST* qp = e.q + (size_t)m * e.d + h * e.hd + c * 8 + i;
-                store_split<ST>(qp, e.q_lo, lo);
-                store_split<ST>(qp + half, e.q_lo, hi);
-            } else if (part == 1) {  // K block: [head][position][feature]
-                ST* kp = e.kv_layer + (size_t)blk * e.blk_stride + ((size_t)h * e.BT + (pos % e.BT)) * e.hd + c * 8 + i;
-                kp[0] = cvt_st<ST>(lo);
-                kp[half] = cvt_st<ST>(hi);
-            } else {  // V block, transposed in groups of 32 positions: [head][position / 32][feature][position % 32], so
-                      // that attention reads the P.V operands of a 32-position tile directly and as one contiguous piece
-                const int pin = pos % e.BT;
-                ST* vp = e.kv_layer + (size_t)blk * e.blk_stride + (size_t)e.H * e.BT * e.hd + (size_t)h * e.hd * e.BT +
-                         (size_t)(pin >> 5) * (e.hd * 32) + (c * 8 + i) * 32 + (pin & 31);
-                vp[0] = cvt_st<ST>(lo);
-                vp[half * 32] = cvt_st<ST>(hi);
-            }
+    const float(*out)[16] = sm.out;
+    const int part = tile / per_part;  // 0 q, 1 k, 2 v
+    const int rem = tile % per_part;
+    const int h = rem / per_head, c = rem % per_head;
+    for (int idx = threadIdx.x; idx < MT * 128; idx += blockDim.x) {
+        int m = idx >> 3, i = idx & 7;
+        if (m >= a.T) continue;
+        float lo = out[m][i], hi = out[m][8 + i];
+        int pos = pos0, blk = blk0;
+        float2 cs = cs0;
+        if (idx != (int)threadIdx.x) {
+            pos = e.pos[m];
+            blk = e.kvblk[m];
+            if (part < 2) cs = e.rope_cs[(size_t)pos * half + c * 8 + i];
+        }
+        if (part < 2) {
+            float nlo = lo * cs.x - hi * cs.y;
+            float nhi = hi * cs.x + lo * cs.y;
+            lo = nlo;
+            hi = nhi;
+        }
+        if (part == 0) {
+            ST* qp = e.q + (size_t)m * e.d + h * e.hd + c * 8 + i;
+            store_split<ST>(qp, e.q_lo, lo);
+            store_split<ST>(qp + half, e.q_lo, hi);
+        } else if (part == 1) {  // K block: [head][position][feature]
+            ST* kp = e.kv_layer + (size_t)blk * e.blk_stride + ((size_t)h * e.BT + (pos % e.BT)) * e.hd + c * 8 + i;
+            kp[0] = cvt_st<ST>(lo);
+            kp[half] = cvt_st<ST>(hi);
+        } else {  // V block, transposed in groups of 32 positions: [head][position / 32][feature][position % 32], so
+                  // that attention reads the P.V operands of a 32-position tile directly and as one contiguous piece
+            const int pin = pos % e.BT;
+            ST* vp = e.kv_layer + (size_t)blk * e.blk_stride + (size_t)e.H * e.BT * e.hd + (size_t)h * e.hd * e.BT +
+                     (size_t)(pin >> 5) * (e.hd * 32) + (c * 8 + i) * 32 + (pin & 31);
+            vp[0] = cvt_st<ST>(lo);
+            vp[half * 32] = cvt_st<ST>(hi);
         }
     }
 }
@@ -1129,10 +900,10 @@ __device__ __forceinline__ int resid_slot(const ResidArgs<ST>& e, int m) {
     return e.has_v ? e.xrow_v[m] : e.xrow[m];
 }
 
-template <typename ST, int KS, int MT, bool ALDS, int ATT, int G>
+template <typename ST, int KS, int MT, bool ALDS, int ATT>
 __device__ __forceinline__ void gemm_resid_body(const GemmArgs& a, const ResidArgs<ST>& e) {
-    __shared__ GemmSmem<KS, MT, G> sm;
-    const int tile0 = blockIdx.x * G;
+    __shared__ GemmSmem<KS, MT> sm;
+    const int tile = blockIdx.x;
     // epilogue operands of this thread's first element of the first tile, fetched while the weights stream
     const int m0 = threadIdx.x >> 4, i0 = threadIdx.x & 15;
     size_t o0 = 0;
@@ -1140,79 +911,69 @@ __device__ __forceinline__ void gemm_resid_body(const GemmArgs& a, const ResidAr
     auto pre = [&](auto one_row) {
         if (m0 < a.T) {
             if constexpr (decltype(one_row)::value)
-                o0 = (size_t)e.xrow_v[0] * e.d + tile0 * 16 + i0;
+                o0 = (size_t)e.xrow_v[0] * e.d + tile * 16 + i0;
             else
-                o0 = (size_t)resid_slot(e, m0) * e.d + tile0 * 16 + i0;
+                o0 = (size_t)resid_slot(e, m0) * e.d + tile * 16 + i0;
             x0 = e.x[o0];
-            gn0 = e.g_next[tile0 * 16 + i0];
-            if (e.xgh) gh0 = e.g_head[tile0 * 16 + i0];
+            gn0 = e.g_next[tile * 16 + i0];
+            if (e.xgh) gh0 = e.g_head[tile * 16 + i0];
         }
     };
-    gemm_mainloop<ST, KS, MT, ALDS, G, decltype(pre), ATT>(a, tile0, sm, pre);
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int tile = tile0 + g;
-        if (tile >= a.n_tiles) break;  // (uniform over the workgroup)
-        float(*out)[16] = sm.out[g];
-        const int n0 = tile * 16;
-        for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
-            int m = idx >> 4, i = idx & 15;
-            if (m >= a.T) continue;
-            size_t o = o0;
-            float xv = x0, gn = gn0, gh = gh0;
-            if (g != 0 || idx != (int)threadIdx.x) {
-                o = (size_t)resid_slot(e, m) * e.d + n0 + i;
-                xv = e.x[o];
-                gn = e.g_next[n0 + i];
-                if (e.xgh) gh = e.g_head[n0 + i];
-            }
-            float v = xv + out[m][i];
-            e.x[o] = v;
-            out[m][i] = v;
-            store_split<ST>(e.xg + o, e.xs_lo, v * gn);
-            if (e.xgh) store_split<ST>(e.xgh + o, e.xs_lo, v * gh);
-            if (e.xg_pk) store_split<ST>(e.xg_pk + pk_index(m, n0 + i, e.d / 32), e.xg_pk_lo, v * gn);
+    gemm_mainloop<ST, KS, MT, ALDS, decltype(pre), ATT>(a, tile, sm, pre);
+    float(*out)[16] = sm.out;
+    const int n0 = tile * 16;
+    for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
+        int m = idx >> 4, i = idx & 15;
+        if (m >= a.T) continue;
+        size_t o = o0;
+        float xv = x0, gn = gn0, gh = gh0;
+        if (idx != (int)threadIdx.x) {
+            o = (size_t)resid_slot(e, m) * e.d + n0 + i;
+            xv = e.x[o];
+            gn = e.g_next[n0 + i];
+            if (e.xgh) gh = e.g_head[n0 + i];
         }
-        __syncthreads();
-        for (int m = threadIdx.x; m < MT * 16; m += blockDim.x) {
-            if (m >= a.T) continue;
-            float s = 0.f;
+        float v = xv + out[m][i];
+        e.x[o] = v;
+        out[m][i] = v;
+        store_split<ST>(e.xg + o, e.xs_lo, v * gn);
+        if (e.xgh) store_split<ST>(e.xgh + o, e.xs_lo, v * gh);
+        if (e.xg_pk) store_split<ST>(e.xg_pk + pk_index(m, n0 + i, e.d / 32), e.xg_pk_lo, v * gn);
+    }
+    __syncthreads();
+    for (int m = threadIdx.x; m < MT * 16; m += blockDim.x) {
+        if (m >= a.T) continue;
+        float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) s += out[m][i] * out[m][i];
-            e.ssq_out[(size_t)resid_slot(e, m) * e.ssq_stride + tile] = s;
-        }
+        for (int i = 0; i < 16; ++i) s += out[m][i] * out[m][i];
+        e.ssq_out[(size_t)resid_slot(e, m) * e.ssq_stride + tile] = s;
     }
 }
 
-template <typename ST, int KS, int MT, bool ALDS, int G = 1>
-__global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_resid_kernel(GemmArgs a, ResidArgs<ST> e) {
-    gemm_resid_body<ST, KS, MT, ALDS, 0, G>(a, e);
+template <typename ST, int KS, int MT, bool ALDS>
+__global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : KS == 4 ? 5 : 6) : 1) void gemm_resid_kernel(GemmArgs a, ResidArgs<ST> e) {
+    gemm_resid_body<ST, KS, MT, ALDS, 0>(a, e);
 }
 
 // O projection whose input rows are merged from the attention kernel's split partials while being staged
 template <int KS, int MAXS>
 __global__ __launch_bounds__(KS * 64) void gemm_resid_att_kernel(GemmArgs a, ResidArgs<__bf16> e) {
-    gemm_resid_body<__bf16, KS, 1, true, MAXS, 1>(a, e);
+    gemm_resid_body<__bf16, KS, 1, true, MAXS>(a, e);
 }
 
 // ---- epilogue 3: SwiGLU.  Tile j: columns 0..7 = gate features 8j.., columns 8..15 = the matching up features
-template <typename ST, int KS, int MT, bool ALDS, int G = 1>
+template <typename ST, int KS, int MT, bool ALDS>
 __global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_swiglu_kernel(GemmArgs a, ST* act, size_t act_lo, int F, int act_pk) {
-    __shared__ GemmSmem<KS, MT, G> sm;
-    const int tile0 = blockIdx.x * G;
-    gemm_mainloop<ST, KS, MT, ALDS, G>(a, tile0, sm, [](auto) {});
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int tile = tile0 + g;
-        if (tile >= a.n_tiles) break;
-        const float(*out)[16] = sm.out[g];
-        for (int idx = threadIdx.x; idx < MT * 128; idx += blockDim.x) {
-            int m = idx >> 3, i = idx & 7;
-            if (m >= a.T) continue;
-            float gt = out[m][i], up = out[m][8 + i];
-            float sl = gt / (1.0f + expf(-gt));
-            store_split_at<ST>(act, act_lo, m, tile * 8 + i, F, act_pk, sl * up);
-        }
+    __shared__ GemmSmem<KS, MT> sm;
+    const int tile = blockIdx.x;
+    gemm_mainloop<ST, KS, MT, ALDS>(a, tile, sm, [](auto) {});
+    const float(*out)[16] = sm.out;
+    for (int idx = threadIdx.x; idx < MT * 128; idx += blockDim.x) {
+        int m = idx >> 3, i = idx & 7;
+        if (m >= a.T) continue;
+        float gt = out[m][i], up = out[m][8 + i];
+        float sl = gt / (1.0f + expf(-gt));
+        store_split_at<ST>(act, act_lo, m, tile * 8 + i, F, act_pk, sl * up);
     }
 }
 
@@ -1236,43 +997,38 @@ __device__ __forceinline__ void merge_partial(float& m, float& s, int& i, float 
     }
 }
 
-template <typename ST, int KS, int MT, bool ALDS, int G = 1>
+template <typename ST, int KS, int MT, bool ALDS>
 __global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_head_kernel(GemmArgs a, HeadArgs e) {
-    __shared__ GemmSmem<KS, MT, G> sm;
-    const int tile0 = blockIdx.x * G;
-    gemm_mainloop<ST, KS, MT, ALDS, G>(a, tile0, sm, [](auto) {});
+    __shared__ GemmSmem<KS, MT> sm;
+    const int tile = blockIdx.x;
+    gemm_mainloop<ST, KS, MT, ALDS>(a, tile, sm, [](auto) {});
+    const float(*out)[16] = sm.out;
+    const int n0 = tile * 16;
+    if (e.logits) {
+        for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
+            int m = idx >> 4, c = idx & 15;
+            if (m < a.T) e.logits[(size_t)m * e.V + n0 + c] = out[m][c];
+        }
+    }
+    for (int m = threadIdx.x; m < MT * 16; m += blockDim.x) {
+        if (m >= a.T) continue;
+        float mx = out[m][0];
+        int ix = 0;
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        const int tile = tile0 + g;
-        if (tile >= a.n_tiles) break;
-        const float(*out)[16] = sm.out[g];
-        const int n0 = tile * 16;
-        if (e.logits) {
-            for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
-                int m = idx >> 4, c = idx & 15;
-                if (m < a.T) e.logits[(size_t)m * e.V + n0 + c] = out[m][c];
+        for (int c = 1; c < 16; ++c)
+            if (out[m][c] > mx) {
+                mx = out[m][c];
+                ix = c;
             }
-        }
-        for (int m = threadIdx.x; m < MT * 16; m += blockDim.x) {
-            if (m >= a.T) continue;
-            float mx = out[m][0];
-            int ix = 0;
+        float s = 0.f;
 #pragma unroll
-            for (int c = 1; c < 16; ++c)
-                if (out[m][c] > mx) {
-                    mx = out[m][c];
-                    ix = c;
-                }
-            float s = 0.f;
-#pragma unroll
-            for (int c = 0; c < 16; ++c) s += expf(out[m][c] - mx);
-            HeadPartial p;
-            p.max = mx;
-            p.sum = s;
-            p.idx = n0 + ix;
-            p.pad = 0;
-            e.partials[(size_t)tile * EE_MAX_SEQS + m] = p;
-        }
+        for (int c = 0; c < 16; ++c) s += expf(out[m][c] - mx);
+        HeadPartial p;
+        p.max = mx;
+        p.sum = s;
+        p.idx = n0 + ix;
+        p.pad = 0;
+        e.partials[(size_t)tile * EE_MAX_SEQS + m] = p;
     }
 }
 
@@ -1353,6 +1109,335 @@ __global__ __launch_bounds__(512) void head_merge_kernel(const HeadPartial* __re
     }
 }
 
+// ------------------------------------------------------------------------------------------------
+// Many rows (bf16 model): the rows arrive in operand order and do not fit LDS.  A workgroup owns G column tiles and all
+// MT row tiles, and its KS waves take the k-tiles in turn (wave ks: ks, ks + KS, ..), each loading its own operands
+// straight into registers: nothing is shared, so the loop has neither barriers nor LDS.  Per k-tile a CU takes in
+// G + 2 MT KB, of which G come from HBM.  Up to 16 rows HBM bounds it (gate|up at the 7B widths 35.7 -> 31.0 us = 5.8
+// TB/s, at the 30B widths 91.5 -> 77.1 us = 6.2 TB/s, 16 and 4 rows); at 64 rows the bytes that a CU can have outstanding
+// do (about 40 KB: 30 to 70 GB/s per CU, the less the more of them come from HBM; neither a deeper ring nor another
+// order of the k-tiles moves it).  Hence as many tiles per workgroup as leave one workgroup per CU, one wave per SIMD
+// with all 512 registers from 33 rows on, and an epilogue that runs on registers behind a single barrier: the product is
+// formed transposed (weights as the A operand), so a lane holds four consecutive features of one row, and everything it
+// needs from memory is requested before the barrier.  64 rows, 7B widths, before (8 waves, at most two tiles, epilogue
+// through LDS with one dependent look-up per element and pass) and now: Q|K|V 79.4 -> 41.8 us, gate|up 86.8 -> 52.1, head
+// 194 -> 128; 32 rows: gate|up 41.4 -> 33.1, Q|K|V 29.2 -> 23.7.
+// ------------------------------------------------------------------------------------------------
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// four consecutive values as two bf16 terms
+__device__ __forceinline__ void store_split4(__bf16* p, size_t lo_off, f32x4 v) {
+    bf16x4 h, l;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        h[r] = (__bf16)v[r];
+        l[r] = (__bf16)(v[r] - (float)h[r]);
+    }
+    *(bf16x4*)p = h;
+    *(bf16x4*)(p + lo_off) = l;
+}
+
+// The RMS scales of the rows in two halves: every load of the wave's rows is requested at once (before the weight ring,
+// so that they are back first), and the sums are formed behind the ring's first loads.  One row after the other, each is
+// two dependent trips to memory: 8 us in front of a 64-row workgroup's first product.
+template <int KS, int MT>
+struct RmsRows {
+    static constexpr int RPW = (MT * 16 + KS - 1) / KS;  // rows per wave
+    static constexpr int NV = 4;                         // pairs of partials per lane: up to 512 partials
+    float2 v[RPW][NV];
+    bool quick;
+    __device__ __forceinline__ void load(const GemmArgs& a) {
+        quick = a.ssq != nullptr && a.ssq_n <= 128 * NV && (a.ssq_n & 1) == 0 && (a.ssq_stride & 1) == 0;
+        if (!quick) return;
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+        int slot[RPW];
+#pragma unroll
+        for (int j = 0; j < RPW; ++j) {
+            const int m = wave * RPW + j;
+            slot[j] = gemm_slot(a, m < a.T ? m : 0);
+        }
+#pragma unroll
+        for (int j = 0; j < RPW; ++j)
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                if (u * 128 < a.ssq_n) {  // (uniform)
+                    const int i = 2 * (u * 64 + lane);
+                    v[j][u] = *(const float2*)(a.ssq + (size_t)slot[j] * a.ssq_stride + (i < a.ssq_n ? i : 0));
+                }
+    }
+    __device__ __forceinline__ void finish(const GemmArgs& a, float* rs) const {
+        if (!quick) {
+            rms_scales<MT>(a, rs);
+            return;
+        }
+        const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+#pragma unroll
+        for (int j = 0; j < RPW; ++j) {
+            float s = 0.f;
+#pragma unroll
+            for (int u = 0; u < NV; ++u)
+                if (2 * (u * 64 + lane) < a.ssq_n) s += v[j][u].x + v[j][u].y;
+            s = wave_sum(s);
+            if (lane == 0 && wave * RPW + j < MT * 16) rs[wave * RPW + j] = 1.0f / sqrtf(s * a.inv_d + a.eps);
+        }
+    }
+};
+
+// Ring slots per wave: as many as the registers hold next to the accumulators (512 per lane with one wave per SIMD, 256
+// with two, 128 with four).
+template <int KS, int MT, int G>
+constexpr int rows_depth() {
+    const int d = ((KS == 4 ? 290 : KS == 8 ? 190 : 84) - 4 * G * MT) / (4 * (G + 2 * MT));
+    return d < 2 ? 2 : d > 8 ? 8 : d;
+}
+
+template <int KS, int MT, int G, typename Epi>
+__global__ __launch_bounds__(KS * 64, KS / 4) void rows_kernel(GemmArgs a, Epi e) {
+    static_assert(KS % MT == 0, "the epilogue gives a wave one row tile");
+    constexpr int D = rows_depth<KS, MT, G>();
+    constexpr int NF = (G * MT + KS - 1) / KS;  // result tiles per wave in the epilogue
+    extern __shared__ f32x4 rows_lds[];         // [KS][G * MT][64]
+    __shared__ float rs[MT * 16];
+    const int ks = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int li = lane & 15, lg = lane >> 4;
+    const int KT = a.KT, tile0 = blockIdx.x * G;
+    const int m = (ks % MT) * 16 + li;  // this lane's row in the epilogue
+    typename Epi::Row row;
+    e.row(row, a, m < a.T ? m : a.T - 1);
+    RmsRows<KS, MT> rms;
+    rms.load(a);
+    const u32x4* wp[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        int t = tile0 + g;
+        if (t >= a.n_tiles) t = a.n_tiles - 1;  // (a surplus tile repeats the last one; its result is dropped)
+        wp[g] = (const u32x4*)a.W + ((size_t)t * KT + ks) * 64 + lane;
+    }
+    const u32x4 *ah_p[MT], *al_p[MT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        ah_p[mt] = (const u32x4*)((const __bf16*)a.A + ((size_t)mt * KT + ks) * 512 + lane * 8);
+        al_p[mt] = (const u32x4*)((const __bf16*)a.A + a.a_lo + ((size_t)mt * KT + ks) * 512 + lane * 8);
+    }
+    f32x4 acc[G][MT];
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) acc[g][mt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 w[G][D], ah[MT][D], al[MT][D];
+    const int n = (KT - ks + KS - 1) / KS;  // k-tiles of this wave
+    auto fill = [&](int u, int t) {
+        const size_t o = (size_t)t * (KS * 64);
+#pragma unroll
+        for (int g = 0; g < G; ++g) w[g][u] = __builtin_nontemporal_load(wp[g] + o);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            ah[mt][u] = ah_p[mt][o];
+            al[mt][u] = al_p[mt][o];
+        }
+    };
+    auto use = [&](int u) {
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[g][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[g][u]),
+                                                                     __builtin_bit_cast(bf16x8, al[mt][u]), acc[g][mt], 0, 0, 0);
+#pragma unroll
+        for (int g = 0; g < G; ++g)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+                acc[g][mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[g][u]),
+                                                                     __builtin_bit_cast(bf16x8, ah[mt][u]), acc[g][mt], 0, 0, 0);
+    };
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+        if (u < n) fill(u, u);
+    rms.finish(a, rs);
+    const int full = n / D, rem = n - full * D;
+    for (int gI = 0; gI + 1 < full; ++gI) {  // steady state: every refill is in range
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            use(u);
+            fill(u, (gI + 1) * D + u);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (full > 0) {  // last full group: refill only the slots the remainder needs
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            use(u);
+            if (u < rem) fill(u, full * D + u);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < D; ++u)
+        if (u < rem) use(u);
+    typename Epi::Ops ops[NF];
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+        const int f = ks + i * KS, tile = tile0 + f / MT;
+        if (f < G * MT && tile < a.n_tiles) e.load(ops[i], row, tile, lg);
+    }
+#pragma unroll
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) rows_lds[((size_t)ks * (G * MT) + g * MT + mt) * 64 + lane] = acc[g][mt];
+    __syncthreads();
+    const float r = rs[m];
+#pragma unroll
+    for (int i = 0; i < NF; ++i) {
+        const int f = ks + i * KS, tile = tile0 + f / MT;
+        if (f >= G * MT || tile >= a.n_tiles) continue;  // (uniform over the wave)
+        f32x4 v = rows_lds[(size_t)f * 64 + lane];
+#pragma unroll
+        for (int k = 1; k < KS; ++k) v += rows_lds[((size_t)k * (G * MT) + f) * 64 + lane];
+        e.store(ops[i], row, m, m < a.T, tile, lg, v * (a.ssq ? r : 1.0f));
+    }
+}
+
+// Epilogues: Row is what depends on the lane's row alone, Ops what a result tile needs from memory.  store() is reached
+// by whole waves (its lanes exchange values); `valid` is false on lanes past the last row.
+struct RowsQkv : QkvArgs<__bf16> {
+    struct Row {
+        int pos, blk;
+    };
+    struct Ops {
+        f32x4 c0, c1;
+    };
+    __device__ __forceinline__ void row(Row& w, const GemmArgs&, int m) const {
+        w.pos = pos[m];
+        w.blk = kvblk[m];
+    }
+    __device__ __forceinline__ void load(Ops& o, const Row& w, int tile, int lg) const {
+        const int per_head = hd / 16, fi = (tile % per_head) * 8 + (lg & 1) * 4;
+        const float* cs = (const float*)(rope_cs + (size_t)w.pos * (hd / 2) + fi);
+        o.c0 = *(const f32x4*)cs;  // (cos, sin) of two features each
+        o.c1 = *(const f32x4*)(cs + 4);
+    }
+    __device__ __forceinline__ void store(const Ops& o, const Row& w, int m, bool valid, int tile, int lg, f32x4 v) const {
+        const int per_head = hd / 16, per_part = H * per_head, half = hd / 2;
+        const int part = tile / per_part, rem = tile % per_part, h = rem / per_head, c = rem % per_head;
+        const bool is_hi = lg >= 2;  // rows 0-7 of a tile = features c*8.., rows 8-15 = their rotary partners
+        const int f = c * 8 + (lg & 1) * 4 + (is_hi ? half : 0);
+        if (part < 2) {
+            const float cx[4] = {o.c0[0], o.c0[2], o.c1[0], o.c1[2]}, sx[4] = {o.c0[1], o.c0[3], o.c1[1], o.c1[3]};
+            f32x4 res;
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) {
+                float lo, hi;
+                halves_of(v[q4], lo, hi);
+                res[q4] = is_hi ? hi * cx[q4] + lo * sx[q4] : lo * cx[q4] - hi * sx[q4];
+            }
+            if (!valid) return;
+            if (part == 0) {
+                store_split4(q + (size_t)m * d + h * hd + f, q_lo, res);
+            } else {  // K block: [head][position][feature]
+                bf16x4 kb;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4) kb[q4] = (__bf16)res[q4];
+                *(bf16x4*)(kv_layer + (size_t)w.blk * blk_stride + ((size_t)h * BT + (w.pos % BT)) * hd + f) = kb;
+            }
+        } else if (valid) {  // V block, transposed in groups of 32 positions
+            const int pin = w.pos % BT;
+            __bf16* vp = kv_layer + (size_t)w.blk * blk_stride + (size_t)H * BT * hd + (size_t)h * hd * BT +
+                         (size_t)(pin >> 5) * (hd * 32) + f * 32 + (pin & 31);
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4) vp[q4 * 32] = (__bf16)v[q4];
+        }
+    }
+};
+
+struct RowsResid : ResidArgs<__bf16> {
+    struct Row {
+        int slot;
+    };
+    struct Ops {
+        f32x4 x, gn, gh;
+    };
+    __device__ __forceinline__ void row(Row& w, const GemmArgs&, int m) const { w.slot = has_v ? xrow_v[m] : xrow[m]; }
+    __device__ __forceinline__ void load(Ops& o, const Row& w, int tile, int lg) const {
+        const int n = tile * 16 + lg * 4;
+        o.x = *(const f32x4*)(x + (size_t)w.slot * d + n);
+        o.gn = *(const f32x4*)(g_next + n);
+        if (xgh) o.gh = *(const f32x4*)(g_head + n);
+    }
+    __device__ __forceinline__ void store(const Ops& o, const Row& w, int m, bool valid, int tile, int lg, f32x4 v) const {
+        const int n = tile * 16 + lg * 4;
+        const size_t at = (size_t)w.slot * d + n;
+        v += o.x;
+        const float sq = rows4_sum(((v[0] * v[0] + v[1] * v[1]) + v[2] * v[2]) + v[3] * v[3]);
+        if (!valid) return;
+        *(f32x4*)(x + at) = v;
+        store_split4(xg + at, xs_lo, v * o.gn);
+        if (xgh) store_split4(xgh + at, xs_lo, v * o.gh);
+        if (xg_pk) store_split4(xg_pk + pk_index(m, n, d / 32), xg_pk_lo, v * o.gn);
+        if (lg == 0) ssq_out[(size_t)w.slot * ssq_stride + tile] = sq;
+    }
+};
+
+struct RowsSwiglu {
+    __bf16* act;
+    size_t act_lo;
+    int F, act_pk;
+    struct Row {};
+    struct Ops {};
+    __device__ __forceinline__ void row(Row&, const GemmArgs&, int) const {}
+    __device__ __forceinline__ void load(Ops&, const Row&, int, int) const {}
+    __device__ __forceinline__ void store(const Ops&, const Row&, int m, bool valid, int tile, int lg, f32x4 v) const {
+        // gate features in the lower 32 lanes, their up partners in the upper 32: the lower half forms features 0 and 1
+        // of its four, the upper half 2 and 3
+        float gt[4], up[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) halves_of(v[q], gt[q], up[q]);
+        const bool hi = lg >= 2;
+        const float g0 = hi ? gt[2] : gt[0], g1 = hi ? gt[3] : gt[1], u0 = hi ? up[2] : up[0], u1 = hi ? up[3] : up[1];
+        if (!valid) return;
+        typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+        const float a0 = g0 / (1.0f + expf(-g0)) * u0, a1 = g1 / (1.0f + expf(-g1)) * u1;
+        bf16x2 h, l;
+        h[0] = (__bf16)a0;
+        h[1] = (__bf16)a1;
+        l[0] = (__bf16)(a0 - (float)h[0]);
+        l[1] = (__bf16)(a1 - (float)h[1]);
+        const int k = tile * 8 + (lg & 1) * 4 + (hi ? 2 : 0);
+        __bf16* p = act + (act_pk ? pk_index(m, k, act_pk) : (size_t)m * F + k);
+        *(bf16x2*)p = h;
+        *(bf16x2*)(p + act_lo) = l;
+    }
+};
+
+struct RowsHead : HeadArgs {
+    struct Row {};
+    struct Ops {};
+    __device__ __forceinline__ void row(Row&, const GemmArgs&, int) const {}
+    __device__ __forceinline__ void load(Ops&, const Row&, int, int) const {}
+    __device__ __forceinline__ void store(const Ops&, const Row&, int m, bool valid, int tile, int lg, f32x4 v) const {
+        const int n = tile * 16 + lg * 4;
+        if (logits && valid) *(f32x4*)(logits + (size_t)m * V + n) = v;
+        float mx = v[0];
+        int ix = n;
+#pragma unroll
+        for (int q = 1; q < 4; ++q)
+            if (v[q] > mx) {
+                mx = v[q];
+                ix = n + q;
+            }
+        const float M = rows4_max(mx);
+        // the lowest index that holds the maximum (indices are below 2^24: exact as floats)
+        const float first = -rows4_max(mx == M ? -(float)ix : -3.0e8f);
+        const float s = rows4_sum(((expf(v[0] - M) + expf(v[1] - M)) + expf(v[2] - M)) + expf(v[3] - M));
+        if (valid && lg == 0) {
+            HeadPartial p;
+            p.max = M;
+            p.sum = s;
+            p.idx = (int)first;
+            p.pad = 0;
+            partials[(size_t)tile * EE_MAX_SEQS + m] = p;
+        }
+    }
+};
+
 // ---- host-side dispatch
 static GemmArgs make_args(const GemmCommon& c) {
     GemmArgs a;
@@ -1393,48 +1478,49 @@ static int mt_of(int T) { return T <= 16 ? 1 : (T <= 32 ? 2 : 4); }
 static int ks_of(const GemmCommon& c) {
     if (c.dtype != EE_BF16) return 4;
     int kt = c.K / 32;
-    if (kt <= 64) return 4;
+    if (kt <= 64 || c.T > 32) return 4;   // (from 33 rows on: one wave per SIMD with all the registers)
     if (kt <= 128 || c.T > 16) return 8;  // (16 waves of 1024 threads leave 128 registers each: one row tile only)
     return 16;
 }
 
-// LDS bytes for the few-rows variant, or 0 when the rows do not fit
-static size_t a_lds_bytes(const GemmCommon& c) {
-    if (c.dtype != EE_BF16 || c.T > 16) return 0;
-    size_t b = (size_t)c.T * a_lds_row_stride(c.K) * 2;
-    if (ks_of(c) == 16 && c.T <= 3) return b <= (size_t)A_LDS_MAX_BYTES_16 ? b : 0;
-    return b <= (size_t)A_LDS_MAX_BYTES ? b : 0;
+// LDS bytes of the few-rows variant
+static size_t a_lds_bytes(int T, int K) { return (size_t)T * a_lds_row_stride(K) * 2; }
+
+// Which rows are staged.  Every workgroup stages all of them for its one column tile, so what a second and third row cost
+// grows with their bytes and with the rounds of workgroups: two or three rows of up to 36 KB (2 rows at K = 4096), or
+// of all the LDS where the launch is a single round (the down projection).  Us per step, staged / rows_kernel: 7B widths,
+// 4 layers, 2 sequences 456 / 489, 3 (48 KB) 503 / 497, 4 526 / 502; 1.3B widths, 8 layers, 3 sequences 451 / 482, 4 503 /
+// 488, 8 647 / 521; 30B widths, 4 layers, 2 sequences (53 KB) 988 / 962, 3 1061 / 966; 768 wide, 12 layers, 4 sequences
+// 474 / 405, 16 624 / 407.
+constexpr size_t A_LDS_MAX_BYTES = 72 * 1024;      // one row, workgroups of up to 8 waves
+constexpr size_t A_LDS_MAX_BYTES_16 = 140 * 1024;  // 16 waves have the CU to themselves whatever their LDS use
+constexpr size_t A_LDS_FEW_BYTES = 36 * 1024;
+
+bool gemm_rows_fit_lds(int dtype, int T, int K, int N) {
+    if (dtype != EE_BF16 || T > 3) return false;
+    GemmCommon c{};
+    c.dtype = dtype;
+    c.T = T;
+    c.K = K;
+    const size_t b = a_lds_bytes(T, K), all = ks_of(c) == 16 ? A_LDS_MAX_BYTES_16 : A_LDS_MAX_BYTES;
+    if (T == 1 || N / 16 <= 256) return b <= all;
+    return b <= A_LDS_FEW_BYTES;
 }
 
-// Column tiles per workgroup for the register path: as many (4 for one row tile, else 2) as still leave
-// gemm_min_wgs() workgroups, so that the rows' operands are re-read from L2 by fewer workgroups without
-// starving the chip of weight streams.  (GemmCommon::min_wgs: 512 unless the model's configuration lowers it, which
-// tests do to reach these variants on small models.)
+// Column tiles per workgroup of a launch of many rows.  One workgroup is resident per CU, so the launch runs in rounds of
+// 256 workgroups (fewer where the test hook GemmCommon::min_wgs asks for it), and per k-tile a workgroup takes in its G
+// weight tiles and the rows' operands in two terms: rounds x (G + 2 mt) is what the launch costs (64 rows at the 7B
+// width: Q|K|V, 768 tiles, 3 tiles per workgroup; gate|up, 1376 tiles, 6).
 static int g_of(int mt, int n_tiles, int min_wgs) {
-    auto gemm_min_wgs = [min_wgs]() { return min_wgs >= 1 ? min_wgs : 512; };
-    if (mt == 1 && n_tiles / 4 >= gemm_min_wgs()) return 4;
-    // Up to two row tiles: at these register counts one workgroup of 8 waves is resident per CU, so a launch runs in
-    // rounds of 256 workgroups.  Give a workgroup as many tiles as there would be rounds (2..6): one round, the same
-    // makespan in tiles, and the row operands and prologues are paid once instead of once per round (Q|K|V at the 7B
-    // width: 768 tiles = 256 x 3; gate|up: 1376 tiles = 230 x 6).  (The test hook scales the 256 with its threshold.)
-    const int cus = gemm_min_wgs() >= 512 ? 256 : (gemm_min_wgs() / 2 > 0 ? gemm_min_wgs() / 2 : 1);
-    const int rounds = (n_tiles + cus - 1) / cus;
-    if (mt <= 2 && rounds >= 2 && rounds <= 6) return rounds;
-    if (n_tiles / 2 >= gemm_min_wgs()) return 2;
-    return 1;
+    const int cus = min_wgs < 1 || min_wgs >= 512 ? 256 : (min_wgs / 2 > 0 ? min_wgs / 2 : 1);
+    int best = 1;
+    long cost = -1;
+    for (int g = 1; g <= 6; ++g) {
+        const long c = (long)((n_tiles + g - 1) / g + cus - 1) / cus * (g + 2 * mt);
+        if (cost < 0 || c < cost) cost = c, best = g;
+    }
+    return best;
 }
-
-#define EE_LAUNCH_G(ST, KERNEL, KS_, MT_, ...)                                                        \
-    do {                                                                                              \
-        constexpr int MTG = MT_ <= 2 ? MT_ : 1; /* 3..6 tiles: up to two row tiles */                 \
-        if (_g == 4 && MT_ == 1) EE_LAUNCH((KERNEL<ST, KS_, 1, false, (KS_ == 16 ? 2 : 4)>), grid, block, s, __VA_ARGS__); \
-        else if (_g == 3 && MT_ <= 2) EE_LAUNCH((KERNEL<ST, KS_, MTG, false, (KS_ == 16 ? 2 : 3)>), grid, block, s, __VA_ARGS__); \
-        else if (_g == 4 && MT_ <= 2) EE_LAUNCH((KERNEL<ST, KS_, MTG, false, (KS_ == 16 ? 2 : 4)>), grid, block, s, __VA_ARGS__); \
-        else if (_g == 5 && MT_ <= 2) EE_LAUNCH((KERNEL<ST, KS_, MTG, false, (KS_ == 16 ? 2 : 5)>), grid, block, s, __VA_ARGS__); \
-        else if (_g == 6 && MT_ <= 2) EE_LAUNCH((KERNEL<ST, KS_, MTG, false, (KS_ == 16 ? 2 : 6)>), grid, block, s, __VA_ARGS__); \
-        else if (_g >= 2) EE_LAUNCH((KERNEL<ST, KS_, MT_, false, 2>), grid, block, s, __VA_ARGS__);   \
-        else EE_LAUNCH((KERNEL<ST, KS_, MT_, false, 1>), grid, block, s, __VA_ARGS__);                \
-    } while (0)
 
 // more dynamic LDS than the default limit has to be asked for once per kernel
 template <auto K>
@@ -1449,27 +1535,51 @@ static hipError_t lds_limit_once() {
         EE_LAUNCH_SM((KERNEL_INST), __VA_ARGS__);                               \
     } while (0)
 
-#define EE_DISPATCH(ST, KERNEL, ...)                                                                               \
-    do {                                                                                                           \
-        int _ks = ks_of(c);                                                                                        \
-        const int _mt = mt_of(c.T), _nt = c.N / 16;                                                                \
-        const size_t _sm = a_lds_bytes(c);                                                                         \
-        int _g = _sm ? 1 : g_of(_mt, _nt, c.min_wgs);                                                                        \
-        /* 1024 threads leave 128 registers per lane: 3..6 tiles need the 8-wave variants (each wave then */       \
-        /* streams K/8, still >= 8 k-tiles here); otherwise 16 waves stay at two tiles */                          \
-        if (_ks == 16 && _g >= 3) { if (_g <= 6 && _mt <= 2) _ks = 8; else _g = 2; }                               \
-        dim3 grid((_nt + _g - 1) / _g), block(_ks * 64);                                                           \
-        if (_sm) {                                                                                                 \
-            if (_ks == 4) EE_LAUNCH_LDS((KERNEL<ST, 4, 1, true, 1>), grid, block, _sm, s, __VA_ARGS__);            \
-            else if (_ks == 8) EE_LAUNCH_LDS((KERNEL<ST, 8, 1, true, 1>), grid, block, _sm, s, __VA_ARGS__);       \
-            else EE_LAUNCH_LDS((KERNEL<ST, 16, 1, true, 1>), grid, block, _sm, s, __VA_ARGS__);                    \
-        } else if (_ks == 4 && _mt == 1) EE_LAUNCH_G(ST, KERNEL, 4, 1, __VA_ARGS__);                               \
-        else if (_ks == 4 && _mt == 2) EE_LAUNCH_G(ST, KERNEL, 4, 2, __VA_ARGS__);                                 \
-        else if (_ks == 4) EE_LAUNCH_G(ST, KERNEL, 4, 4, __VA_ARGS__);                                             \
-        else if (_ks == 8 && _mt == 1) EE_LAUNCH_G(ST, KERNEL, 8, 1, __VA_ARGS__);                                 \
-        else if (_ks == 8 && _mt == 2) EE_LAUNCH_G(ST, KERNEL, 8, 2, __VA_ARGS__);                                 \
-        else if (_ks == 8) EE_LAUNCH_G(ST, KERNEL, 8, 4, __VA_ARGS__);                                             \
-        else EE_LAUNCH_G(ST, KERNEL, 16, 1, __VA_ARGS__);                                                          \
+template <int KS, int MT, int G, typename Epi>
+static hipError_t launch_rows_as(const GemmArgs& a, const Epi& e, hipStream_t s) {
+    constexpr size_t lds = (size_t)KS * G * MT * 1024;
+    static hipError_t once = hipFuncSetAttribute((const void*)rows_kernel<KS, MT, G, Epi>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (once != hipSuccess) return once;
+    EE_LAUNCH_SM((rows_kernel<KS, MT, G, Epi>), dim3((a.n_tiles + G - 1) / G), dim3(KS * 64), lds, s, a, e);
+    return hipGetLastError();
+}
+
+template <int KS, int MT, typename Epi>
+static hipError_t launch_rows_g(const GemmArgs& a, const Epi& e, int g, hipStream_t s) {
+    if constexpr (KS == 16) {
+        return g >= 2 ? launch_rows_as<KS, MT, 2>(a, e, s) : launch_rows_as<KS, MT, 1>(a, e, s);
+    } else {
+        switch (g) {
+            case 1: return launch_rows_as<KS, MT, 1>(a, e, s);
+            case 2: return launch_rows_as<KS, MT, 2>(a, e, s);
+            case 3: return launch_rows_as<KS, MT, 3>(a, e, s);
+            case 4: return launch_rows_as<KS, MT, 4>(a, e, s);
+            case 5: return launch_rows_as<KS, MT, 5>(a, e, s);
+            default: return launch_rows_as<KS, MT, 6>(a, e, s);
+        }
+    }
+}
+
+// a launch of many rows (A in operand order)
+template <typename Epi>
+static hipError_t launch_rows(const GemmCommon& c, const GemmArgs& a, const Epi& e, hipStream_t s) {
+    int ks = ks_of(c);
+    const int mt = mt_of(c.T), g = g_of(mt, a.n_tiles, c.min_wgs);
+    if (ks == 16 && g >= 3) ks = 8;  // (1024 threads leave 128 registers per lane: two tiles at most)
+    if (mt == 4) return launch_rows_g<4, 4>(a, e, g, s);
+    if (mt == 2) return ks == 4 ? launch_rows_g<4, 2>(a, e, g, s) : launch_rows_g<8, 2>(a, e, g, s);
+    return ks == 4 ? launch_rows_g<4, 1>(a, e, g, s) : ks == 8 ? launch_rows_g<8, 1>(a, e, g, s) : launch_rows_g<16, 1>(a, e, g, s);
+}
+
+// few rows, staged in LDS (the caller has made sure that they fit)
+#define EE_DISPATCH_LDS(KERNEL, ...)                                                                                                    \
+    do {                                                                                                                                \
+        const size_t _sm = a_lds_bytes(c.T, c.K);                                                                                             \
+        const int _ks = ks_of(c);                                                                                                       \
+        dim3 grid(c.N / 16), block(_ks * 64);                                                                                           \
+        if (_ks == 4) EE_LAUNCH_LDS((KERNEL<__bf16, 4, 1, true>), grid, block, _sm, s, __VA_ARGS__);                                 \
+        else if (_ks == 8) EE_LAUNCH_LDS((KERNEL<__bf16, 8, 1, true>), grid, block, _sm, s, __VA_ARGS__);                            \
+        else EE_LAUNCH_LDS((KERNEL<__bf16, 16, 1, true>), grid, block, _sm, s, __VA_ARGS__);                                         \
     } while (0)
 
 #define EE_DISPATCH_F32(KERNEL, ...)                                                             \
@@ -1483,14 +1593,6 @@ static hipError_t lds_limit_once() {
     } while (0)
 
 int gemm_resid_tiles_per_wg() { return 1; }
-
-bool gemm_rows_fit_lds(int dtype, int T, int K) {
-    GemmCommon c{};
-    c.dtype = dtype;
-    c.T = T;
-    c.K = K;
-    return a_lds_bytes(c) != 0;
-}
 
 // Rows are processed in passes of at most 64 (the largest row tile count the kernels are built for).
 constexpr int PASS_ROWS = 64;
@@ -1522,7 +1624,12 @@ hipError_t launch_gemm_qkv(const GemmCommon& cc, void* q, size_t q_lo, const flo
             QkvArgs<__bf16> e{(__bf16*)q + (size_t)r0 * d, q_lo, d, (const float2*)rope_cs,
                               (__bf16*)kv.pool + (size_t)layer * kv.layer_stride, kv.blk_stride, kv.H, kv.hd, kv.BT, pos, blk,
                               c.desc_host ? c.desc_host->pos[r0] : 0, c.desc_host ? c.desc_host->kvblk[r0] : 0};
-            EE_DISPATCH(__bf16, gemm_qkv_kernel, a, e);
+            if (c.a_packed) {
+                const hipError_t err = launch_rows(c, a, RowsQkv{e}, s);
+                if (err != hipSuccess) return err;
+                continue;
+            }
+            EE_DISPATCH_LDS(gemm_qkv_kernel, a, e);
         } else {
             QkvArgs<float> e{(float*)q + (size_t)r0 * d, q_lo, d, (const float2*)rope_cs,
                              (float*)kv.pool + (size_t)layer * kv.layer_stride, kv.blk_stride, kv.H, kv.hd, kv.BT, pos, blk, 0, 0};
@@ -1549,8 +1656,8 @@ hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh
         const int32_t* xrow = desc_array(c.desc, offsetof(SegDesc, xrow), r0);
         if (c.dtype == EE_BF16 && c.att_part != nullptr) {
             // input still lies as attention split partials: only the few-rows variant can merge them
-            const size_t sm = a_lds_bytes(c);
-            if (sm == 0 || cc.T > PASS_ROWS) return hipErrorInvalidValue;
+            const size_t sm = a_lds_bytes(c.T, c.K);
+            if (c.a_packed || cc.T > PASS_ROWS) return hipErrorInvalidValue;
             ResidArgs<__bf16> e{x, (__bf16*)xg, (__bf16*)xgh, xs_lo, ssq_out, c.ssq_stride, g_next, g_head, d, xrow, nullptr, 0, 0, {}};
             fill_rows(e, c, cc.T);
             // (at most 8 waves: the merge holds every split's partials in registers at once)
@@ -1565,7 +1672,12 @@ hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh
             __bf16* pk = xg_pk ? (__bf16*)xg_pk + (size_t)(r0 / 16) * (d / 32) * 512 : nullptr;
             ResidArgs<__bf16> e{x, (__bf16*)xg, (__bf16*)xgh, xs_lo, ssq_out, c.ssq_stride, g_next, g_head, d, xrow, pk, xg_pk_lo, 0, {}};
             fill_rows(e, c, cc.T);
-            EE_DISPATCH(__bf16, gemm_resid_kernel, a, e);
+            if (c.a_packed) {
+                const hipError_t err = launch_rows(c, a, RowsResid{e}, s);
+                if (err != hipSuccess) return err;
+                continue;
+            }
+            EE_DISPATCH_LDS(gemm_resid_kernel, a, e);
         } else {
             ResidArgs<float> e{x, (float*)xg, (float*)xgh, xs_lo, ssq_out, c.ssq_stride, g_next, g_head, d, xrow, nullptr, 0, 0, {}};
             fill_rows(e, c, cc.T);
@@ -1583,7 +1695,12 @@ hipError_t launch_gemm_swiglu(const GemmCommon& cc, void* act, size_t act_lo, in
         GemmArgs a = make_args(c);
         if (c.dtype == EE_BF16) {
             __bf16* ap = act_packed ? (__bf16*)act + (size_t)(r0 / 16) * (F / 32) * 512 : (__bf16*)act + (size_t)r0 * F;
-            EE_DISPATCH(__bf16, gemm_swiglu_kernel, a, ap, act_lo, F, act_packed ? F / 32 : 0);
+            if (c.a_packed) {
+                const hipError_t err = launch_rows(c, a, RowsSwiglu{ap, act_lo, F, act_packed ? F / 32 : 0}, s);
+                if (err != hipSuccess) return err;
+                continue;
+            }
+            EE_DISPATCH_LDS(gemm_swiglu_kernel, a, ap, act_lo, F, act_packed ? F / 32 : 0);
         } else {
             EE_DISPATCH_F32(gemm_swiglu_kernel, a, (float*)act + (size_t)r0 * F, act_lo, F, 0);
         }
@@ -1601,7 +1718,12 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t*
     GemmArgs a = make_args(c);
     HeadArgs e{partials, logits, c.N};
     if (c.dtype == EE_BF16) {
-        EE_DISPATCH(__bf16, gemm_head_kernel, a, e);
+        if (c.a_packed) {
+            const hipError_t err = launch_rows(c, a, RowsHead{e}, s);
+            if (err != hipSuccess) return err;
+        } else {
+            EE_DISPATCH_LDS(gemm_head_kernel, a, e);
+        }
     } else {
         EE_DISPATCH_F32(gemm_head_kernel, a, e);
     }
