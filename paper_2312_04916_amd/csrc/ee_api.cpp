@@ -110,7 +110,7 @@ struct WorkspaceLayout {
     int max_blocks_per_seq;
     // prompt phase (bf16 model): buffers for pf_rows positions at a time, activations in the packed operand layout
     int pf_rows;  // 0: the prompt phase runs through the decode kernels in chunks
-    size_t pf_begin, pf_tokens, pf_x, pf_xg, pf_xgh, pf_q, pf_attn, pf_act, pf_ssq, pf_ssqe, pf_partials, pf_tok, pf_conf, pf_tgt, pf_zt, pf_nll;
+    size_t pf_begin, pf_tokens, pf_x, pf_xg, pf_xgh, pf_q, pf_attn, pf_act, pf_ssq, pf_ssqe, pf_partials, pf_tok, pf_conf, pf_tgt, pf_zt, pf_nll, pf_part;
 };
 
 // Rows per pass of the prompt-phase GEMM path; 0 when the model does not qualify (fp32, or widths the
@@ -171,6 +171,7 @@ WorkspaceLayout workspace_layout(const ee_config& c, int max_rows, int max_seqs)
         w.pf_tgt = take(Mp * 4);   // per row: the next token of the prompt (scoring its log-likelihood)
         w.pf_zt = take(Mp * 4);    // its logit
         w.pf_nll = take(Mp * 4);
+        w.pf_part = take(pf_part_bytes((int)Mp, (int)std::max(3 * d, 2 * F)));
     }
     w.total = off;
     return w;
@@ -977,6 +978,7 @@ int prefill_large(ee_model* m, ee_kv_cache* c, int seq, const int32_t* tokens, i
     EECHK(upload(m, st));
     const int32_t* bt = m->dev_btab();
     PfGemm g{};
+    g.part = ws + w.pf_part;
     g.inv_d = 1.0f / (float)d;
     g.eps = cf.rms_eps;
     g.ssq_n = ssq_n;

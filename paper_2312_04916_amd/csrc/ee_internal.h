@@ -136,7 +136,9 @@ struct PfGemm {
     int ssq_n;
     float inv_d, eps;
     int M;            // rows
+    void* part;       // scratch of pf_part_bytes() for partial sums where the contraction is split over workgroups
 };
+size_t pf_part_bytes(int max_rows, int max_N);
 hipError_t launch_pf_embed(const void* embed, const int32_t* dev_tokens, int M, int d, const float* g_next, float* x, void* xg_hi,
                            void* xg_lo, float* ssq, int ssq_n, hipStream_t s);
 hipError_t launch_pf_qkv(const PfGemm& g, void* q_hi, void* q_lo, const float* rope_cs, const KvGeom& kv, int layer, const int32_t* bt,

@@ -14,6 +14,8 @@
 // activation operand, of a K-cache row, or of a packed q row.
 #include "ee_internal.h"
 
+#include <algorithm>
+
 #include "ee_lanes.h"
 #include "ee_launch.h"
 
@@ -30,6 +32,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 namespace {
 
 constexpr int PF_NTL = 16;  // 16-column weight tiles per workgroup (256 output features)
+constexpr int PF_WNF = 4;   // weight tiles per wave
 
 // element index of (row m, feature k) in a packed activation array with KT = K/32 tiles per row group
 __device__ __forceinline__ size_t pk_index(int m, int k, int KT) {
@@ -70,6 +73,7 @@ struct PfArgs {
     const u32x4* Xl;
     int KT, n_tiles, m_tiles;  // valid 16-wide tiles of W and X (loads of tiles beyond them are clamped)
     int n_wgN, n_wgM;
+    int unit;  // k-tiles per workgroup where the contraction is split over workgroups (see pf_part_kernel)
     int M, N;
     const float* ssq;  // [rows][ssq_n] partial sums of squares of the rows of X before their gain, or NULL
     int ssq_n;
@@ -81,15 +85,15 @@ struct PfArgs {
 // activations.  Tile = 256 features x MTL*16 rows; K advances 32 per stage; the stages are filled by direct
 // global->LDS copies that run ahead of the MFMAs.
 // ---------------------------------------------------------------------------------------------------
-// NWAVE waves per workgroup, arranged (NWAVE/2) along the features x 2 along the rows: a wave owns
-// WNF = 32/NWAVE weight tiles and MTL/2 row tiles.  A single wave per SIMD cannot issue 16x16x32 MFMAs back to
-// back fast enough to keep the matrix core busy, and the more waves share a SIMD the better it is fed: the QKV and
-// gate|up GEMMs run 8 waves with two workgroups per CU (four waves per SIMD), and so does the head GEMM; the residual
-// GEMMs (a grid of one workgroup per CU at 1024 rows, and an epilogue that needs more registers) run 8 waves with one
-// workgroup per CU and a deeper ring.
+// 8 waves per workgroup, arranged 4 along the features x 2 along the rows: a wave owns 4 weight tiles and MTL/2 row tiles.
+// A single wave per SIMD cannot issue 16x16x32 MFMAs back to back fast enough to keep the matrix core busy, and the more
+// waves share a SIMD the better it is fed: the QKV and gate|up GEMMs run two workgroups per CU (four waves per SIMD), and
+// so does the head GEMM; the residual GEMMs (a grid of one workgroup per CU at 1024 rows, and an epilogue that needs more
+// registers) and the partial sums of short prompts run one workgroup per CU and a deeper ring.
 template <int MTL>
 struct PfTile {
     int nt0, mt0, n_wg, wn, wm;
+    int kt0, nkt;  // k-tiles to work through
 };
 
 template <int MTL, int NWAVE>
@@ -100,6 +104,8 @@ __device__ __forceinline__ bool pf_tile_of(const PfArgs& a, PfTile<MTL>& t) {
     t.n_wg = (j / a.n_wgM) * 8 + xcd;
     const int m_wg = j % a.n_wgM;
     if (t.n_wg >= a.n_wgN) return false;
+    t.kt0 = 0;
+    t.nkt = a.KT;
     t.nt0 = t.n_wg * PF_NTL;
     t.mt0 = m_wg * MTL;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -113,15 +119,14 @@ __device__ __forceinline__ bool pf_tile_of(const PfArgs& a, PfTile<MTL>& t) {
 //    workgroup's MFMAs cover this one's barriers and copy waits, so few stages suffice (2 for the 128-row tile, 3
 //    for the 64-row tile, which also has room for a second operand set in registers);
 //  - otherwise one workgroup per CU with four stages and two operand sets (the residual epilogue needs the registers).
-// The head GEMM (4 waves, two workgroups per CU, 2 stages) is its own case.
 // (LO = false: the activations' hi term only, 24 KB instead of 32 KB per stage of the 128-row tile, so three stages fit twice)
 template <int MTL, int NWAVE, bool WIDE, bool LO = true>
 constexpr int pf_stages() {
-    return NWAVE == 4 ? 2 : (WIDE ? (MTL == 8 && LO ? 2 : 3) : 4);
+    return WIDE ? (MTL == 8 && LO ? 2 : 3) : 4;
 }
 template <int MTL, int NWAVE, bool WIDE>
 constexpr bool pf_pipe() {  // (the residual epilogue overrides this for its two-workgroups-per-CU variant)
-    return NWAVE == 8 && MTL == 4;
+    return false;
 }
 
 // The operand reads and the wait counts are written by hand: the compiler would make every LDS read wait
@@ -137,9 +142,9 @@ __device__ __forceinline__ void pf_wait_vm() {
 
 template <int MTL, int NWAVE, bool WIDE, bool PIPE = pf_pipe<MTL, NWAVE, WIDE>(), bool LO = true>
 __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& t, u32x4* lds, float* rs,
-                                            f32x4 (&acc)[32 / NWAVE][MTL / 2]) {
-    constexpr int WNF = 32 / NWAVE;
-    constexpr int NF = PF_NTL + (LO ? 2 : 1) * MTL;  // fragments (1 KB each) per stage
+                                            f32x4 (&acc)[PF_WNF][MTL / 2]) {
+    constexpr int WNF = PF_WNF, NTL = PF_NTL;
+    constexpr int NF = NTL + (LO ? 2 : 1) * MTL;     // fragments (1 KB each) per stage
     constexpr int FPW = NF / NWAVE;                  // copied per wave
     constexpr int NST = pf_stages<MTL, NWAVE, WIDE, LO>();
     static_assert(LO || !PIPE, "the single-term loop has one operand set");
@@ -149,20 +154,20 @@ __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& 
     constexpr int MW = MTL / 2;
     static_assert(MW == 2 || MW == 4, "row tiles per wave");
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const int KT = a.KT;
+    const int KT = t.nkt;
     const u32x4* src[FPW];
 #pragma unroll
     for (int i = 0; i < FPW; ++i) {
         const int f = wave * FPW + i;
-        if (f < PF_NTL) {
+        if (f < NTL) {
             int tt = t.nt0 + f;
             if (tt >= a.n_tiles) tt = a.n_tiles - 1;
-            src[i] = a.W + (size_t)tt * KT * 64 + lane;
+            src[i] = a.W + ((size_t)tt * a.KT + t.kt0) * 64 + lane;
         } else {
-            const int g = f - PF_NTL;  // (g < MTL always in the single-term loop)
+            const int g = f - NTL;  // (g < MTL always in the single-term loop)
             int mt = t.mt0 + (g < MTL ? g : g - MTL);
             if (mt >= a.m_tiles) mt = a.m_tiles - 1;
-            src[i] = (g < MTL ? a.Xh : a.Xl) + (size_t)mt * KT * 64 + lane;
+            src[i] = (g < MTL ? a.Xh : a.Xl) + ((size_t)mt * a.KT + t.kt0) * 64 + lane;
         }
     }
     auto issue = [&](int st, int kt) {
@@ -192,7 +197,7 @@ __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& 
 #pragma unroll
     for (int p = 0; p < NST - 1; ++p) issue(p, p < KT ? p : KT - 1);
     const unsigned lds0 = (unsigned)(size_t)EE_LDS_PTR(lds) + lane * 16;
-    const unsigned woff = t.wn * WNF * 1024, xoff = (PF_NTL + t.wm * MW) * 1024;
+    const unsigned woff = t.wn * WNF * 1024, xoff = (NTL + t.wm * MW) * 1024;
     int st_r = 0, st_w = NST - 1;
     struct Frags {
         u32x4 wf[WNF], xh[MW], xl[MW];
@@ -204,9 +209,6 @@ __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& 
         __builtin_amdgcn_s_barrier();      // ... and everybody else's; the buffer refilled below is no longer read
         const unsigned wb = lds0 + st_r * (STAGE * 16) + woff, xb = lds0 + st_r * (STAGE * 16) + xoff;
         PF_DSR(f.wf[0], wb, 0); PF_DSR(f.wf[1], wb, 1024); PF_DSR(f.wf[2], wb, 2048); PF_DSR(f.wf[3], wb, 3072);
-        if constexpr (WNF == 8) {
-            PF_DSR(f.wf[4], wb, 4096); PF_DSR(f.wf[5], wb, 5120); PF_DSR(f.wf[6], wb, 6144); PF_DSR(f.wf[7], wb, 7168);
-        }
         PF_DSR(f.xh[0], xb, 0); PF_DSR(f.xh[1], xb, 1024);
         if constexpr (MW == 4) {
             PF_DSR(f.xh[2], xb, 2048); PF_DSR(f.xh[3], xb, 3072);
@@ -224,17 +226,10 @@ __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& 
     // the operands are in registers after this (and the MFMAs that use them may not move above it)
     auto landed = [&](Frags& f) {
         if constexpr (!LO) {
-            static_assert(LO || (WNF == 4 && MW == 4), "single-term loop: 8 waves on the 128-row tile");
+            static_assert(LO || MW == 4, "single-term loop: the 128-row tile");
             asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.wf[0]), "+v"(f.wf[1]), "+v"(f.wf[2]), "+v"(f.wf[3]), "+v"(f.xh[0]), "+v"(f.xh[1]),
                          "+v"(f.xh[2]), "+v"(f.xh[3]));
-        } else if constexpr (WNF == 8 && MW == 4)
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.wf[0]), "+v"(f.wf[1]), "+v"(f.wf[2]), "+v"(f.wf[3]), "+v"(f.wf[4]), "+v"(f.wf[5]),
-                         "+v"(f.wf[6]), "+v"(f.wf[7]), "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xh[2]), "+v"(f.xh[3]), "+v"(f.xl[0]),
-                         "+v"(f.xl[1]), "+v"(f.xl[2]), "+v"(f.xl[3]));
-        else if constexpr (WNF == 8)
-            asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.wf[0]), "+v"(f.wf[1]), "+v"(f.wf[2]), "+v"(f.wf[3]), "+v"(f.wf[4]), "+v"(f.wf[5]),
-                         "+v"(f.wf[6]), "+v"(f.wf[7]), "+v"(f.xh[0]), "+v"(f.xh[1]), "+v"(f.xl[0]), "+v"(f.xl[1]));
-        else if constexpr (MW == 4)
+        } else if constexpr (MW == 4)
             asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(f.wf[0]), "+v"(f.wf[1]), "+v"(f.wf[2]), "+v"(f.wf[3]), "+v"(f.xh[0]), "+v"(f.xh[1]),
                          "+v"(f.xh[2]), "+v"(f.xh[3]), "+v"(f.xl[0]), "+v"(f.xl[1]), "+v"(f.xl[2]), "+v"(f.xl[3]));
         else
@@ -424,70 +419,85 @@ struct PfQkv {
     int p0;             // position of row 0 (multiple of 16)
 };
 
+// One position's row of the epilogue: what depends on the position alone is formed once for all its tiles.
+struct PfQkvRow {
+    int m, pos, blk, pin;
+    float r;  // RMS scale
+};
+__device__ __forceinline__ PfQkvRow pf_qkv_row(const PfQkv& e, int m, float r) {
+    PfQkvRow w;
+    w.m = m;
+    w.r = r;
+    w.pos = e.p0 + m;
+    w.blk = e.bt[w.pos / e.BT];
+    w.pin = w.pos % e.BT;
+    return w;
+}
+
+// Tile T of the packed q|k|v matrix: lane (row li, group rg) holds features rg*4..rg*4+3 of it for its position.
+__device__ __forceinline__ void pf_qkv_store(const PfQkv& e, const PfQkvRow& w, int T, const f32x4& a, int rg) {
+    const int tiles_per_part = e.d / 16, per_head = e.hd / 16, half = e.hd / 2;
+    const bool is_hi = rg >= 2;
+    const int part = T / tiles_per_part, rem = T % tiles_per_part;
+    const int h = rem / per_head, c = rem % per_head;
+
+    if (part < 2) {
+        // rows 0-7 of the tile = features c*8.., rows 8-15 = their rotary partners
+        const f32x4 v = a * w.r;
+        f32x4 o;
+        // (a lane swap instead of this shuffle costs the kernel eight more live registers, which it does not have:
+        // 48 spilled, four times the run time)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = __shfl_xor(v[q], 32);
+        const int fi = c * 8 + (rg & 1) * 4;
+        const f32x4 cs0 = *(const f32x4*)(e.rope_cs + (size_t)w.pos * half + fi);
+        const f32x4 cs1 = *(const f32x4*)(e.rope_cs + (size_t)w.pos * half + fi + 2);
+        const float cx[4] = {cs0[0], cs0[2], cs1[0], cs1[2]}, sx[4] = {cs0[1], cs0[3], cs1[1], cs1[3]};
+        float res[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) res[q] = is_hi ? v[q] * cx[q] + o[q] * sx[q] : v[q] * cx[q] - o[q] * sx[q];
+        const int f = fi + (is_hi ? half : 0);
+        if (part == 0) {
+            pk_store4(e.q_hi, e.q_lo, w.m, h * e.hd + f, e.d / 32, res);
+        } else {
+            __bf16* kp = e.kv_layer + (size_t)w.blk * e.blk_stride + ((size_t)h * e.BT + w.pin) * e.hd + f;
+            bf16x4 kb;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) kb[q] = (__bf16)res[q];
+            *(bf16x4*)kp = kb;
+        }
+    } else {
+        // V block, transposed [head][position / 32][feature][position % 32]: four 2-byte stores per lane; the
+        // 16 lanes of a group cover 16 consecutive positions of one feature
+        const int f = c * 8 + (rg & 1) * 4 + (is_hi ? half : 0);
+        __bf16* vp = e.kv_layer + (size_t)w.blk * e.blk_stride + (size_t)e.H * e.BT * e.hd + (size_t)h * e.hd * e.BT +
+                     (size_t)(w.pin >> 5) * (e.hd * 32) + f * 32 + (w.pin & 31);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) vp[q * 32] = (__bf16)(a[q] * w.r);
+    }
+}
+
 template <int MTL, int NWAVE>
 __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_qkv_kernel(PfArgs a, PfQkv e) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
     if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
-    constexpr int WNF = 32 / NWAVE;
     constexpr int MW = MTL / 2;
     float* rs = pf_rs_ptr<MTL, NWAVE, true>(pf_lds);
-    const int tiles_per_part = e.d / 16, per_head = e.hd / 16, half = e.hd / 2;
-    f32x4 acc[WNF][MW];
-    pf_mainloop<MTL, NWAVE, true>(a, t, pf_lds, rs, acc);
+    f32x4 acc[PF_WNF][MW];
+    pf_mainloop<MTL, NWAVE, true, MTL == 4>(a, t, pf_lds, rs, acc);
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
-    const int KTd = e.d / 32;
-    // (row tiles outside, weight tiles inside: what depends on the position alone, its cache block, its place in the
-    // block and its RMS scale, is formed once per row instead of once per tile)
+    // (row tiles outside, weight tiles inside: a row's look-ups are made once)
 #pragma unroll
     for (int j = 0; j < MW; ++j) {
         const int ml = (t.wm * MW + j) * 16 + li, m = t.mt0 * 16 + ml;
         if (m >= a.M) continue;
-        const float r = rs[ml];
-        const int pos = e.p0 + m;
-        const int blk = e.bt[pos / e.BT], pin = pos % e.BT;
-        const bool is_hi = rg >= 2;
+        const PfQkvRow w = pf_qkv_row(e, m, rs[ml]);
 #pragma unroll
-        for (int i = 0; i < WNF; ++i) {
-            const int T = t.nt0 + t.wn * WNF + i;
+        for (int i = 0; i < PF_WNF; ++i) {
+            const int T = t.nt0 + t.wn * PF_WNF + i;
             if (T >= a.n_tiles) continue;  // (uniform over the wave)
-            const int part = T / tiles_per_part, rem = T % tiles_per_part;
-            const int h = rem / per_head, c = rem % per_head;
-            if (part < 2) {
-                // lane: features rg*4..rg*4+3 of the tile (rows 0-7 = features c*8.., rows 8-15 = their rotary
-                // partners) for position m
-                f32x4 v = acc[i][j] * r;
-                f32x4 o;
-                // (a lane swap instead of this shuffle costs the kernel eight more live registers, which it does not have:
-                // 48 spilled, four times the run time)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) o[q] = __shfl_xor(v[q], 32);
-                const int fi = c * 8 + (rg & 1) * 4;
-                const f32x4 cs0 = *(const f32x4*)(e.rope_cs + (size_t)pos * half + fi);
-                const f32x4 cs1 = *(const f32x4*)(e.rope_cs + (size_t)pos * half + fi + 2);
-                const float cx[4] = {cs0[0], cs0[2], cs1[0], cs1[2]}, sx[4] = {cs0[1], cs0[3], cs1[1], cs1[3]};
-                float res[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) res[q] = is_hi ? v[q] * cx[q] + o[q] * sx[q] : v[q] * cx[q] - o[q] * sx[q];
-                const int f = fi + (is_hi ? half : 0);
-                if (part == 0) {
-                    pk_store4(e.q_hi, e.q_lo, m, h * e.hd + f, KTd, res);
-                } else {
-                    __bf16* kp = e.kv_layer + (size_t)blk * e.blk_stride + ((size_t)h * e.BT + pin) * e.hd + f;
-                    bf16x4 kb;
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) kb[q] = (__bf16)res[q];
-                    *(bf16x4*)kp = kb;
-                }
-            } else {
-                // V block, transposed [head][position / 32][feature][position % 32]: four 2-byte stores per lane; the
-                // 16 lanes of a group cover 16 consecutive positions of one feature
-                const int f = c * 8 + (rg & 1) * 4 + (is_hi ? half : 0);
-                __bf16* vp = e.kv_layer + (size_t)blk * e.blk_stride + (size_t)e.H * e.BT * e.hd + (size_t)h * e.hd * e.BT +
-                             (size_t)(pin >> 5) * (e.hd * 32) + f * 32 + (pin & 31);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) vp[q * 32] = (__bf16)(acc[i][j][q] * r);
-            }
+            pf_qkv_store(e, w, T, acc[i][j], rg);
         }
     }
 }
@@ -504,8 +514,8 @@ struct PfResid {
 // (waves with active == false hold no sums: they only keep the barriers company)
 template <int MTL, int NWAVE>
 __device__ __forceinline__ void pf_resid_epilogue(const PfArgs& a, const PfResid& e, const PfTile<MTL>& t, const float* rs, float* red,
-                                                  const f32x4 (&acc)[32 / NWAVE][MTL / 2], bool active = true) {
-    constexpr int WNF = 32 / NWAVE;
+                                                  const f32x4 (&acc)[PF_WNF][MTL / 2], bool active = true) {
+    constexpr int WNF = PF_WNF;
     constexpr int MW = MTL / 2;
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     const int KTd = e.d / 32;
@@ -569,7 +579,7 @@ __global__ __launch_bounds__(NWAVE * 64, WIDE ? 4 : 2) void pf_resid_kernel(PfAr
     if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
     float* rs = pf_rs_ptr<MTL, NWAVE, WIDE>(pf_lds);
     float* red = rs + MTL * 16;  // [NWAVE/2][MTL*16]
-    f32x4 acc[32 / NWAVE][MTL / 2];
+    f32x4 acc[PF_WNF][MTL / 2];
     pf_mainloop<MTL, NWAVE, WIDE, (!WIDE && MTL == 4)>(a, t, pf_lds, rs, acc);  // (two operand sets need 152 registers here)
     pf_resid_epilogue<MTL, NWAVE>(a, e, t, rs, red, acc);
 }
@@ -590,43 +600,204 @@ __global__ __launch_bounds__(1024, 4) void pf_resid_k16_kernel(PfArgs a, PfResid
     pf_resid_epilogue<4, 8>(a, e, t, rs, red, acc, kh == 0);
 }
 
+// SwiGLU of tile T of the packed gate|up matrix.  The gate features sit in the lower 32 lanes, their up partners in the
+// upper 32.  Both halves get both (a lane swap each) and share the work: the lower half forms features 0 and 1 of its four,
+// the upper half 2 and 3.  Hardware exponential and reciprocal (a few 1e-7 relative: the results are kept to 16 mantissa
+// bits); with the library routines and one half idle this epilogue was 8 % of the kernel.
+__device__ __forceinline__ void pf_swiglu_store(__bf16* act_hi, __bf16* act_lo, int m, bool valid, int T, int KTf, f32x4 v, int rg) {
+    float gq[4], uq[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) halves_of(v[q], gq[q], uq[q]);
+    const bool upper = rg >= 2;
+    const float g0 = upper ? gq[2] : gq[0], g1 = upper ? gq[3] : gq[1];
+    const float u0 = upper ? uq[2] : uq[0], u1 = upper ? uq[3] : uq[1];
+    if (valid)
+        pk_store2(act_hi, act_lo, m, T * 8 + (rg & 1) * 4 + (upper ? 2 : 0), KTf, __fdividef(g0, 1.0f + __expf(-g0)) * u0,
+                  __fdividef(g1, 1.0f + __expf(-g1)) * u1);
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Few rows: a grid of one workgroup per 256 columns and row tile leaves CUs idle (32 workgroups for the residual GEMMs at
+// 99 rows of the 7B widths), and what a CU can take in through its vector memory path, not HBM, is what such a launch
+// waits for (30 to 40 GB/s per CU; neither deeper rings nor narrower tiles, which take in the rows more often, help).
+// So the work is cut evenly over the CUs instead: the k-tiles of all result tiles stand behind each other, workgroup w
+// takes a.unit of them from w * unit on, and leaves the sums of each result tile that its range touches (at most two) in
+// `part`; a second kernel adds a tile's parts in the order of K and runs the epilogue.  The parts of workgroup w of result
+// tile p lie at slot w + p (both only grow along the line, so no two share one), as they stand in the registers:
+// [16 weight tiles][MTL row tiles][64 lanes] of four floats, 1 KB per wave store.
+// ---------------------------------------------------------------------------------------------------
+template <int MTL>
+__global__ __launch_bounds__(512, 2) void pf_part_kernel(PfArgs a, f32x4* __restrict__ part) {
+    extern __shared__ u32x4 pf_lds[];
+    constexpr int MW = MTL / 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    // an XCD's workgroups take neighbouring ranges, so that the row tiles of a column panel share its L2
+    const int w = (int)(blockIdx.x & 7) * ((int)gridDim.x >> 3) + (int)(blockIdx.x >> 3);
+    const int total = a.n_wgN * a.n_wgM * a.KT;
+    int at = w * a.unit;
+    const int end = at + a.unit < total ? at + a.unit : total;
+    while (at < end) {
+        const int p = at / a.KT;
+        PfTile<MTL> t;
+        t.n_wg = p / a.n_wgM;
+        t.nt0 = t.n_wg * PF_NTL;
+        t.mt0 = (p % a.n_wgM) * MTL;
+        t.wn = wave % 4;
+        t.wm = wave / 4;
+        t.kt0 = at - p * a.KT;
+        t.nkt = (end - at < a.KT - t.kt0) ? end - at : a.KT - t.kt0;
+        f32x4 acc[PF_WNF][MW];
+        pf_mainloop<MTL, 8, false, MTL == 4>(a, t, pf_lds, pf_rs_ptr<MTL, 8, false>(pf_lds), acc);  // (a.ssq is NULL)
+        f32x4* o = part + ((size_t)(w + p) * (PF_NTL * MTL) + t.wn * (PF_WNF * MTL) + t.wm * MW) * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < PF_WNF; ++i)
+#pragma unroll
+            for (int j = 0; j < MW; ++j) o[(i * MTL + j) * 64] = acc[i][j];
+        at += t.nkt;
+    }
+}
+
+// Sums of N neighbouring weight tiles T0.. (of one panel) and row tile mt, in the order of K.  All the loads of up to eight
+// parts go out before the first is used.
+template <int N>
+__device__ __forceinline__ void pf_sum_parts(const PfArgs& a, int MTL, const f32x4* __restrict__ part, int mt, int T0, int lane, f32x4 (&v)[N]) {
+    const int p = (T0 / PF_NTL) * a.n_wgM + mt / MTL;
+    const int w0 = p * a.KT / a.unit, n = ((p + 1) * a.KT - 1) / a.unit - w0 + 1;
+    const size_t slot = (size_t)PF_NTL * MTL * 64;
+    const f32x4* q = part + (size_t)(w0 + p) * slot + ((T0 % PF_NTL) * MTL + mt % MTL) * 64 + lane;
+#pragma unroll
+    for (int i = 0; i < N; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s = 0; s < n; s += 8) {
+        f32x4 u[8][N];
+#pragma unroll
+        for (int h = 0; h < 8; h += 4)
+            if (s + h < n) {  // (uniform)
+#pragma unroll
+                for (int k = h; k < h + 4; ++k)
+#pragma unroll
+                    for (int i = 0; i < N; ++i) u[k][i] = q[(size_t)(s + k < n ? s + k : s) * slot + i * MTL * 64];
+            }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (s + k < n) v[i] += u[k][i];
+    }
+}
+
+// 16 rows x 256 columns per workgroup, a wave two tiles
+__global__ __launch_bounds__(512) void pf_resid_sum_kernel(PfArgs a, PfResid e, int MTL, const f32x4* __restrict__ part) {
+    __shared__ float red[8][16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
+    const int cg = blockIdx.x % a.n_wgN, mt = blockIdx.x / a.n_wgN;
+    const int m = mt * 16 + li, KTd = e.d / 32, T0 = cg * PF_NTL + wave * 2;
+    float sq = 0.f;
+    f32x4 v[2], xv[2], gn[2], gh[2];
+    if (T0 < a.n_tiles) {  // (the number of tiles is even)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int n = (T0 + i) * 16 + rg * 4;
+            xv[i] = *(const f32x4*)(e.x + (size_t)(m < a.M ? m : a.M - 1) * e.d + n);
+            gn[i] = *(const f32x4*)(e.g_next + n);
+            gh[i] = e.g_head ? *(const f32x4*)(e.g_head + n) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+        pf_sum_parts<2>(a, MTL, part, mt, T0, lane, v);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int n = (T0 + i) * 16 + rg * 4;
+            if (m >= a.M) continue;
+            v[i] += xv[i];
+            *(f32x4*)(e.x + (size_t)m * e.d + n) = v[i];
+            float o[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                o[q] = v[i][q] * gn[i][q];
+                sq += v[i][q] * v[i][q];
+            }
+            pk_store4(e.xg_hi, e.xg_lo, m, n, KTd, o);
+            if (e.g_head) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) o[q] = v[i][q] * gh[i][q];
+                pk_store4(e.xgh_hi, e.xgh_lo, m, n, KTd, o);
+            }
+        }
+    }
+    sq = rows4_sum(sq);
+    if (rg == 0) red[wave][li] = sq;
+    __syncthreads();
+    if (threadIdx.x < 16 && mt * 16 + (int)threadIdx.x < a.M) {
+        float sum = red[0][threadIdx.x];
+#pragma unroll
+        for (int w = 1; w < 8; ++w) sum += red[w][threadIdx.x];
+        e.ssq_out[(size_t)(mt * 16 + threadIdx.x) * e.ssq_n_out + cg] = sum;
+    }
+}
+
+// RMS scale of row m from its partial sums: the lanes (row, rg = 0..3) of a wave take every fourth each
+__device__ __forceinline__ float pf_row_scale(const PfArgs& a, int m, int rg) {
+    const float* p = a.ssq + (size_t)m * a.ssq_n;
+    float s = 0.f;
+    for (int i0 = rg; i0 < a.ssq_n; i0 += 32) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = p[i0 + 4 * u < a.ssq_n ? i0 + 4 * u : i0];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+            if (i0 + 4 * u < a.ssq_n) s += v[u];
+    }
+    return 1.0f / sqrtf(rows4_sum(s) * a.inv_d + a.eps);
+}
+
+// 16 rows x 128 columns per workgroup, a wave two tiles
+__global__ __launch_bounds__(256) void pf_qkv_sum_kernel(PfArgs a, PfQkv e, int MTL, const f32x4* __restrict__ part) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
+    const int n_cg = (a.n_tiles + 7) / 8, cg = blockIdx.x % n_cg, mt = blockIdx.x / n_cg;
+    const int m = mt * 16 + li, mv = m < a.M ? m : a.M - 1, T0 = cg * 8 + wave * 2;
+    if (T0 >= a.n_tiles) return;
+    const float r = pf_row_scale(a, mv, rg);
+    const PfQkvRow w = pf_qkv_row(e, mv, r);
+    f32x4 v[2];
+    pf_sum_parts<2>(a, MTL, part, mt, T0, lane, v);
+    if (m >= a.M) return;
+    pf_qkv_store(e, w, T0, v[0], rg);
+    pf_qkv_store(e, w, T0 + 1, v[1], rg);
+}
+
+__global__ __launch_bounds__(256) void pf_swiglu_sum_kernel(PfArgs a, __bf16* act_hi, __bf16* act_lo, int F, int MTL,
+                                                            const f32x4* __restrict__ part) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
+    const int n_cg = (a.n_tiles + 7) / 8, cg = blockIdx.x % n_cg, mt = blockIdx.x / n_cg;
+    const int m = mt * 16 + li, T0 = cg * 8 + wave * 2;
+    if (T0 >= a.n_tiles) return;
+    const float r = pf_row_scale(a, m < a.M ? m : a.M - 1, rg);
+    f32x4 v[2];
+    pf_sum_parts<2>(a, MTL, part, mt, T0, lane, v);
+    pf_swiglu_store(act_hi, act_lo, m, m < a.M, T0, F / 32, v[0] * r, rg);
+    pf_swiglu_store(act_hi, act_lo, m, m < a.M, T0 + 1, F / 32, v[1] * r, rg);
+}
+
 // ---- epilogue 3: SwiGLU.  Tile j of the packed gate|up matrix: rows 0-7 gate features 8j.., rows 8-15 the up features
 template <int MTL, int NWAVE>
 __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_swiglu_kernel(PfArgs a, __bf16* act_hi, __bf16* act_lo, int F) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
     if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
-    constexpr int WNF = 32 / NWAVE;
     constexpr int MW = MTL / 2;
     float* rs = pf_rs_ptr<MTL, NWAVE, true>(pf_lds);
-    f32x4 acc[WNF][MW];
+    f32x4 acc[PF_WNF][MW];
     // One operand set for both tiles: with two, the 64-row tile's epilogue put 24 registers of the main loop into scratch
     // at the 128 that two workgroups per CU leave (2422 us at 2048 rows of the 7B widths; 76 registers now.  Prompts, 7B
     // widths: 5000 tokens through 4 layers 30.6 -> 16.3 ms, 99 tokens through 8 layers 4.79 -> 3.03 ms).
-    pf_mainloop<MTL, NWAVE, true, false>(a, t, pf_lds, rs, acc);
+    pf_mainloop<MTL, NWAVE, true>(a, t, pf_lds, rs, acc);
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
-    const int KTf = F / 32;
 #pragma unroll
-    for (int i = 0; i < WNF; ++i) {
-        const int T = t.nt0 + t.wn * WNF + i;
+    for (int i = 0; i < PF_WNF; ++i) {
+        const int T = t.nt0 + t.wn * PF_WNF + i;
         if (T >= a.n_tiles) continue;
 #pragma unroll
         for (int j = 0; j < MW; ++j) {
             const int ml = (t.wm * MW + j) * 16 + li, m = t.mt0 * 16 + ml;
-            const f32x4 v = acc[i][j] * rs[ml];
-            // The gate features sit in the lower 32 lanes, their up partners in the upper 32.  Both halves get both
-            // (a lane swap each) and share the work: the lower half forms features 0 and 1 of its four, the upper
-            // half 2 and 3.  Hardware exponential and reciprocal (a few 1e-7 relative: the results are kept to 16
-            // mantissa bits); with the library routines and one half idle this epilogue was 8 % of the kernel.
-            float gq[4], uq[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) halves_of(v[q], gq[q], uq[q]);
-            const bool upper = rg >= 2;
-            const float g0 = upper ? gq[2] : gq[0], g1 = upper ? gq[3] : gq[1];
-            const float u0 = upper ? uq[2] : uq[0], u1 = upper ? uq[3] : uq[1];
-            if (m < a.M)
-                pk_store2(act_hi, act_lo, m, T * 8 + (rg & 1) * 4 + (upper ? 2 : 0), KTf, __fdividef(g0, 1.0f + __expf(-g0)) * u0,
-                          __fdividef(g1, 1.0f + __expf(-g1)) * u1);
+            pf_swiglu_store(act_hi, act_lo, m, m < a.M, T, F / 32, acc[i][j] * rs[ml], rg);
         }
     }
 }
@@ -654,7 +825,7 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
     if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
-    constexpr int WNF = 32 / NWAVE;
+    constexpr int WNF = PF_WNF;
     constexpr int MW = MTL / 2;
     float* rs = pf_rs_ptr<MTL, NWAVE, (NWAVE == 8), LO>(pf_lds);
     constexpr int WN = NWAVE / 2;        // waves along the features
@@ -1072,7 +1243,8 @@ PfArgs pf_args(const PfGemm& g, int MTL) {
     a.KT = g.K / 32;
     a.n_tiles = g.N / 16;
     a.m_tiles = (g.M + 15) / 16;
-    a.n_wgN = (g.N + 255) / 256;
+    a.n_wgN = (a.n_tiles + PF_NTL - 1) / PF_NTL;
+    a.unit = 0;
     a.n_wgM = (g.M + MTL * 16 - 1) / (MTL * 16);
     a.M = g.M;
     a.N = g.N;
@@ -1098,7 +1270,63 @@ hipError_t pf_set_lds(K kernel, size_t bytes) {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+constexpr int PF_CUS = 256, PF_PART_TILES = 256;
+
+
+template <int MTL>
+hipError_t pf_launch_part(const PfArgs& a, void* part, hipStream_t s) {
+    constexpr size_t lds_b = pf_lds_bytes<MTL, 8, false>();
+    static hipError_t once = pf_set_lds(pf_part_kernel<MTL>, lds_b);
+    if (once != hipSuccess) return once;
+    const int wgs = (a.n_wgN * a.n_wgM * a.KT + a.unit - 1) / a.unit;
+    EE_LAUNCH_SM(pf_part_kernel<MTL>, dim3((wgs + 7) / 8 * 8), dim3(512), lds_b, s, a, (f32x4*)part);
+    return hipGetLastError();
+}
+
+int pf_part_mtl(int M) { return M <= 64 ? 4 : 8; }
+
+// k-tiles per workgroup: an even share, but no fewer than eight (a part costs its writing and reading)
+int pf_part_unit(int tiles, int KT) {
+    int u = (int)(((long)tiles * KT + PF_CUS - 1) / PF_CUS);
+    if (u < 8) u = 8;
+    return u < KT ? u : KT;
+}
+
+// Is the even cut (pf_part_kernel and its sum) faster than a workgroup per result tile?  Both wait for what a CU takes in:
+// a direct launch `rounds` x KT x (16 + 2 mtl) KB, at 47 GB/s with 64-row tiles and 33 with 128-row tiles; the cut its
+// unit's share of that at 33 GB/s, plus writing one or two parts, reading all of them back, and a second launch.  Fitted
+// to the times of all four GEMMs at 768 to 6656 wide, 40 to 1024 rows (per layer, 7B widths, 99 rows, direct and cut: Q|K|V 65
+// -> 46 us, O 60 -> 25, gate|up 67 -> 58, down 135 -> 38; 64 rows: 60 -> 33, 60 -> 21, 66 -> 42, 130 -> 30; 256
+// rows: gate|up 123 -> 103, down 140 -> 60, Q|K|V stays direct).
+bool pf_cut_pays(const PfGemm& g, int mtl_direct) {
+    const int KT = g.K / 32, n_wgN = (g.N + 255) / 256, mtl = pf_part_mtl(g.M);
+    const int tiles = n_wgN * ((g.M + mtl * 16 - 1) / (mtl * 16));
+    if (tiles > PF_PART_TILES) return false;
+    const int unit = pf_part_unit(tiles, KT), wgs = (tiles * KT + unit - 1) / unit;
+    const float part_kb = 16.0f * mtl;
+    const float cut = unit * (16 + 2 * mtl) / 33.0f + part_kb * (1.0f + (float)tiles / wgs) / 60.0f + (wgs + tiles) * part_kb / 5000.0f + 5.0f;
+    const long direct_tiles = (long)n_wgN * ((g.M + mtl_direct * 16 - 1) / (mtl_direct * 16));
+    const long rounds = (direct_tiles + PF_CUS - 1) / PF_CUS;
+    const float direct = rounds * KT * (16 + 2 * mtl_direct) / (mtl_direct == 4 ? 47.0f : 33.0f) + 2.0f;
+    return cut < direct;
+}
+
+// The partial sums of g (see pf_part_kernel); *a and *mtl are what the summing kernel needs.
+hipError_t pf_part(const PfGemm& g, PfArgs* a, int* mtl, hipStream_t s) {
+    *mtl = pf_part_mtl(g.M);
+    *a = pf_args(g, *mtl);
+    a->unit = pf_part_unit(a->n_wgN * a->n_wgM, a->KT);
+    PfArgs b = *a;
+    b.ssq = nullptr;
+    return *mtl == 8 ? pf_launch_part<8>(b, g.part, s) : pf_launch_part<4>(b, g.part, s);
+}
+
 }  // namespace
+
+size_t pf_part_bytes(int max_rows, int max_N) {
+    const int tiles = std::min(PF_PART_TILES, (max_N + 255) / 256 * ((max_rows + 63) / 64));
+    return (size_t)(PF_CUS + tiles + 8) * (PF_NTL * 8) * 1024;
+}
 
 #define PF_DISPATCH(KERNEL, WIDE, ...)                                                                        \
     do {                                                                                                  \
@@ -1123,12 +1351,31 @@ hipError_t launch_pf_qkv(const PfGemm& g, void* q_hi, void* q_lo, const float* r
     const int d = g.N / 3;
     PfQkv e{(__bf16*)q_hi, (__bf16*)q_lo, d, kv.H, kv.hd, (const float2*)rope_cs, (__bf16*)kv.pool + (size_t)layer * kv.layer_stride,
             kv.blk_stride, kv.BT, bt, p0};
+    if (pf_cut_pays(g, pf_mtl(g))) {
+        PfArgs a;
+        int mtl;
+        const hipError_t err = pf_part(g, &a, &mtl, s);
+        if (err != hipSuccess) return err;
+        EE_LAUNCH(pf_qkv_sum_kernel, dim3((a.n_tiles + 7) / 8 * a.m_tiles), dim3(256), s, a, e, mtl, (const f32x4*)g.part);
+        return hipGetLastError();
+    }
     PF_DISPATCH(pf_qkv_kernel, true, e);
 }
 
 hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, void* xgh_hi, void* xgh_lo, const float* g_next,
                            const float* g_head, float* ssq_out, int ssq_n_out, hipStream_t s) {
     PfResid e{x, (__bf16*)xg_hi, (__bf16*)xg_lo, (__bf16*)xgh_hi, (__bf16*)xgh_lo, g_next, g_head, ssq_out, ssq_n_out, g.N};
+    // (With more than four row tiles of a few column panels the ranges of one panel's row tiles no longer run side by side,
+    // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 4 us for O and 9 us for down.)
+    const int cut_tiles = (g.N + 255) / 256 * ((g.M + 127) / 128);
+    if (cut_tiles <= 64 && pf_cut_pays(g, pf_mtl(g))) {
+        PfArgs a;
+        int mtl;
+        const hipError_t err = pf_part(g, &a, &mtl, s);
+        if (err != hipSuccess) return err;
+        EE_LAUNCH(pf_resid_sum_kernel, dim3(a.n_wgN * a.m_tiles), dim3(512), s, a, e, mtl, (const f32x4*)g.part);
+        return hipGetLastError();
+    }
     // Two workgroups per CU (four waves per SIMD) once the grid has more workgroups than CUs (30B widths at 2048
     // rows: O 359 -> 332 us, down 922 -> 840 us); a grid of one workgroup per CU keeps the deeper ring and the
     // second operand set.
@@ -1165,6 +1412,15 @@ hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, 
 }
 
 hipError_t launch_pf_swiglu(const PfGemm& g, void* act_hi, void* act_lo, int F, hipStream_t s) {
+    if (pf_cut_pays(g, pf_mtl(g))) {
+        PfArgs a;
+        int mtl;
+        const hipError_t err = pf_part(g, &a, &mtl, s);
+        if (err != hipSuccess) return err;
+        EE_LAUNCH(pf_swiglu_sum_kernel, dim3((a.n_tiles + 7) / 8 * a.m_tiles), dim3(256), s, a, (__bf16*)act_hi, (__bf16*)act_lo, F, mtl,
+                  (const f32x4*)g.part);
+        return hipGetLastError();
+    }
     PF_DISPATCH(pf_swiglu_kernel, true, (__bf16*)act_hi, (__bf16*)act_lo, F);
 }
 

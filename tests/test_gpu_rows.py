@@ -9,6 +9,7 @@ from oracle.from_workload import build_model
 from workload import ModelShape, prompt_tokens
 
 from common import TOL, kv_check, load_gpu_model, rel_err
+from test_gpu_prefill import check_prefill
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +58,12 @@ def test_full_depth_step_over_a_given_number_of_rows(name, min_wgs):
                 kv_check(k, ko[l], "bf16", "K", l), kv_check(v, vo[l], "bf16", "V", l)
         cache.close()
     gm.close()
+
+
+@pytest.mark.parametrize("n,rows_env", [(33, 0), (64, 0), (65, 0), (128, 0), (129, 0), (200, 128)])
+def test_short_prompts_whose_gemms_are_cut_over_the_contraction(n, rows_env):
+    """Prompts around the row tiles of the prompt phase (64, 128 rows, one and two tiles, a second pass), on a width at
+    which all four GEMMs are cut over K: 32 and 65 k-tiles, 17 column panels of which the last holds a single pair."""
+    print(f"case: cut prompt n={n} rows_env={rows_env}", flush=True)
+    shape = ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5)
+    check_prefill(shape, n, 4, rows_env=rows_env, scored=False)
