@@ -50,12 +50,6 @@ template <> __device__ __forceinline__ void store_split<__bf16>(__bf16* p, size_
     p[0] = hi;
     p[lo_off] = (__bf16)(v - (float)hi);
 }
-template <typename ST> __device__ __forceinline__ float load_split(const ST* p, size_t lo_off);
-template <> __device__ __forceinline__ float load_split<float>(const float* p, size_t) { return *p; }
-template <> __device__ __forceinline__ float load_split<__bf16>(const __bf16* p, size_t lo_off) {
-    return (float)p[0] + (float)p[lo_off];
-}
-
 // Element index of (row m, feature k) in an operand-order ("packed") activation array: 16-row groups,
 // [m/16][K/32][64 lanes][8], lane = ((k%32)/8)*16 + m%16: one k-step of one row group is 1 KB that a wave
 // loads as a ready MFMA operand.  Used for the rows of a launch when there are too many for LDS.
@@ -765,24 +759,79 @@ __device__ __forceinline__ void gemm_mainloop_bf16_lds(const GemmArgs& a, int ti
     __syncthreads();
 }
 
-// fp32 path (tiny model, parity only): plain FMA loop, weights row-major [tile][16][K]
-template <int KS, int MT, typename Pre>
-__device__ __forceinline__ void gemm_mainloop_f32(const GemmArgs& a, int tile, GemmSmem<KS, MT>& sm, Pre pre) {
-    rms_scales<MT>(a, sm.rs);
-    pre(std::false_type{});
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < MT * 256; idx += blockDim.x) {
-        int m = idx >> 4, c = idx & 15;
-        float s = 0.f;
-        if (m < a.T) {
-            int slot = a.arow ? a.arow[m] : m;
-            const float* ar = (const float*)a.A + (size_t)slot * a.lda;
-            const float* wr = (const float*)a.W + ((size_t)tile * 16 + c) * a.K;
-            for (int k = 0; k < a.K; ++k) s = fmaf(ar[k], wr[k], s);
+// fp32 path: weights row-major [tile][16][K].  A launch is a few kilobytes per workgroup, so latency is all there is: K is
+// dealt in pieces of four to 16 threads per column (all of a thread's loads in flight together) and added up across lanes
+// and waves in a fixed order.  (One thread per column and row walked K alone before: 27.6 us for K = 128 and 352, one row,
+// now 5.)  NR rows at a time share the loads of the weights.
+template <int NR, int KS, int MT>
+__device__ __forceinline__ void gemm_rows_f32(const GemmArgs& a, int tile, int m0, GemmSmem<KS, MT>& sm) {
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, c = threadIdx.x & 15, sl = threadIdx.x >> 4;
+    const float* wr = (const float*)a.W + ((size_t)tile * 16 + c) * a.K;
+    const float* ar[NR];
+    float acc[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        ar[j] = (const float*)a.A + (size_t)gemm_slot(a, m0 + j < a.T ? m0 + j : a.T - 1) * a.lda;
+        acc[j] = 0.f;
+    }
+    constexpr int U = 4;
+    for (int k0 = sl * 4; k0 < a.K; k0 += 64 * U) {
+        f32x4 w[U], v[U][NR];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int k = k0 + 64 * u < a.K ? k0 + 64 * u : k0;  // (a surplus piece repeats the first one and is dropped)
+            w[u] = *(const f32x4*)(wr + k);
+#pragma unroll
+            for (int j = 0; j < NR; ++j) v[u][j] = *(const f32x4*)(ar[j] + k);
         }
-        sm.out[m][c] = s * sm.rs[m];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (k0 + 64 * u < a.K)
+#pragma unroll
+                for (int j = 0; j < NR; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) acc[j] = fmaf(v[u][j][q], w[u][q], acc[j]);
+    }
+    float* red = &sm.red[0][0][0];  // [wave][NR][16]
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const float t = rows4_sum(acc[j]);
+        if (lane < 16) red[(wave * NR + j) * 16 + c] = t;
     }
     __syncthreads();
+    if ((int)threadIdx.x < NR * 16) {
+        const int j = threadIdx.x >> 4, m = m0 + j;
+        const float t = ((red[j * 16 + c] + red[(NR + j) * 16 + c]) + red[(2 * NR + j) * 16 + c]) + red[(3 * NR + j) * 16 + c];
+        if (m < a.T) sm.out[m][c] = t * sm.rs[m];
+    }
+    __syncthreads();
+}
+
+template <int KS, int MT, typename Pre>
+__device__ __forceinline__ void gemm_mainloop_f32(const GemmArgs& a, int tile, GemmSmem<KS, MT>& sm, Pre pre) {
+    static_assert(KS == 4, "256 threads");
+    pre(std::false_type{});
+    {  // RMS scales: 16 lanes per row
+        const int c = threadIdx.x & 15;
+        for (int m = threadIdx.x >> 4; m < a.T; m += 16) {
+            float r = 1.f;
+            if (a.ssq != nullptr) {
+                const float* p = a.ssq + (size_t)gemm_slot(a, m) * a.ssq_stride;
+                float s = 0.f;
+                for (int i = c; i < a.ssq_n; i += 16) s += p[i];
+                s += row_rotate<8>(s);
+                s += row_rotate<4>(s);
+                s += row_rotate<2>(s);
+                s += row_rotate<1>(s);
+                r = 1.0f / sqrtf(s * a.inv_d + a.eps);
+            }
+            if (c == 0) sm.rs[m] = r;
+        }
+    }
+    if (a.T == 1)
+        gemm_rows_f32<1>(a, tile, 0, sm);
+    else
+        for (int m0 = 0; m0 < a.T; m0 += 4) gemm_rows_f32<4>(a, tile, m0, sm);
 }
 
 // `pre` runs once the first weight loads are in flight: the place to fetch what the epilogue needs.
@@ -1734,9 +1783,9 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t*
 }
 
 // ------------------------------------------------------------------------------------------------
-// attention, reference-grade kernel: one workgroup per (row, head); the row at position p attends to
-// cache positions 0..p of its sequence (which includes the rows before it in this launch: their K,V
-// were written by the QKV kernel).  Online soft-max over chunks of 1024 positions.
+// attention, fp32 model: one workgroup per (row, head); the row at position p attends to cache positions 0..p of its
+// sequence (which includes the rows before it in this launch: their K,V were written by the QKV kernel).  Online
+// soft-max over chunks of 1024 positions.
 // ------------------------------------------------------------------------------------------------
 // K of (head, position): pointer to its hd contiguous features.  V of (head, position, feature): one
 // element of the transposed V block [head][position / 32][feature][position % 32].
@@ -1753,68 +1802,92 @@ __device__ __forceinline__ const ST* v_ptr(const ST* layer_base, const KvGeom& k
            (size_t)(pin >> 5) * (kv.hd * 32) + c * 32 + (pin & 31);
 }
 
-__device__ __forceinline__ float block_reduce(float v, float* red, bool is_max) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if ((int)threadIdx.x < o) {
-            float b = red[threadIdx.x + o];
-            red[threadIdx.x] = is_max ? fmaxf(red[threadIdx.x], b) : red[threadIdx.x] + b;
-        }
-        __syncthreads();
+// over the 256 threads of a workgroup: a wave's lanes, then the four waves in order
+template <bool MAX>
+__device__ __forceinline__ float block_reduce(float v, float* red) {
+    if constexpr (MAX) {
+        v = fmaxf(v, row_rotate<8>(v));
+        v = fmaxf(v, row_rotate<4>(v));
+        v = fmaxf(v, row_rotate<2>(v));
+        v = fmaxf(v, row_rotate<1>(v));
+        v = rows4_max(v);
+    } else {
+        v = wave_sum(v);
     }
-    float r = red[0];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    const float r = MAX ? fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])) : ((red[0] + red[1]) + red[2]) + red[3];
     __syncthreads();
     return r;
 }
 
-template <typename ST>
-__global__ __launch_bounds__(256) void attn_simple_kernel(const ST* __restrict__ q, ST* __restrict__ out,
-                                                          size_t io_lo, const SegDesc* __restrict__ desc,
-                                                          const int32_t* __restrict__ btab, KvGeom kv,
-                                                          const ST* __restrict__ layer_base, int d) {
-    __shared__ float qs[128];
-    __shared__ float sc[1024];
+// A context of a few dozen positions is a chain of latencies: every thread's loads are requested together, scores by
+// position, P.V by (feature, group of four positions) with the groups added up at the end.  (One thread per feature walked
+// the positions alone before: 10 us at 40 positions, now 5.)
+__global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__ q, float* __restrict__ out, const SegDesc* __restrict__ desc,
+                                                       const int32_t* __restrict__ btab, KvGeom kv, const float* __restrict__ layer_base, int d) {
+    __shared__ __attribute__((aligned(16))) float qs[128];
+    __shared__ __attribute__((aligned(16))) float sc[1024];
     __shared__ float red[256];
     const int r = blockIdx.x, h = blockIdx.y, hd = kv.hd;
     const int pos = desc->pos[r];
     const int32_t* bt = btab + (size_t)desc->rseq[r] * kv.max_blocks_per_seq;
     const float scale = 1.0f / sqrtf((float)hd);
-    for (int i = threadIdx.x; i < hd; i += 256) qs[i] = load_split<ST>(q + (size_t)r * d + h * hd + i, io_lo);
+    if ((int)threadIdx.x < hd) qs[threadIdx.x] = q[(size_t)r * d + h * hd + threadIdx.x];
     __syncthreads();
+    const int c = threadIdx.x % hd, g = threadIdx.x / hd, ng = 256 / hd;  // P.V: feature, group of four positions
     float m = -INFINITY, l = 0.f, acc = 0.f;
     const int n_ctx = pos + 1;
     for (int j0 = 0; j0 < n_ctx; j0 += 1024) {
-        int nj = min(1024, n_ctx - j0);
+        const int nj = min(1024, n_ctx - j0), nj4 = (nj + 3) & ~3;
         float cmax = -INFINITY;
-        for (int jj = threadIdx.x; jj < nj; jj += 256) {
-            const ST* kp = k_ptr(layer_base, kv, bt, h, j0 + jj);
-            float s = 0.f;
-            for (int c = 0; c < hd; ++c) s = fmaf(qs[c], (float)kp[c], s);
-            s *= scale;
-            sc[jj] = s;
+        for (int jj = threadIdx.x; jj < nj4; jj += 256) {
+            float s = -INFINITY;
+            if (jj < nj) {
+                const float* kp = k_ptr(layer_base, kv, bt, h, j0 + jj);
+                float s4[4] = {0.f, 0.f, 0.f, 0.f};
+                for (int e = 0; e < hd; e += 32) {  // (hd is 32, 64 or 128)
+                    f32x4 kk[8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) kk[u] = *(const f32x4*)(kp + e + u * 4);
+#pragma unroll
+                    for (int u = 0; u < 8; ++u)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s4[i] = fmaf(qs[e + u * 4 + i], kk[u][i], s4[i]);
+                }
+                s = ((s4[0] + s4[1]) + (s4[2] + s4[3])) * scale;
+            }
+            sc[jj] = s;  // (-inf past the context: probability 0)
             cmax = fmaxf(cmax, s);
         }
-        cmax = block_reduce(cmax, red, true);
-        float m_new = fmaxf(m, cmax);
+        cmax = block_reduce<true>(cmax, red);
+        const float m_new = fmaxf(m, cmax);
         float psum = 0.f;
-        for (int jj = threadIdx.x; jj < nj; jj += 256) {
-            float p = expf(sc[jj] - m_new);
+        for (int jj = threadIdx.x; jj < nj4; jj += 256) {
+            const float p = expf(sc[jj] - m_new);
             sc[jj] = p;
             psum += p;
         }
-        psum = block_reduce(psum, red, false);
-        float corr = expf(m - m_new);  // exp(-inf) = 0 on the first chunk
+        psum = block_reduce<false>(psum, red);  // (its barriers also publish sc)
+        const float corr = expf(m - m_new);  // exp(-inf) = 0 on the first chunk
         l = l * corr + psum;
-        if ((int)threadIdx.x < hd) {
-            float a2 = 0.f;
-            for (int jj = 0; jj < nj; ++jj) a2 = fmaf(sc[jj], (float)*v_ptr(layer_base, kv, bt, h, j0 + jj, (int)threadIdx.x), a2);
-            acc = acc * corr + a2;
+        acc *= corr;
+        for (int jj = g * 4; jj < nj; jj += ng * 4) {
+            const f32x4 v = *(const f32x4*)v_ptr(layer_base, kv, bt, h, j0 + jj, c);  // four positions of one 32-position group
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (jj + i < nj) acc = fmaf(sc[jj + i], v[i], acc);  // (positions past the context hold unknown bits)
         }
         m = m_new;
         __syncthreads();
     }
-    if ((int)threadIdx.x < hd) store_split<ST>(out + (size_t)r * d + h * hd + threadIdx.x, io_lo, acc / l);
+    red[threadIdx.x] = acc;
+    __syncthreads();
+    if ((int)threadIdx.x < hd) {
+        float o = red[threadIdx.x];
+        for (int i = 1; i < ng; ++i) o += red[i * hd + threadIdx.x];
+        out[(size_t)r * d + h * hd + threadIdx.x] = o / l;
+    }
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -2119,8 +2192,8 @@ hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, c
         }
     }
     dim3 grid(T, kv.H), block(256);
-    EE_LAUNCH(attn_simple_kernel<float>, grid, block, s, (const float*)q, (float*)out, io_lo, desc, btab, kv,
-                       (const float*)kv.pool + (size_t)layer * kv.layer_stride, d);
+    EE_LAUNCH(attn_f32_kernel, grid, block, s, (const float*)q, (float*)out, desc, btab, kv,
+              (const float*)kv.pool + (size_t)layer * kv.layer_stride, d);
     return hipGetLastError();
 }
 
