@@ -1031,7 +1031,7 @@ __global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_s
 // decision (an in-kernel "last workgroup merges" scheme needs a device-wide fence in every workgroup,
 // which costs more than the extra launch).
 struct HeadArgs {
-    HeadPartial* partials;  // [n_wg][EE_MAX_SEQS]
+    HeadPartial* partials;  // [row][V / 16]: what the merge of a row reads stands together
     float* logits;          // optional [row][V]
     int V;
 };
@@ -1077,7 +1077,7 @@ __global__ __launch_bounds__(KS * 64, ALDS ? (KS == 16 ? 4 : 6) : 1) void gemm_h
         p.sum = s;
         p.idx = n0 + ix;
         p.pad = 0;
-        e.partials[(size_t)tile * EE_MAX_SEQS + m] = p;
+        e.partials[(size_t)m * (e.V / 16) + tile] = p;
     }
 }
 
@@ -1101,7 +1101,7 @@ __global__ __launch_bounds__(512) void head_merge_kernel(const HeadPartial* __re
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const int w = w0 + j * 512;
-                if (w < n_wg) p[j] = partials[(size_t)w * EE_MAX_SEQS + m];
+                if (w < n_wg) p[j] = partials[(size_t)m * n_wg + w];
             }
 #pragma unroll
             for (int j = 0; j < 8; ++j)
@@ -1482,7 +1482,7 @@ struct RowsHead : HeadArgs {
             p.sum = s;
             p.idx = (int)first;
             p.pad = 0;
-            partials[(size_t)tile * EE_MAX_SEQS + m] = p;
+            partials[(size_t)m * (V / 16) + tile] = p;
         }
     }
 };
