@@ -208,6 +208,10 @@ struct ee_model {
     bool spec_recorded = false;
     std::vector<hipEvent_t> prof_ev;    // event pairs
     size_t prof_used = 0;               // events recorded so far
+    // Scratch for partial sums inside the decode workspace: the head and attention partials are idle while a projection
+    // runs (a pass on a stream of its own has a workspace of its own).
+    char* step_part() const { return ws + wsl.partials; }
+    size_t step_part_bytes() const { return wsl.stage - wsl.partials; }
     size_t lo_rows(size_t ld) const { return cfg.dtype == EE_BF16 ? rows_padded(max_rows) * ld : 0; }  // hi -> lo distance
     int n_seg() const { return cfg.n_exits + 1; }
     int seg_begin(int s) const { return s == 0 ? 0 : cfg.exit_layers[s - 1]; }
@@ -447,6 +451,8 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
     g.dtype = dt;
     g.T = T;
     g.min_wgs = cf.gemm_min_workgroups;
+    g.part = m->step_part();
+    g.part_bytes = m->step_part_bytes();
     g.desc = dd;
     g.desc_host = m->host_desc(di);
     g.inv_d = 1.0f / (float)d;
@@ -599,6 +605,8 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
     GemmCommon g{};
     g.dtype = dt;
     g.min_wgs = cf.gemm_min_workgroups;
+    g.part = m->step_part();
+    g.part_bytes = m->step_part_bytes();
     g.inv_d = 1.0f / (float)d;
     g.eps = cf.rms_eps;
     g.ssq_stride = c->ssq_stride;
@@ -979,6 +987,7 @@ int prefill_large(ee_model* m, ee_kv_cache* c, int seq, const int32_t* tokens, i
     const int32_t* bt = m->dev_btab();
     PfGemm g{};
     g.part = ws + w.pf_part;
+    g.part_bytes = w.total - w.pf_part;
     g.inv_d = 1.0f / (float)d;
     g.eps = cf.rms_eps;
     g.ssq_n = ssq_n;

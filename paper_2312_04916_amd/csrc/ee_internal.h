@@ -99,6 +99,8 @@ struct GemmCommon {
     // while the rows are staged; NULL otherwise
     const float* att_part;
     int att_ns, att_H, att_hd;
+    void* part;  // scratch for partial sums (many rows: the contraction may be cut over workgroups), or NULL
+    size_t part_bytes;
 };
 
 hipError_t launch_gemm_qkv(const GemmCommon& c, void* q, size_t q_lo, const float* rope_cs, const KvGeom& kv, int layer,
@@ -125,6 +127,17 @@ bool gemm_rows_fit_lds(int dtype, int T, int K, int N);
 hipError_t launch_kv_gather(int dtype, const KvGeom& kv, int layer, const int32_t* btab_seq, int pos0, int n,
                             float* k_out, float* v_out, hipStream_t s);
 
+// ---- a GEMM cut along its contraction (ee_prefill.hip): the k-tiles of all result tiles (256 columns x mtl row tiles) stand
+// behind each other and every workgroup takes `unit` of them.
+struct PartGeom {
+    int n_tiles, n_wgN, n_wgM, m_tiles, KT, unit, mtl;
+};
+// true when `bytes` of scratch hold the parts and the cut with its sum takes less than other_us
+bool cut_pays_over(int N, int K, int M, size_t bytes, float other_us, PartGeom* pg);
+hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N, int K, int M, void* part, const PartGeom& pg, hipStream_t s);
+hipError_t launch_head64(const void* W, const void* A_hi, const void* A_lo, int V, int d, int M, const float* ssq, int ssq_n,
+                         const int32_t* arow, float inv_d, float eps, HeadPartial* partials, float* logits, hipStream_t s);
+
 // ---- prompt phase (ee_prefill.hip): many rows at once, activations in the packed operand layout
 // [row/16][K/32][64 lanes][8 bf16] (hi and lo arrays), bf16 model only.
 struct PfGemm {
@@ -136,7 +149,8 @@ struct PfGemm {
     int ssq_n;
     float inv_d, eps;
     int M;            // rows
-    void* part;       // scratch of pf_part_bytes() for partial sums where the contraction is split over workgroups
+    void* part;       // scratch for partial sums where the contraction is cut over workgroups
+    size_t part_bytes;
 };
 size_t pf_part_bytes(int max_rows, int max_N);
 hipError_t launch_pf_embed(const void* embed, const int32_t* dev_tokens, int M, int d, const float* g_next, float* x, void* xg_hi,

@@ -12,6 +12,7 @@
 
 #include "ee_lanes.h"
 #include "ee_launch.h"
+#include "ee_part.h"
 
 #include <cstdlib>
 #include <type_traits>
@@ -1487,6 +1488,60 @@ struct RowsHead : HeadArgs {
     }
 };
 
+// The parts of a launch cut along K (ee_part.h) added up, with the same epilogues: 16 rows x 128 columns per workgroup, a
+// wave two tiles.
+template <typename Epi>
+__global__ __launch_bounds__(256) void rows_sum_kernel(GemmArgs a, Epi e, PartGeom g, const f32x4* __restrict__ part) {
+    __shared__ float rs[16];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, lg = lane >> 4;
+    const int n_cg = (g.n_tiles + 7) / 8, mt = blockIdx.x / n_cg;
+    const int T0 = (blockIdx.x % n_cg) * 8 + wave * 2, m = mt * 16 + li;
+    typename Epi::Row row;
+    e.row(row, a, m < a.T ? m : a.T - 1);
+    if (a.ssq != nullptr) {  // four rows per wave, all loads at once
+        float2 v[4][4];
+        const bool quick = a.ssq_n <= 512 && (a.ssq_n & 1) == 0 && (a.ssq_stride & 1) == 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = mt * 16 + wave * 4 + j;
+            const float* p = a.ssq + (size_t)gemm_slot(a, r < a.T ? r : a.T - 1) * a.ssq_stride;
+            float s = 0.f;
+            if (quick) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (u * 128 < a.ssq_n) v[j][u] = *(const float2*)(p + (2 * (u * 64 + lane) < a.ssq_n ? 2 * (u * 64 + lane) : 0));
+            } else {
+                for (int i = lane; i < a.ssq_n; i += 64) s += p[i];
+                v[j][0] = make_float2(s, 0.f);
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            float s = quick ? 0.f : v[j][0].x;
+            if (quick) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (2 * (u * 64 + lane) < a.ssq_n) s += v[j][u].x + v[j][u].y;
+            }
+            s = wave_sum(s);
+            if (lane == 0) rs[wave * 4 + j] = 1.0f / sqrtf(s * a.inv_d + a.eps);
+        }
+    }
+    typename Epi::Ops ops[2];
+    f32x4 v[2];
+    const bool live = T0 < g.n_tiles;  // (the number of tiles is even)
+    if (live) {
+        e.load(ops[0], row, T0, lg);
+        e.load(ops[1], row, T0 + 1, lg);
+        sum_parts<2>(g, part, mt, T0, lane, v);
+    }
+    __syncthreads();
+    if (!live) return;
+    const float r = a.ssq != nullptr ? rs[li] : 1.0f;
+    e.store(ops[0], row, m, m < a.T, T0, lg, v[0] * r);
+    e.store(ops[1], row, m, m < a.T, T0 + 1, lg, v[1] * r);
+}
+
 // ---- host-side dispatch
 static GemmArgs make_args(const GemmCommon& c) {
     GemmArgs a;
@@ -1620,6 +1675,29 @@ static hipError_t launch_rows(const GemmCommon& c, const GemmArgs& a, const Epi&
     return ks == 4 ? launch_rows_g<4, 1>(a, e, g, s) : ks == 8 ? launch_rows_g<8, 1>(a, e, g, s) : launch_rows_g<16, 1>(a, e, g, s);
 }
 
+// What launch_rows takes, in microseconds, and whether the cut along K beats it: per pass of 64 rows, G / 23 GB/s of weights
+// and 2 mt / 70 GB/s of rows per k-tile and round (fitted to all five projections at 64 rows of the 7B widths).  64 rows,
+// rows_kernel and cut with its sum: down 51 -> 30 us, Q|K|V 42 -> 33, gate|up 52 -> 42; O stays (23 and 21).  Up to 32 rows
+// rows_kernel takes in less and needs no second launch.
+static bool cut_pays(const GemmCommon& c, PartGeom* g) {
+    if (c.T <= 32 || c.part == nullptr || !c.a_packed || c.min_wgs > 0) return false;
+    float us = 0.f;
+    for (int r0 = 0; r0 < c.T; r0 += 64) {
+        const int mt = mt_of(c.T - r0 < 64 ? c.T - r0 : 64), G = g_of(mt, c.N / 16, 0);
+        const int rounds = ((c.N / 16 + G - 1) / G + 255) / 256;
+        us += rounds * (c.K / 32) * (G / 23.0f + 2 * mt / 70.0f) + 6.0f;
+    }
+    return cut_pays_over(c.N, c.K, c.T, c.part_bytes, us, g);
+}
+
+template <typename Epi>
+static hipError_t launch_cut(const GemmCommon& c, const GemmArgs& a, const Epi& e, const PartGeom& g, hipStream_t s) {
+    const hipError_t err = launch_part(c.W, c.A, (const char*)c.A + c.a_lo * 2, c.N, c.K, c.T, c.part, g, s);
+    if (err != hipSuccess) return err;
+    EE_LAUNCH(rows_sum_kernel<Epi>, dim3((g.n_tiles + 7) / 8 * g.m_tiles), dim3(256), s, a, e, g, (const f32x4*)c.part);
+    return hipGetLastError();
+}
+
 // few rows, staged in LDS (the caller has made sure that they fit)
 #define EE_DISPATCH_LDS(KERNEL, ...)                                                                                                    \
     do {                                                                                                                                \
@@ -1663,6 +1741,12 @@ static const int32_t* desc_array(const SegDesc* d, size_t field_offset, int r0) 
 
 hipError_t launch_gemm_qkv(const GemmCommon& cc, void* q, size_t q_lo, const float* rope_cs, const KvGeom& kv, int layer,
                            hipStream_t s) {
+    PartGeom pg;
+    if (cc.dtype == EE_BF16 && cut_pays(cc, &pg)) {
+        RowsQkv e{{(__bf16*)q, q_lo, cc.N / 3, (const float2*)rope_cs, (__bf16*)kv.pool + (size_t)layer * kv.layer_stride, kv.blk_stride, kv.H,
+                   kv.hd, kv.BT, desc_array(cc.desc, offsetof(SegDesc, pos), 0), desc_array(cc.desc, offsetof(SegDesc, kvblk), 0), 0, 0}};
+        return launch_cut(cc, make_args(cc), e, pg, s);
+    }
     for (int r0 = 0; r0 < cc.T; r0 += PASS_ROWS) {
         const GemmCommon c = pass_of(cc, r0);
         GemmArgs a = make_args(c);
@@ -1699,6 +1783,12 @@ static void fill_rows(ResidArgs<ST>& e, const GemmCommon& c, int T_all) {
 
 hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh, size_t xs_lo, float* ssq_out,
                              const float* g_next, const float* g_head, int d, void* xg_pk, size_t xg_pk_lo, hipStream_t s) {
+    PartGeom pg;
+    if (cc.dtype == EE_BF16 && cut_pays(cc, &pg)) {
+        RowsResid e{{x, (__bf16*)xg, (__bf16*)xgh, xs_lo, ssq_out, cc.ssq_stride, g_next, g_head, d,
+                     desc_array(cc.desc, offsetof(SegDesc, xrow), 0), (__bf16*)xg_pk, xg_pk_lo, 0, {}}};
+        return launch_cut(cc, make_args(cc), e, pg, s);
+    }
     for (int r0 = 0; r0 < cc.T; r0 += PASS_ROWS) {
         const GemmCommon c = pass_of(cc, r0);
         GemmArgs a = make_args(c);
@@ -1739,6 +1829,9 @@ hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh
 }
 
 hipError_t launch_gemm_swiglu(const GemmCommon& cc, void* act, size_t act_lo, int F, bool act_packed, hipStream_t s) {
+    PartGeom pg;
+    if (cc.dtype == EE_BF16 && cut_pays(cc, &pg))
+        return launch_cut(cc, make_args(cc), RowsSwiglu{(__bf16*)act, act_lo, F, act_packed ? F / 32 : 0}, pg, s);
     for (int r0 = 0; r0 < cc.T; r0 += PASS_ROWS) {
         const GemmCommon c = pass_of(cc, r0);
         GemmArgs a = make_args(c);
@@ -1766,7 +1859,15 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t*
     if (c.T > 64) return hipErrorInvalidValue;
     GemmArgs a = make_args(c);
     HeadArgs e{partials, logits, c.N};
-    if (c.dtype == EE_BF16) {
+    int n_parts = c.N / 16;
+    if (c.dtype == EE_BF16 && c.a_packed && c.T > 32 && c.min_wgs <= 0 && c.ssq_stride == c.ssq_n && c.N >= 128 * 256) {
+        // (a vocabulary of at least half as many 256-column panels as there are CUs; 64 rows, 50304 words, 4096 wide: 128 ->
+        // 75 us)
+        n_parts = (c.N + 255) / 256;
+        const hipError_t err = launch_head64(c.W, c.A, (const char*)c.A + c.a_lo * 2, c.N, c.K, c.T, c.ssq, c.ssq_n, c.arow, c.inv_d, c.eps,
+                                             partials, logits, s);
+        if (err != hipSuccess) return err;
+    } else if (c.dtype == EE_BF16) {
         if (c.a_packed) {
             const hipError_t err = launch_rows(c, a, RowsHead{e}, s);
             if (err != hipSuccess) return err;
@@ -1778,7 +1879,7 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t*
     }
     hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    EE_LAUNCH(head_merge_kernel, dim3(c.T), dim3(512), s, (const HeadPartial*)partials, c.N / 16, c.T, mode, threshold, results, c.desc, tag);
+    EE_LAUNCH(head_merge_kernel, dim3(c.T), dim3(512), s, (const HeadPartial*)partials, n_parts, c.T, mode, threshold, results, c.desc, tag);
     return hipGetLastError();
 }
 

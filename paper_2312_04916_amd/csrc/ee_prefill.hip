@@ -18,6 +18,7 @@
 
 #include "ee_lanes.h"
 #include "ee_launch.h"
+#include "ee_part.h"
 
 namespace ee {
 
@@ -74,6 +75,7 @@ struct PfArgs {
     int KT, n_tiles, m_tiles;  // valid 16-wide tiles of W and X (loads of tiles beyond them are clamped)
     int n_wgN, n_wgM;
     int unit;  // k-tiles per workgroup where the contraction is split over workgroups (see pf_part_kernel)
+    const int32_t* arow;  // index of a row's partial sums of squares, or NULL: the row itself
     int M, N;
     const float* ssq;  // [rows][ssq_n] partial sums of squares of the rows of X before their gain, or NULL
     int ssq_n;
@@ -176,17 +178,25 @@ __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& 
             __builtin_amdgcn_global_load_lds(EE_GLB_PTR(src[i] + (size_t)kt * 64), EE_LDS_PTR(lds + st * STAGE + (wave * FPW + i) * 64), 16,
                                              0, 0);
     };
-    // r[m] = 1/sqrt(mean(x^2)+eps) of this tile's rows, from the producers' partial sums (fixed order)
-    for (int ml = threadIdx.x; ml < MTL * 16; ml += blockDim.x) {
-        const int m = t.mt0 * 16 + ml;
+    // r[m] = 1/sqrt(mean(x^2)+eps) of this tile's rows, from the producers' partial sums (fixed order): NWAVE * 4 / MTL
+    // neighbouring threads per row
+    {
+        constexpr int TPR = NWAVE * 4 / MTL;
+        static_assert(TPR == 4 || TPR == 8, "threads per row");
+        const int ml = threadIdx.x / TPR, m = t.mt0 * 16 + ml;
         float r = 1.f;
-        if (a.ssq != nullptr && m < a.M) {
-            const float* p = a.ssq + (size_t)m * a.ssq_n;
+        if (a.ssq != nullptr) {
             float s = 0.f;
-            for (int i = 0; i < a.ssq_n; ++i) s += p[i];
+            if (m < a.M) {
+                const float* p = a.ssq + (size_t)(a.arow ? a.arow[m] : m) * a.ssq_n;
+#pragma unroll 4
+                for (int i = threadIdx.x % TPR; i < a.ssq_n; i += TPR) s += p[i];
+            }
+#pragma unroll
+            for (int o = TPR / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
             r = 1.0f / sqrtf(s * a.inv_d + a.eps);
         }
-        rs[ml] = r;
+        if (threadIdx.x % TPR == 0) rs[ml] = r;
     }
 #pragma unroll
     for (int i = 0; i < WNF; ++i)
@@ -657,36 +667,8 @@ __global__ __launch_bounds__(512, 2) void pf_part_kernel(PfArgs a, f32x4* __rest
     }
 }
 
-// Sums of N neighbouring weight tiles T0.. (of one panel) and row tile mt, in the order of K.  All the loads of up to eight
-// parts go out before the first is used.
-template <int N>
-__device__ __forceinline__ void pf_sum_parts(const PfArgs& a, int MTL, const f32x4* __restrict__ part, int mt, int T0, int lane, f32x4 (&v)[N]) {
-    const int p = (T0 / PF_NTL) * a.n_wgM + mt / MTL;
-    const int w0 = p * a.KT / a.unit, n = ((p + 1) * a.KT - 1) / a.unit - w0 + 1;
-    const size_t slot = (size_t)PF_NTL * MTL * 64;
-    const f32x4* q = part + (size_t)(w0 + p) * slot + ((T0 % PF_NTL) * MTL + mt % MTL) * 64 + lane;
-#pragma unroll
-    for (int i = 0; i < N; ++i) v[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s = 0; s < n; s += 8) {
-        f32x4 u[8][N];
-#pragma unroll
-        for (int h = 0; h < 8; h += 4)
-            if (s + h < n) {  // (uniform)
-#pragma unroll
-                for (int k = h; k < h + 4; ++k)
-#pragma unroll
-                    for (int i = 0; i < N; ++i) u[k][i] = q[(size_t)(s + k < n ? s + k : s) * slot + i * MTL * 64];
-            }
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-#pragma unroll
-            for (int i = 0; i < N; ++i)
-                if (s + k < n) v[i] += u[k][i];
-    }
-}
-
 // 16 rows x 256 columns per workgroup, a wave two tiles
-__global__ __launch_bounds__(512) void pf_resid_sum_kernel(PfArgs a, PfResid e, int MTL, const f32x4* __restrict__ part) {
+__global__ __launch_bounds__(512) void pf_resid_sum_kernel(PfArgs a, PfResid e, PartGeom pg, const f32x4* __restrict__ part) {
     __shared__ float red[8][16];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     const int cg = blockIdx.x % a.n_wgN, mt = blockIdx.x / a.n_wgN;
@@ -701,7 +683,7 @@ __global__ __launch_bounds__(512) void pf_resid_sum_kernel(PfArgs a, PfResid e, 
             gn[i] = *(const f32x4*)(e.g_next + n);
             gh[i] = e.g_head ? *(const f32x4*)(e.g_head + n) : f32x4{0.f, 0.f, 0.f, 0.f};
         }
-        pf_sum_parts<2>(a, MTL, part, mt, T0, lane, v);
+        sum_parts<2>(pg, part, mt, T0, lane, v);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int n = (T0 + i) * 16 + rg * 4;
@@ -749,7 +731,7 @@ __device__ __forceinline__ float pf_row_scale(const PfArgs& a, int m, int rg) {
 }
 
 // 16 rows x 128 columns per workgroup, a wave two tiles
-__global__ __launch_bounds__(256) void pf_qkv_sum_kernel(PfArgs a, PfQkv e, int MTL, const f32x4* __restrict__ part) {
+__global__ __launch_bounds__(256) void pf_qkv_sum_kernel(PfArgs a, PfQkv e, PartGeom pg, const f32x4* __restrict__ part) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     const int n_cg = (a.n_tiles + 7) / 8, cg = blockIdx.x % n_cg, mt = blockIdx.x / n_cg;
     const int m = mt * 16 + li, mv = m < a.M ? m : a.M - 1, T0 = cg * 8 + wave * 2;
@@ -757,13 +739,13 @@ __global__ __launch_bounds__(256) void pf_qkv_sum_kernel(PfArgs a, PfQkv e, int 
     const float r = pf_row_scale(a, mv, rg);
     const PfQkvRow w = pf_qkv_row(e, mv, r);
     f32x4 v[2];
-    pf_sum_parts<2>(a, MTL, part, mt, T0, lane, v);
+    sum_parts<2>(pg, part, mt, T0, lane, v);
     if (m >= a.M) return;
     pf_qkv_store(e, w, T0, v[0], rg);
     pf_qkv_store(e, w, T0 + 1, v[1], rg);
 }
 
-__global__ __launch_bounds__(256) void pf_swiglu_sum_kernel(PfArgs a, __bf16* act_hi, __bf16* act_lo, int F, int MTL,
+__global__ __launch_bounds__(256) void pf_swiglu_sum_kernel(PfArgs a, __bf16* act_hi, __bf16* act_lo, int F, PartGeom pg,
                                                             const f32x4* __restrict__ part) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     const int n_cg = (a.n_tiles + 7) / 8, cg = blockIdx.x % n_cg, mt = blockIdx.x / n_cg;
@@ -771,7 +753,7 @@ __global__ __launch_bounds__(256) void pf_swiglu_sum_kernel(PfArgs a, __bf16* ac
     if (T0 >= a.n_tiles) return;
     const float r = pf_row_scale(a, m < a.M ? m : a.M - 1, rg);
     f32x4 v[2];
-    pf_sum_parts<2>(a, MTL, part, mt, T0, lane, v);
+    sum_parts<2>(pg, part, mt, T0, lane, v);
     pf_swiglu_store(act_hi, act_lo, m, m < a.M, T0, F / 32, v[0] * r, rg);
     pf_swiglu_store(act_hi, act_lo, m, m < a.M, T0 + 1, F / 32, v[1] * r, rg);
 }
@@ -808,15 +790,26 @@ struct PfHead {
     int V;
     const int32_t* target;  // per row: the token whose logit is wanted (negative: none), or NULL
     float* target_logit;    // per row: that logit
+    float* logits;          // [row][V], or NULL (64-row tile: the heads of a decode step)
 };
 
+// exponential of a head: the hardware's for scored positions, the library's where a decode step decides by it
+template <bool DECIDES>
+__device__ __forceinline__ float pf_exp(float x) {
+    if constexpr (DECIDES)
+        return expf(x);
+    else
+        return __expf(x);
+}
+
+template <bool DECIDES = false>
 __device__ __forceinline__ void pf_merge(float& m, float& s, int& i, float m2, float s2, int i2) {
     if (m2 > m || (m2 == m && i2 < i)) {
-        s = s * __expf(m - m2) + s2;
+        s = s * pf_exp<DECIDES>(m - m2) + s2;
         m = m2;
         i = i2;
     } else if (m2 > -INFINITY) {
-        s = s + s2 * __expf(m2 - m);
+        s = s + s2 * pf_exp<DECIDES>(m2 - m);
     }
 }
 
@@ -857,6 +850,9 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel
                     ix = n + q;
                 }
             }
+            if constexpr (MTL == 4) {
+                if (e.logits != nullptr && m_row < a.M) *(f32x4*)(e.logits + (size_t)m_row * e.V + n) = acc[i][j];
+            }
             if ((unsigned)(tgt - n) < 4u) {  // (exactly one lane of one workgroup holds the wanted token's logit)
                 const int q = tgt - n;
                 e.target_logit[m_row] = q == 0 ? acc[i][j][0] : q == 1 ? acc[i][j][1] : q == 2 ? acc[i][j][2] : acc[i][j][3];
@@ -869,7 +865,7 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel
             const int n = (t.nt0 + t.wn * WNF + i) * 16 + rg * 4;
             if (n >= e.V) continue;
 #pragma unroll
-            for (int q = 0; q < 4; ++q) sm += __expf(acc[i][j][q] - mx);
+            for (int q = 0; q < 4; ++q) sm += pf_exp<MTL == 4>(acc[i][j][q] - mx);
         }
         // the four lane groups of a row, in a fixed order (even row then odd row, lower half then upper half: every
         // lane forms the same merge, so all four groups end up equal)
@@ -879,12 +875,12 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel
             row_pair_of(sm, s0, s1);
             row_pair_of(__int_as_float(ix), i0, i1);
             int ia = __float_as_int(i0);
-            pf_merge(m0, s0, ia, m1, s1, __float_as_int(i1));
+            pf_merge<MTL == 4>(m0, s0, ia, m1, s1, __float_as_int(i1));
             halves_of(m0, mx, m1);
             halves_of(s0, sm, s1);
             halves_of(__int_as_float(ia), i0, i1);
             ix = __float_as_int(i0);
-            pf_merge(mx, sm, ix, m1, s1, __float_as_int(i1));
+            pf_merge<MTL == 4>(mx, sm, ix, m1, s1, __float_as_int(i1));
         }
         if (t.wn > 0 && rg == 0) {
             red[(2 * (t.wn - 1)) * (MTL * 16) + ml] = mx;
@@ -902,7 +898,7 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel
             int ix = ixs[j];
 #pragma unroll
             for (int wv = 1; wv < WN; ++wv)
-                pf_merge(mx, sm, ix, red[(2 * (wv - 1)) * (MTL * 16) + ml], red[(2 * (wv - 1) + 1) * (MTL * 16) + ml],
+                pf_merge<MTL == 4>(mx, sm, ix, red[(2 * (wv - 1)) * (MTL * 16) + ml], red[(2 * (wv - 1) + 1) * (MTL * 16) + ml],
                          redi[(wv - 1) * (MTL * 16) + ml]);
             const int m = t.mt0 * 16 + ml;
             if (m < a.M) {
@@ -1245,6 +1241,7 @@ PfArgs pf_args(const PfGemm& g, int MTL) {
     a.m_tiles = (g.M + 15) / 16;
     a.n_wgN = (a.n_tiles + PF_NTL - 1) / PF_NTL;
     a.unit = 0;
+    a.arow = nullptr;
     a.n_wgM = (g.M + MTL * 16 - 1) / (MTL * 16);
     a.M = g.M;
     a.N = g.N;
@@ -1285,40 +1282,50 @@ hipError_t pf_launch_part(const PfArgs& a, void* part, hipStream_t s) {
 
 int pf_part_mtl(int M) { return M <= 64 ? 4 : 8; }
 
-// k-tiles per workgroup: an even share, but no fewer than eight (a part costs its writing and reading)
-int pf_part_unit(int tiles, int KT) {
-    int u = (int)(((long)tiles * KT + PF_CUS - 1) / PF_CUS);
-    if (u < 8) u = 8;
-    return u < KT ? u : KT;
+// Geometry of the cut of an N x K matrix over M rows: every workgroup an even share, but no fewer than eight k-tiles (a
+// part costs its writing and reading) and no more parts than fit `bytes`.  False: it cannot be cut so.
+bool pf_part_geom(int N, int K, int M, size_t bytes, PartGeom* g) {
+    g->mtl = pf_part_mtl(M);
+    g->KT = K / 32;
+    g->n_tiles = N / 16;
+    g->n_wgN = (g->n_tiles + PF_NTL - 1) / PF_NTL;
+    g->n_wgM = (M + g->mtl * 16 - 1) / (g->mtl * 16);
+    g->m_tiles = (M + 15) / 16;
+    const long tiles = (long)g->n_wgN * g->n_wgM;
+    if (tiles > PF_PART_TILES || g->n_tiles % 2) return false;
+    const long wgs = std::min<long>(PF_CUS, (long)(bytes / ((size_t)PF_NTL * g->mtl * 1024)) - tiles);
+    if (wgs < 1) return false;
+    const long u = (tiles * g->KT + wgs - 1) / wgs;
+    if (u > g->KT) return false;
+    g->unit = (int)std::min<long>(std::max<long>(u, 8), g->KT);
+    return true;
 }
 
-// Is the even cut (pf_part_kernel and its sum) faster than a workgroup per result tile?  Both wait for what a CU takes in:
-// a direct launch `rounds` x KT x (16 + 2 mtl) KB, at 47 GB/s with 64-row tiles and 33 with 128-row tiles; the cut its
-// unit's share of that at 33 GB/s, plus writing one or two parts, reading all of them back, and a second launch.  Fitted
-// to the times of all four GEMMs at 768 to 6656 wide, 40 to 1024 rows (per layer, 7B widths, 99 rows, direct and cut: Q|K|V 65
-// -> 46 us, O 60 -> 25, gate|up 67 -> 58, down 135 -> 38; 64 rows: 60 -> 33, 60 -> 21, 66 -> 42, 130 -> 30; 256
-// rows: gate|up 123 -> 103, down 140 -> 60, Q|K|V stays direct).
-bool pf_cut_pays(const PfGemm& g, int mtl_direct) {
-    const int KT = g.K / 32, n_wgN = (g.N + 255) / 256, mtl = pf_part_mtl(g.M);
-    const int tiles = n_wgN * ((g.M + mtl * 16 - 1) / (mtl * 16));
-    if (tiles > PF_PART_TILES) return false;
-    const int unit = pf_part_unit(tiles, KT), wgs = (tiles * KT + unit - 1) / unit;
-    const float part_kb = 16.0f * mtl;
-    const float cut = unit * (16 + 2 * mtl) / 33.0f + part_kb * (1.0f + (float)tiles / wgs) / 60.0f + (wgs + tiles) * part_kb / 5000.0f + 5.0f;
-    const long direct_tiles = (long)n_wgN * ((g.M + mtl_direct * 16 - 1) / (mtl_direct * 16));
+// What the cut and its sum take, in microseconds: what a CU takes in bounds it, at 33 GB/s, then come writing one or two
+// parts, reading all of them back, and a second launch.
+float pf_cut_us(const PartGeom& g) {
+    const int tiles = g.n_wgN * g.n_wgM, wgs = (tiles * g.KT + g.unit - 1) / g.unit;
+    const float part_kb = 16.0f * g.mtl;
+    return g.unit * (16 + 2 * g.mtl) / 33.0f + part_kb * (1.0f + (float)tiles / wgs) / 60.0f + (wgs + tiles) * part_kb / 5000.0f + 5.0f;
+}
+
+// Is it faster than a workgroup per result tile?  Such a launch takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at 47
+// GB/s with 64-row tiles and 33 with 128-row tiles.  Both fitted to the times of all four GEMMs at 768 to 6656 wide, 40 to
+// 1024 rows (per layer, 7B widths, 99 rows, direct and cut: Q|K|V 65 -> 46 us, O 60 -> 25, gate|up 67 -> 58, down 135 ->
+// 38; 64 rows: 60 -> 33, 60 -> 21, 66 -> 42, 130 -> 30; 256 rows: gate|up 123 -> 103, down 140 -> 60, Q|K|V stays direct).
+bool pf_cut_pays(const PfGemm& g, int mtl_direct, PartGeom* pg) {
+    if (!pf_part_geom(g.N, g.K, g.M, g.part_bytes, pg)) return false;
+    const long direct_tiles = (long)pg->n_wgN * ((g.M + mtl_direct * 16 - 1) / (mtl_direct * 16));
     const long rounds = (direct_tiles + PF_CUS - 1) / PF_CUS;
-    const float direct = rounds * KT * (16 + 2 * mtl_direct) / (mtl_direct == 4 ? 47.0f : 33.0f) + 2.0f;
-    return cut < direct;
+    return pf_cut_us(*pg) < rounds * pg->KT * (16 + 2 * mtl_direct) / (mtl_direct == 4 ? 47.0f : 33.0f) + 2.0f;
 }
 
-// The partial sums of g (see pf_part_kernel); *a and *mtl are what the summing kernel needs.
-hipError_t pf_part(const PfGemm& g, PfArgs* a, int* mtl, hipStream_t s) {
-    *mtl = pf_part_mtl(g.M);
-    *a = pf_args(g, *mtl);
-    a->unit = pf_part_unit(a->n_wgN * a->n_wgM, a->KT);
-    PfArgs b = *a;
-    b.ssq = nullptr;
-    return *mtl == 8 ? pf_launch_part<8>(b, g.part, s) : pf_launch_part<4>(b, g.part, s);
+// The partial sums of g (see pf_part_kernel), cut as pg says.
+hipError_t pf_part(const PfGemm& g, const PartGeom& pg, hipStream_t s) {
+    PfArgs a = pf_args(g, pg.mtl);
+    a.unit = pg.unit;
+    a.ssq = nullptr;
+    return pg.mtl == 8 ? pf_launch_part<8>(a, g.part, s) : pf_launch_part<4>(a, g.part, s);
 }
 
 }  // namespace
@@ -1326,6 +1333,22 @@ hipError_t pf_part(const PfGemm& g, PfArgs* a, int* mtl, hipStream_t s) {
 size_t pf_part_bytes(int max_rows, int max_N) {
     const int tiles = std::min(PF_PART_TILES, (max_N + 255) / 256 * ((max_rows + 63) / 64));
     return (size_t)(PF_CUS + tiles + 8) * (PF_NTL * 8) * 1024;
+}
+
+bool cut_pays_over(int N, int K, int M, size_t bytes, float other_us, PartGeom* pg) {
+    return pf_part_geom(N, K, M, bytes, pg) && pf_cut_us(*pg) < other_us;
+}
+
+hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N, int K, int M, void* part, const PartGeom& pg, hipStream_t s) {
+    PfGemm g{};
+    g.W = W;
+    g.N = N;
+    g.K = K;
+    g.A_hi = A_hi;
+    g.A_lo = A_lo;
+    g.M = M;
+    g.part = part;
+    return pf_part(g, pg, s);
 }
 
 #define PF_DISPATCH(KERNEL, WIDE, ...)                                                                        \
@@ -1351,12 +1374,12 @@ hipError_t launch_pf_qkv(const PfGemm& g, void* q_hi, void* q_lo, const float* r
     const int d = g.N / 3;
     PfQkv e{(__bf16*)q_hi, (__bf16*)q_lo, d, kv.H, kv.hd, (const float2*)rope_cs, (__bf16*)kv.pool + (size_t)layer * kv.layer_stride,
             kv.blk_stride, kv.BT, bt, p0};
-    if (pf_cut_pays(g, pf_mtl(g))) {
-        PfArgs a;
-        int mtl;
-        const hipError_t err = pf_part(g, &a, &mtl, s);
+    PartGeom pg;
+    if (pf_cut_pays(g, pf_mtl(g), &pg)) {
+        const PfArgs a = pf_args(g, pg.mtl);
+        const hipError_t err = pf_part(g, pg, s);
         if (err != hipSuccess) return err;
-        EE_LAUNCH(pf_qkv_sum_kernel, dim3((a.n_tiles + 7) / 8 * a.m_tiles), dim3(256), s, a, e, mtl, (const f32x4*)g.part);
+        EE_LAUNCH(pf_qkv_sum_kernel, dim3((a.n_tiles + 7) / 8 * a.m_tiles), dim3(256), s, a, e, pg, (const f32x4*)g.part);
         return hipGetLastError();
     }
     PF_DISPATCH(pf_qkv_kernel, true, e);
@@ -1368,12 +1391,12 @@ hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, 
     // (With more than four row tiles of a few column panels the ranges of one panel's row tiles no longer run side by side,
     // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 4 us for O and 9 us for down.)
     const int cut_tiles = (g.N + 255) / 256 * ((g.M + 127) / 128);
-    if (cut_tiles <= 64 && pf_cut_pays(g, pf_mtl(g))) {
-        PfArgs a;
-        int mtl;
-        const hipError_t err = pf_part(g, &a, &mtl, s);
+    PartGeom pg;
+    if (cut_tiles <= 64 && pf_cut_pays(g, pf_mtl(g), &pg)) {
+        const PfArgs a = pf_args(g, pg.mtl);
+        const hipError_t err = pf_part(g, pg, s);
         if (err != hipSuccess) return err;
-        EE_LAUNCH(pf_resid_sum_kernel, dim3(a.n_wgN * a.m_tiles), dim3(512), s, a, e, mtl, (const f32x4*)g.part);
+        EE_LAUNCH(pf_resid_sum_kernel, dim3(a.n_wgN * a.m_tiles), dim3(512), s, a, e, pg, (const f32x4*)g.part);
         return hipGetLastError();
     }
     // Two workgroups per CU (four waves per SIMD) once the grid has more workgroups than CUs (30B widths at 2048
@@ -1412,12 +1435,12 @@ hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, 
 }
 
 hipError_t launch_pf_swiglu(const PfGemm& g, void* act_hi, void* act_lo, int F, hipStream_t s) {
-    if (pf_cut_pays(g, pf_mtl(g))) {
-        PfArgs a;
-        int mtl;
-        const hipError_t err = pf_part(g, &a, &mtl, s);
+    PartGeom pg;
+    if (pf_cut_pays(g, pf_mtl(g), &pg)) {
+        const PfArgs a = pf_args(g, pg.mtl);
+        const hipError_t err = pf_part(g, pg, s);
         if (err != hipSuccess) return err;
-        EE_LAUNCH(pf_swiglu_sum_kernel, dim3((a.n_tiles + 7) / 8 * a.m_tiles), dim3(256), s, a, (__bf16*)act_hi, (__bf16*)act_lo, F, mtl,
+        EE_LAUNCH(pf_swiglu_sum_kernel, dim3((a.n_tiles + 7) / 8 * a.m_tiles), dim3(256), s, a, (__bf16*)act_hi, (__bf16*)act_lo, F, pg,
                   (const f32x4*)g.part);
         return hipGetLastError();
     }
@@ -1427,7 +1450,7 @@ hipError_t launch_pf_swiglu(const PfGemm& g, void* act_hi, void* act_lo, int F, 
 hipError_t launch_pf_head(const PfGemm& g, HeadPartial* partials, int32_t* tok, float* conf, const int32_t* target,
                           float* target_logit, float* nll, bool two_terms, hipStream_t s) {
     const int n_wg = (g.N + 255) / 256;
-    PfHead e{partials, g.N, nll ? target : nullptr, target_logit};
+    PfHead e{partials, g.N, nll ? target : nullptr, target_logit, nullptr};
     PfArgs a = pf_args(g, 8);
     if (two_terms) {
         // (8 waves, two workgroups per CU, two stages: 633 us at 1024 rows; 4 waves with two workgroups per CU measured
@@ -1449,6 +1472,30 @@ hipError_t launch_pf_head(const PfGemm& g, HeadPartial* partials, int32_t* tok, 
     }
     EE_LAUNCH(pf_head_merge_kernel, dim3(g.M), dim3(64), s, (const HeadPartial*)partials, n_wg, g.M, tok, conf,
               nll ? target : (const int32_t*)nullptr, (const float*)target_logit, nll);
+    return hipGetLastError();
+}
+
+// One head over up to 64 rows of a decode step (operand order, both terms): one partial per row and 256 logits.
+hipError_t launch_head64(const void* W, const void* A_hi, const void* A_lo, int V, int d, int M, const float* ssq, int ssq_n,
+                         const int32_t* arow, float inv_d, float eps, HeadPartial* partials, float* logits, hipStream_t s) {
+    PfGemm g{};
+    g.W = W;
+    g.N = V;
+    g.K = d;
+    g.A_hi = A_hi;
+    g.A_lo = A_lo;
+    g.ssq = ssq;
+    g.ssq_n = ssq_n;
+    g.inv_d = inv_d;
+    g.eps = eps;
+    g.M = M;
+    PfArgs a = pf_args(g, 4);
+    a.arow = arow;
+    PfHead e{partials, V, nullptr, nullptr, logits};
+    constexpr size_t lds_b = pf_lds_bytes<4, 8, true>();
+    static hipError_t once = pf_set_lds(pf_head_kernel<4, 8, true>, lds_b);
+    if (once != hipSuccess) return once;
+    EE_LAUNCH_SM((pf_head_kernel<4, 8, true>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, e);
     return hipGetLastError();
 }
 

@@ -16,17 +16,20 @@ pytestmark = pytest.mark.gpu
 SHAPES = {
     "d128": ModelShape(3, 128, 4, 32, 352, 1056, (1,), "bf16", 0.02, 0.3),
     "d192": ModelShape(2, 192, 3, 64, 224, 544, (1,), "bf16", 0.02, 0.3),
+    # wide enough that from 33 rows on projections are cut over K (65 k-tiles, 17 panels of which the last holds one pair)
+    "d1024": ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5),
 }
+ROWS = {"d1024": (33, 64, 66, 128, 129)}
 
 
-@pytest.mark.parametrize("name,min_wgs", [("d128", 0), ("d192", 0), ("d128", 16), ("d192", 6)])
+@pytest.mark.parametrize("name,min_wgs", [("d128", 0), ("d192", 0), ("d128", 16), ("d192", 6), ("d1024", 0)])
 def test_full_depth_step_over_a_given_number_of_rows(name, min_wgs):
     shape = SHAPES[name]
     om = build_model(shape, 5, gain_jitter=0.1)
-    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=128, max_rows=128, max_seqs=4, gemm_min_workgroups=min_wgs)
+    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=128, max_rows=160, max_seqs=4, gemm_min_workgroups=min_wgs)
     n_seq, cap = 4, 40
     fed = [prompt_tokens(shape.vocab, 80, 60 + s).numpy().astype(np.int32) for s in range(n_seq)]
-    for rows in (1, 2, 3, 4, 5, 16, 17, 32, 33, 64, 66, 80, 81):
+    for rows in ROWS.get(name, (1, 2, 3, 4, 5, 16, 17, 32, 33, 64, 66, 80, 81)):
         print(f"case: {name} tiles {min_wgs} rows {rows}", flush=True)
         ids = list(range(min(n_seq, rows)))
         lens = [7 + 5 * s for s in ids]
@@ -67,3 +70,39 @@ def test_short_prompts_whose_gemms_are_cut_over_the_contraction(n, rows_env):
     print(f"case: cut prompt n={n} rows_env={rows_env}", flush=True)
     shape = ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5)
     check_prefill(shape, n, 4, rows_env=rows_env, scored=False)
+
+
+def test_head_over_more_than_half_a_batch_of_rows():
+    """A step of 33 and of 64 sequences with a vocabulary of 129 column panels of 256 (the last one ragged): logits, arg max
+    and confidence of the final head as each sequence gets them in a step of its own."""
+    shape = ModelShape(2, 128, 4, 32, 352, 128 * 256 + 96, (1,), "bf16", 0.02, 0.3)
+    gm = load_gpu_model(shape, 6, gain_jitter=0.1, max_positions=64, max_rows=64, max_seqs=64)
+    logits = gm.enable_logits(64)
+    for n in (33, 64):
+        print(f"case: head over {n} rows", flush=True)
+        ids = list(range(n))
+        got = []
+        for groups in ([ids], [[s] for s in ids]):
+            cache = ee.KvCache(gm, 64, 64 * 64, 32, 4)
+            seqs = ee.Sequences(shape.n_layers)
+            z, tok, cf = [], [], []
+            for s in ids:
+                p = prompt_tokens(shape.vocab, 3 + s % 5, 90 + s).numpy()
+                t, _, _ = ee.prefill(gm, cache, s, p, 1.0)
+                seqs.start(s, t)
+            for g in groups:
+                ro, tk, pm = seqs.rows(g)
+                nt, ex, c = ee.decode_step(gm, cache, g, ro, tk, pm, 1.0)
+                z.append(logits[: len(g)].cpu().numpy().copy())
+                tok.extend(int(t) for t in nt)
+                cf.extend(float(v) for v in c)
+            cache.close()
+            got.append((np.concatenate(z), tok, cf))
+        (za, ta, ca), (zb, tb, cb) = got
+        assert rel_err(za, zb) <= TOL["bf16"]
+        for s in ids:
+            top = np.sort(zb[s])[-2:]
+            assert ta[s] == int(za[s].argmax()) and (ta[s] == tb[s] or top[1] - top[0] < 1e-2), s
+            want = 1.0 / np.exp(za[s].astype(np.float64) - za[s].max()).sum()
+            assert abs(ca[s] - want) <= 1e-5 * want, (s, ca[s], want)  # 32-bit exponentials and sums over 32864 terms
+    gm.close()
