@@ -871,13 +871,21 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
                 if (nd->T > 0 && (m->cfg.dtype != EE_BF16 || (nd->T <= 16 && nd->T * m->cfg.d_model <= 17408))) {
                     EECHK(run_layers(m, c, s + 1, nd->T, nd->n_qt, m->seg_begin(s + 1), m->seg_end(s + 1), max_ctx, st, BLOCK_FRONT, &spec_ns));
                     spec_seg = s + 1;
-                    HIPCHK(hipEventRecord(m->spec_ev, st));
-                    m->spec_stream = st;
-                    m->spec_recorded = true;
                     c->spec_used = true;
                 }
             }
-            EECHK(wait_head_results(m, hd, st));
+            // (The event that other streams wait for is recorded only where the call returns with those kernels in flight: in
+            // a step that goes on, each record is a barrier between the attention and the O projection.)
+            auto leave_in_flight = [&]() -> int {
+                HIPCHK(hipEventRecord(m->spec_ev, st));
+                m->spec_stream = st;
+                m->spec_recorded = true;
+                return EE_OK;
+            };
+            if (const int rc = wait_head_results(m, hd, st)) {
+                if (spec_seg == s + 1) (void)leave_in_flight();
+                return rc;
+            }
             int fired_now = 0;
             for (int i = 0; i < hd->n_head; ++i) {
                 int slot = hd->head_slot[i];
@@ -894,6 +902,7 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
                 }
             }
             n_active -= fired_now;
+            if (n_active == 0 && spec_seg == s + 1) EECHK(leave_in_flight());
             if (fired_now && n_active > 0 && !is_final) EECHK(rebuild(s + 1));
         }
         if (is_final) {
