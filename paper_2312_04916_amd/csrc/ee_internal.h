@@ -92,7 +92,7 @@ struct GemmCommon {
     int ssq_stride, ssq_n;
     float inv_d, eps;
     int T;  // rows
-    int min_wgs;  // workgroups a launch keeps when it gives a workgroup several column tiles (0: 512)
+    int min_wgs;  // ee_config::gemm_min_workgroups
     const SegDesc* desc;
     const SegDesc* desc_host;  // host copy of *desc, or NULL: launches of up to 16 rows then carry the row indices by value
     // O projection only: A still lies as the attention kernel's split partials (att_ns splits), to be merged

@@ -1864,7 +1864,7 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t*
     int n_parts = c.N / 16;
     if (c.dtype == EE_BF16 && c.a_packed && c.T > 32 && c.min_wgs <= 0 && c.ssq_stride == c.ssq_n && c.N >= 128 * 256) {
         // (a vocabulary of at least half as many 256-column panels as there are CUs; 64 rows, 50304 words, 4096 wide: 128 ->
-        // 75 us)
+        // 98 us)
         n_parts = (c.N + 255) / 256;
         const hipError_t err = launch_head64(c.W, c.A, (const char*)c.A + c.a_lo * 2, c.N, c.K, c.T, c.ssq, c.ssq_n, c.arow, c.inv_d, c.eps,
                                              partials, logits, s);
