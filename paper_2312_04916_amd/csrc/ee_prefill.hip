@@ -845,7 +845,8 @@ __global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const float z = acc[i][j][q];
-                if (z > mx) {
+                // (a decode step returns this index as the next token: logits that are all -inf have one too)
+                if (z > mx || (MTL == 4 && z == mx && ix == 0x7fffffff)) {
                     mx = z;
                     ix = n + q;
                 }

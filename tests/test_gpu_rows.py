@@ -3,6 +3,7 @@ count at which the projections change kernel, row tile or pass (3 | 4 staged / p
 rows), on widths that leave ragged column groups, with one and with several column tiles per workgroup."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2312_04916_amd as ee
 from oracle.from_workload import build_model
@@ -105,4 +106,36 @@ def test_head_over_more_than_half_a_batch_of_rows():
             assert ta[s] == int(za[s].argmax()) and (ta[s] == tb[s] or top[1] - top[0] < 1e-2), s
             want = 1.0 / np.exp(za[s].astype(np.float64) - za[s].max()).sum()
             assert abs(ca[s] - want) <= 1e-5 * want, (s, ca[s], want)  # 32-bit exponentials and sums over 32864 terms
+    gm.close()
+
+
+def test_head_whose_logits_are_all_minus_infinity():
+    """Every logit of every row overflows to -inf: the token is the lowest index whichever kernel the head runs in (32 rows:
+    16-column tiles, 33: 256-column panels), and can be fed back."""
+    shape = ModelShape(2, 128, 4, 32, 352, 128 * 256 + 96, (1,), "bf16", 0.02, 0.3)
+    gm = load_gpu_model(shape, 6, max_positions=64, max_rows=64, max_seqs=33)
+    bf16 = dict(dtype=torch.bfloat16, device="cuda:0")
+    for l in range(shape.n_layers):  # the layers add nothing: x stays the embedding row
+        gm.set_tensor(ee.EE_T_WO, l, torch.zeros(128, 128, **bf16))
+        gm.set_tensor(ee.EE_T_WD, l, torch.zeros(128, 352, **bf16))
+    embed = torch.zeros(shape.vocab, 128, **bf16)
+    embed[:, 0] = 4.0
+    head = torch.zeros(shape.vocab, 128, **bf16)
+    head[:, 0] = -3.0e38  # times 4 times the RMS scale: past the largest float32
+    gm.set_tensor(ee.EE_T_EMBED, 0, embed)
+    gm.set_tensor(ee.EE_T_FINAL_HEAD, 0, head)
+    logits = gm.enable_logits(33)
+    for n in (32, 33):
+        print(f"case: all logits -inf over {n} rows", flush=True)
+        cache = ee.KvCache(gm, 33, 33 * 64, 32, 4)
+        seqs = ee.Sequences(shape.n_layers)
+        for s in range(n):
+            seqs.start(s, ee.prefill(gm, cache, s, [1, 2, 3], 1.0)[0])
+        for _ in range(2):
+            ro, tk, pm = seqs.rows(list(range(n)))
+            nt, ex, _ = ee.decode_step(gm, cache, list(range(n)), ro, tk, pm, 1.0)
+            assert bool(torch.isneginf(logits[:n]).all())
+            assert list(nt) == [0] * n
+            seqs.update(list(range(n)), nt, ex)
+        cache.close()
     gm.close()
