@@ -186,6 +186,15 @@ int ee_model_free(ee_model* m);
  * non-increasing, EE_ERR_ARG on bad counts. */
 int ee_debug_plan(int n_segments, int32_t* filled, int position, int max_pending, int refeed, int reached,
                   int32_t* forced, int32_t* row_lo, int32_t* row_hi);
+/* Test hook, host only: the kernels that a GEMM of `rows` rows runs in, in a bf16 model of these sizes (EE_ERR_CONFIG for
+ * fp32).  kernel: EE_K_QKV, _OPROJ, _SWIGLU, _DOWN, or _HEAD (decode steps only).  prompt = 0: a decode step whose
+ * segment carries that many rows (heads: that many sequences); prompt = 1: a pass of the prompt phase.
+ *   EE_ROUTE_STAGED  few rows, staged in LDS
+ *   EE_ROUTE_ROWS    many rows in operand order (prompt phase: one workgroup per result tile)
+ *   EE_ROUTE_CUT     cut along the contraction, the parts added up by a second kernel
+ *   EE_ROUTE_PANELS  a head in panels of 256 columns */
+enum { EE_ROUTE_STAGED = 0, EE_ROUTE_ROWS = 1, EE_ROUTE_CUT = 2, EE_ROUTE_PANELS = 3 };
+int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route);
 /* Measurement hook: the confidence every head reported in the latest ee_decode_step, conf[n_seqs][n_exits+1] (host;
  * row b = the b-th sequence of that call, column i = exit i, last column = final head); -1 where the head was not
  * evaluated for that sequence in that step (the token had left at a shallower exit, exits disabled or step forced).

@@ -13,12 +13,13 @@ import torch
 EE_F32, EE_BF16 = 0, 1
 EE_MAX_ROWS, EE_MAX_SEQS, EE_MAX_EXITS = 256, 64, 8
 EE_K_QKV, EE_K_ATTN, EE_K_OPROJ, EE_K_SWIGLU, EE_K_DOWN, EE_K_HEAD = range(6)
+EE_ROUTE_STAGED, EE_ROUTE_ROWS, EE_ROUTE_CUT, EE_ROUTE_PANELS = range(4)
 KERNEL_NAMES = ["qkv", "attention", "oproj", "swiglu", "down", "head"]
 (EE_T_EMBED, EE_T_ATTN_NORM, EE_T_WQ, EE_T_WK, EE_T_WV, EE_T_WO, EE_T_MLP_NORM, EE_T_WG, EE_T_WU, EE_T_WD,
  EE_T_EXIT_NORM, EE_T_EXIT_HEAD, EE_T_FINAL_NORM, EE_T_FINAL_HEAD) = range(14)
 
 EXPORTS = ["ee_strerror", "ee_last_hip_error", "ee_model_bytes", "ee_model_create", "ee_model_set_tensor",
-           "ee_model_load", "ee_model_free", "ee_debug_set_logits", "ee_debug_step_confidences", "ee_debug_plan", "ee_profile_begin", "ee_profile_end", "ee_profile_every", "ee_measure_stream_read", "ee_debug_lane_reductions", "ee_kv_cache_bytes", "ee_kv_cache_create",
+           "ee_model_load", "ee_model_free", "ee_debug_set_logits", "ee_debug_step_confidences", "ee_debug_plan", "ee_debug_gemm_route", "ee_profile_begin", "ee_profile_end", "ee_profile_every", "ee_measure_stream_read", "ee_debug_lane_reductions", "ee_kv_cache_bytes", "ee_kv_cache_create",
            "ee_kv_cache_set_refeed", "ee_kv_cache_set_pipeline", "ee_kv_cache_reset", "ee_kv_cache_filled", "ee_kv_cache_pending", "ee_kv_cache_read",
            "ee_kv_cache_flush", "ee_kv_cache_free", "ee_debug_read_hidden", "ee_prefill", "ee_prefill_scored",
            "ee_decode_step", "ee_decode_step_static"]
@@ -73,6 +74,7 @@ def lib():
         L.ee_debug_set_logits.argtypes = [vp, vp, C.c_int]
         L.ee_debug_step_confidences.argtypes = [vp, C.c_int, fp]
         L.ee_debug_plan.argtypes = [C.c_int, i32p, C.c_int, C.c_int, C.c_int, C.c_int, i32p, i32p, i32p]
+        L.ee_debug_gemm_route.argtypes = [C.POINTER(ee_config), C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i32p]
         L.ee_profile_begin.argtypes = [vp, C.c_int, C.c_int]
         L.ee_profile_end.argtypes = [vp, i32p, fp]
         L.ee_profile_every.argtypes = [vp, C.c_int]
@@ -329,6 +331,13 @@ def plan(filled: Sequence[int], position: int, max_pending: int, refeed: bool = 
     _chk(lib().ee_debug_plan(n, f, int(position), int(max_pending), int(bool(refeed)), int(reached), C.byref(forced), lo, hi),
          "ee_debug_plan")
     return bool(forced.value), [(lo[i], hi[i]) for i in range(n)], [f[i] for i in range(n)]
+
+
+def gemm_route(cfg: ee_config, kernel: int, rows: int, prompt: bool = False, max_rows: int = EE_MAX_ROWS, max_seqs: int = EE_MAX_SEQS) -> int:
+    """ee_debug_gemm_route (host only) -> EE_ROUTE_*."""
+    r = C.c_int32()
+    _chk(lib().ee_debug_gemm_route(C.byref(cfg), max_rows, max_seqs, kernel, rows, int(prompt), C.byref(r)), "ee_debug_gemm_route")
+    return r.value
 
 
 def prefill(model: Model, cache: KvCache, seq: int, tokens: Sequence[int], threshold: float, stream=None):

@@ -444,8 +444,8 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
     const int d = cf.d_model, F = cf.d_ff, dt = cf.dtype;
     SegDesc* dd = m->dev_desc(di);
     const int32_t* xrow = (const int32_t*)((char*)dd + offsetof(SegDesc, xrow));
-    const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d, 3 * d);
-    const bool pk_F = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, F, d);
+    const bool pk_d = dt == EE_BF16 && !route::rows_staged(T, d, 3 * d);
+    const bool pk_F = dt == EE_BF16 && !route::rows_staged(T, F, d);
     char* xg_pk = m->ws + m->wsl.xg_pk;
     GemmCommon g{};
     g.dtype = dt;
@@ -480,7 +480,7 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
         HIPCHK(launch_attention(dt, m->ws + m->wsl.q, m->ws + m->wsl.attn, m->lo_rows(d), dd, g.desc_host, T, n_qt, m->dev_btab(), c->geom,
                                 kv_layer, d,
                                 (float*)(m->ws + m->wsl.attn_part), (int32_t*)(m->ws + m->wsl.counters) + 64, max_ctx,
-                                gemm_rows_fit_lds(dt, T, d, 3 * d) ? &att_ns : nullptr, pk_d, st));
+                                (dt == EE_BF16 && !pk_d) ? &att_ns : nullptr, pk_d, st));
     }
     if (phase == BLOCK_FRONT) {
         *att_ns_io = att_ns;
@@ -523,7 +523,7 @@ int run_layers(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int l0, int
     // More rows than a workgroup can stage in LDS: the GEMMs then take their row operands from packed arrays
     // (dense rows of this launch in MFMA operand order) that the producing epilogues write, and the segment
     // starts by packing the rows' x.g operands out of the residual store.
-    const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d, 3 * d);
+    const bool pk_d = dt == EE_BF16 && !route::rows_staged(T, d, 3 * d);
     if (pk_d && l0 < l1 && first_phase != BLOCK_REST)
         HIPCHK(launch_pack_rows(c->xg(), c->xs_lo, d, xrow, T, d, m->ws + m->wsl.xg_pk, m->lo_rows(d), st));
     for (int l = l0; l < l1; ++l) {
@@ -588,7 +588,7 @@ int run_exit_layer(ee_model* m, ee_kv_cache* c, int seg, const int32_t* src, boo
     if (T <= 0) return EE_OK;
     const int32_t* dst = (const int32_t*)((char*)m->dev_desc(me) + offsetof(SegDesc, xrow));
     HIPCHK(launch_copy_slots(dt, src, dst, T, d, c->x(), c->xgh(), c->xs_lo, c->ssq(), c->ssq_stride, st));
-    if (dt == EE_BF16 && !gemm_rows_fit_lds(dt, T, d, 3 * d))
+    if (dt == EE_BF16 && !route::rows_staged(T, d, 3 * d))
         HIPCHK(launch_pack_rows(c->xgh(), c->xs_lo, d, dst, T, d, m->ws + m->wsl.xg_pk, m->lo_rows(d), st));
     const BlockW w{m->wbase + m->wl.eqkv[seg], m->wbase + m->wl.ewo[seg], m->wbase + m->wl.egu[seg], m->wbase + m->wl.ewd[seg],
                    m->gain(m->wl.gm[seg])};
@@ -629,8 +629,8 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
         const int32_t* src = (const int32_t*)((char*)dd + offsetof(SegDesc, head_xrow));
         const int32_t* dst = (const int32_t*)((char*)ed + offsetof(SegDesc, xrow));
         HIPCHK(launch_copy_slots(dt, src, dst, n_head, d, c->x(), c->xgh(), c->xs_lo, c->ssq(), c->ssq_stride, st));
-        const bool pk_d = dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, d, 3 * d);
-        const bool pk_F = dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, cf.d_ff, d);
+        const bool pk_d = dt == EE_BF16 && !route::rows_staged(n_head, d, 3 * d);
+        const bool pk_F = dt == EE_BF16 && !route::rows_staged(n_head, cf.d_ff, d);
         if (pk_d) HIPCHK(launch_pack_rows(c->xgh(), c->xs_lo, d, dst, n_head, d, m->ws + m->wsl.xg_pk, m->lo_rows(d), st));
         g.desc = ed;
         g.desc_host = eh;
@@ -650,7 +650,7 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
     g.a_packed = 0;
     g.lda = d;
     g.arow = (const int32_t*)((char*)dd + offsetof(SegDesc, head_xrow));
-    if (dt == EE_BF16 && !gemm_rows_fit_lds(dt, n_head, d, 3 * d)) {  // many rows: packed operands
+    if (dt == EE_BF16 && !route::rows_staged(n_head, d, 3 * d)) {  // many rows: packed operands
         char* hp = m->ws + m->wsl.head_pk;
         HIPCHK(launch_pack_rows(g.A, g.a_lo, d, g.arow, n_head, d, hp, (size_t)64 * d, st));
         g.A = hp;
@@ -1479,6 +1479,35 @@ int ee_debug_plan(int n_segments, int32_t* filled, int position, int max_pending
         if (position >= 0) plan::commit(filled, reached, position);
         else plan::flushed(filled, n_segments);
     }
+    return EE_OK;
+}
+
+int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route) {
+    if (!cfg || !route) return EE_ERR_ARG;
+    EECHK(ee_model_bytes(cfg, max_rows, max_seqs, nullptr, nullptr));
+    if (cfg->dtype != EE_BF16) return EE_ERR_CONFIG;
+    const WorkspaceLayout w = workspace_layout(*cfg, max_rows, max_seqs);
+    const int d = cfg->d_model, F = cfg->d_ff;
+    const bool head = kernel == EE_K_HEAD;
+    int N, K = d;
+    switch (kernel) {
+        case EE_K_QKV: N = 3 * d; break;
+        case EE_K_OPROJ: N = d; break;
+        case EE_K_SWIGLU: N = 2 * F; break;
+        case EE_K_DOWN: N = d, K = F; break;
+        case EE_K_HEAD: N = cfg->vocab; break;
+        default: return EE_ERR_ARG;
+    }
+    if (rows < 1 || rows > (prompt ? w.pf_rows : head ? max_seqs : max_rows) || (prompt && head)) return EE_ERR_ARG;
+    PartGeom g;
+    if (prompt)
+        *route = route::prompt_cut(kernel, N, K, rows, w.total - w.pf_part, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
+    else if (route::rows_staged(rows, K, kernel == EE_K_DOWN ? d : 3 * d))  // (the d wide GEMMs share their row operands)
+        *route = EE_ROUTE_STAGED;
+    else if (head)
+        *route = route::head_panels(rows, N, cfg->gemm_min_workgroups) ? EE_ROUTE_PANELS : EE_ROUTE_ROWS;
+    else
+        *route = route::step_cut(N, K, rows, cfg->gemm_min_workgroups, w.stage - w.partials, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
     return EE_OK;
 }
 

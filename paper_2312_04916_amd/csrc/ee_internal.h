@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "ee.h"
+#include "ee_route.h"
 
 namespace ee {
 
@@ -121,19 +122,10 @@ hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, c
                             bool out_packed, hipStream_t s);
 // defer_ns != NULL: when the KV range was split, leave the partials unmerged and report the number of splits
 // (the O projection then merges them, see GemmCommon::att_part); 0 is reported when `out` is complete.
-// true when GEMMs of T rows with K inputs and N outputs stage their rows in LDS; the rows are packed (a_packed) otherwise
-bool gemm_rows_fit_lds(int dtype, int T, int K, int N);
-
 hipError_t launch_kv_gather(int dtype, const KvGeom& kv, int layer, const int32_t* btab_seq, int pos0, int n,
                             float* k_out, float* v_out, hipStream_t s);
 
-// ---- a GEMM cut along its contraction (ee_prefill.hip): the k-tiles of all result tiles (256 columns x mtl row tiles) stand
-// behind each other and every workgroup takes `unit` of them.
-struct PartGeom {
-    int n_tiles, n_wgN, n_wgM, m_tiles, KT, unit, mtl;
-};
-// true when `bytes` of scratch hold the parts and the cut with its sum takes less than other_us
-bool cut_pays_over(int N, int K, int M, size_t bytes, float other_us, PartGeom* pg);
+// the k-tiles of a GEMM that is cut along its contraction (see PartGeom): partial sums into `part`
 hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N, int K, int M, void* part, const PartGeom& pg, hipStream_t s);
 hipError_t launch_head64(const void* W, const void* A_hi, const void* A_lo, int V, int d, int M, const float* ssq, int ssq_n,
                          const int32_t* arow, float inv_d, float eps, HeadPartial* partials, float* logits, hipStream_t s);

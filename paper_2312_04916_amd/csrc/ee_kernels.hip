@@ -465,7 +465,6 @@ __device__ __forceinline__ void rms_scales(const GemmArgs& a, float* rs) {
 // (hi and lo terms) into LDS, and the loop takes its A operands from there.  The vector-memory queue
 // then carries weight loads only (deeper ring, no registers spent on A look-ahead), and the lower
 // register count lets more workgroups share a CU.
-__host__ __device__ inline int a_lds_row_stride(int K) { return 2 * K + 32; }  // elements; +64 B staggers the banks of two rows
 
 // Workgroup barrier that orders LDS traffic only.  __syncthreads() also waits for every outstanding global load of
 // the wave (its release fence covers vector memory as a whole), which is not wanted where a ring of weight loads is
@@ -489,7 +488,7 @@ __device__ __forceinline__ void gemm_mainloop_bf16_lds(const GemmArgs& a, int ti
     u32x4 w[D];
     const int n = kt1 - kt0;
     auto fill = [&](int u, int t) { w[u] = __builtin_nontemporal_load(wp + (size_t)t * 64); };
-    const int rstride = a_lds_row_stride(K);
+    const int rstride = route::lds_row_stride(K);
     const int cpr = K / 8;  // 16-byte chunks per row and term
     constexpr int RC = KS == 16 ? 2 : 1;  // 16-byte chunks of a row that a thread of the single-row path holds
     constexpr int MAXS = ATT > 0 ? ATT : 1;
@@ -1577,61 +1576,14 @@ static GemmArgs make_args(const GemmCommon& c) {
     return a;
 }
 
-static int mt_of(int T) { return T <= 16 ? 1 : (T <= 32 ? 2 : 4); }
-// waves per workgroup: each should stream about 16 k-tiles (16 KB)
 static int ks_of(const GemmCommon& c) {
-    if (c.dtype != EE_BF16) return 4;
-    int kt = c.K / 32;
-    // (a residual GEMM of one workgroup or less per CU: more waves, shorter chains; 48 workgroups of 64 k-tiles 5.7 -> 5.2 us)
-    if (kt >= 32 && kt <= 64 && c.T <= 3 && c.N / 16 <= 256 && c.att_part == nullptr && !c.a_packed) return 8;
-    if (kt <= 64 || c.T > 32) return 4;   // (from 33 rows on: one wave per SIMD with all the registers)
-    if (kt <= 128 || c.T > 16) return 8;  // (16 waves of 1024 threads leave 128 registers each: one row tile only)
-    return 16;
-}
-
-// LDS bytes of the few-rows variant
-static size_t a_lds_bytes(int T, int K) { return (size_t)T * a_lds_row_stride(K) * 2; }
-
-// Which rows are staged.  Every workgroup stages all of them for its one column tile, so what a second and third row cost
-// grows with their bytes and with the rounds of workgroups: two or three rows of up to 36 KB (2 rows at K = 4096), or
-// of all the LDS where the launch is a single round (the down projection).  Us per step, staged / rows_kernel: 7B widths,
-// 4 layers, 2 sequences 456 / 489, 3 (48 KB) 503 / 497, 4 526 / 502; 1.3B widths, 8 layers, 3 sequences 451 / 482, 4 503 /
-// 488, 8 647 / 521; 30B widths, 4 layers, 2 sequences (53 KB) 988 / 962, 3 1061 / 966; 768 wide, 12 layers, 4 sequences
-// 474 / 405, 16 624 / 407.
-constexpr size_t A_LDS_MAX_BYTES = 72 * 1024;      // one row, workgroups of up to 8 waves
-constexpr size_t A_LDS_MAX_BYTES_16 = 140 * 1024;  // 16 waves have the CU to themselves whatever their LDS use
-constexpr size_t A_LDS_FEW_BYTES = 36 * 1024;
-
-bool gemm_rows_fit_lds(int dtype, int T, int K, int N) {
-    if (dtype != EE_BF16 || T > 3) return false;
-    GemmCommon c{};
-    c.dtype = dtype;
-    c.T = T;
-    c.K = K;
-    const size_t b = a_lds_bytes(T, K), all = ks_of(c) == 16 ? A_LDS_MAX_BYTES_16 : A_LDS_MAX_BYTES;
-    if (T == 1 || N / 16 <= 256) return b <= all;
-    return b <= A_LDS_FEW_BYTES;
-}
-
-// Column tiles per workgroup of a launch of many rows.  One workgroup is resident per CU, so the launch runs in rounds of
-// 256 workgroups (fewer where the test hook GemmCommon::min_wgs asks for it), and per k-tile a workgroup takes in its G
-// weight tiles and the rows' operands in two terms: rounds x (G + 2 mt) is what the launch costs (64 rows at the 7B
-// width: Q|K|V, 768 tiles, 3 tiles per workgroup; gate|up, 1376 tiles, 6).
-static int g_of(int mt, int n_tiles, int min_wgs) {
-    const int cus = min_wgs < 1 || min_wgs >= 512 ? 256 : (min_wgs / 2 > 0 ? min_wgs / 2 : 1);
-    int best = 1;
-    long cost = -1;
-    for (int g = 1; g <= 6; ++g) {
-        const long c = (long)((n_tiles + g - 1) / g + cus - 1) / cus * (g + 2 * mt);
-        if (cost < 0 || c < cost) cost = c, best = g;
-    }
-    return best;
+    return c.dtype != EE_BF16 ? 4 : route::step_waves(c.T, c.K, c.N, c.a_packed, c.att_part != nullptr);
 }
 
 // more dynamic LDS than the default limit has to be asked for once per kernel
 template <auto K>
 static hipError_t lds_limit_once() {
-    static hipError_t e = hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, A_LDS_MAX_BYTES_16);
+    static hipError_t e = hipFuncSetAttribute((const void*)K, hipFuncAttributeMaxDynamicSharedMemorySize, (int)route::LDS_MAX_BYTES_16);
     return e;
 }
 #define EE_LAUNCH_LDS(KERNEL_INST, ...)                                         \
@@ -1670,26 +1622,15 @@ static hipError_t launch_rows_g(const GemmArgs& a, const Epi& e, int g, hipStrea
 template <typename Epi>
 static hipError_t launch_rows(const GemmCommon& c, const GemmArgs& a, const Epi& e, hipStream_t s) {
     int ks = ks_of(c);
-    const int mt = mt_of(c.T), g = g_of(mt, a.n_tiles, c.min_wgs);
+    const int mt = route::row_tiles(c.T), g = route::tiles_per_wg(mt, a.n_tiles, c.min_wgs);
     if (ks == 16 && g >= 3) ks = 8;  // (1024 threads leave 128 registers per lane: two tiles at most)
     if (mt == 4) return launch_rows_g<4, 4>(a, e, g, s);
     if (mt == 2) return ks == 4 ? launch_rows_g<4, 2>(a, e, g, s) : launch_rows_g<8, 2>(a, e, g, s);
     return ks == 4 ? launch_rows_g<4, 1>(a, e, g, s) : ks == 8 ? launch_rows_g<8, 1>(a, e, g, s) : launch_rows_g<16, 1>(a, e, g, s);
 }
 
-// What launch_rows takes, in microseconds, and whether the cut along K beats it: per pass of 64 rows, G / 23 GB/s of weights
-// and 2 mt / 70 GB/s of rows per k-tile and round (fitted to all five projections at 64 rows of the 7B widths).  64 rows,
-// rows_kernel and cut with its sum: down 51 -> 30 us, Q|K|V 42 -> 33, gate|up 52 -> 42; O stays (23 and 21).  Up to 32 rows
-// rows_kernel takes in less and needs no second launch.
-static bool cut_pays(const GemmCommon& c, PartGeom* g) {
-    if (c.T <= 32 || c.part == nullptr || !c.a_packed || c.min_wgs > 0) return false;
-    float us = 0.f;
-    for (int r0 = 0; r0 < c.T; r0 += 64) {
-        const int mt = mt_of(c.T - r0 < 64 ? c.T - r0 : 64), G = g_of(mt, c.N / 16, 0);
-        const int rounds = ((c.N / 16 + G - 1) / G + 255) / 256;
-        us += rounds * (c.K / 32) * (G / 23.0f + 2 * mt / 70.0f) + 6.0f;
-    }
-    return cut_pays_over(c.N, c.K, c.T, c.part_bytes, us, g);
+static bool is_cut(const GemmCommon& c, PartGeom* g) {
+    return c.dtype == EE_BF16 && c.a_packed && c.part != nullptr && route::step_cut(c.N, c.K, c.T, c.min_wgs, c.part_bytes, g);
 }
 
 template <typename Epi>
@@ -1703,7 +1644,7 @@ static hipError_t launch_cut(const GemmCommon& c, const GemmArgs& a, const Epi& 
 // few rows, staged in LDS (the caller has made sure that they fit)
 #define EE_DISPATCH_LDS(KERNEL, ...)                                                                                                    \
     do {                                                                                                                                \
-        const size_t _sm = a_lds_bytes(c.T, c.K);                                                                                             \
+        const size_t _sm = route::lds_rows_bytes(c.T, c.K);                                                                                             \
         const int _ks = ks_of(c);                                                                                                       \
         dim3 grid(c.N / 16), block(_ks * 64);                                                                                           \
         if (_ks == 4) EE_LAUNCH_LDS((KERNEL<__bf16, 4, 1, true>), grid, block, _sm, s, __VA_ARGS__);                                 \
@@ -1713,7 +1654,7 @@ static hipError_t launch_cut(const GemmCommon& c, const GemmArgs& a, const Epi& 
 
 #define EE_DISPATCH_F32(KERNEL, ...)                                                             \
     do {                                                                                         \
-        const int _mt = mt_of(c.T);                                                              \
+        const int _mt = route::row_tiles(c.T);                                                              \
         dim3 block(256);                                                                         \
         dim3 grid(c.N / 16);                                                                     \
         if (_mt == 1) EE_LAUNCH((KERNEL<float, 4, 1, false>), grid, block, s, __VA_ARGS__);      \
@@ -1723,8 +1664,7 @@ static hipError_t launch_cut(const GemmCommon& c, const GemmArgs& a, const Epi& 
 
 int gemm_resid_tiles_per_wg() { return 1; }
 
-// Rows are processed in passes of at most 64 (the largest row tile count the kernels are built for).
-constexpr int PASS_ROWS = 64;
+using route::PASS_ROWS;  // rows are processed in passes of at most 64
 
 static GemmCommon pass_of(const GemmCommon& c, int r0) {
     GemmCommon p = c;
@@ -1744,7 +1684,7 @@ static const int32_t* desc_array(const SegDesc* d, size_t field_offset, int r0) 
 hipError_t launch_gemm_qkv(const GemmCommon& cc, void* q, size_t q_lo, const float* rope_cs, const KvGeom& kv, int layer,
                            hipStream_t s) {
     PartGeom pg;
-    if (cc.dtype == EE_BF16 && cut_pays(cc, &pg)) {
+    if (is_cut(cc, &pg)) {
         RowsQkv e{{(__bf16*)q, q_lo, cc.N / 3, (const float2*)rope_cs, (__bf16*)kv.pool + (size_t)layer * kv.layer_stride, kv.blk_stride, kv.H,
                    kv.hd, kv.BT, desc_array(cc.desc, offsetof(SegDesc, pos), 0), desc_array(cc.desc, offsetof(SegDesc, kvblk), 0), 0, 0}};
         return launch_cut(cc, make_args(cc), e, pg, s);
@@ -1786,7 +1726,7 @@ static void fill_rows(ResidArgs<ST>& e, const GemmCommon& c, int T_all) {
 hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh, size_t xs_lo, float* ssq_out,
                              const float* g_next, const float* g_head, int d, void* xg_pk, size_t xg_pk_lo, hipStream_t s) {
     PartGeom pg;
-    if (cc.dtype == EE_BF16 && cut_pays(cc, &pg)) {
+    if (is_cut(cc, &pg)) {
         RowsResid e{{x, (__bf16*)xg, (__bf16*)xgh, xs_lo, ssq_out, cc.ssq_stride, g_next, g_head, d,
                      desc_array(cc.desc, offsetof(SegDesc, xrow), 0), (__bf16*)xg_pk, xg_pk_lo, 0, {}}};
         return launch_cut(cc, make_args(cc), e, pg, s);
@@ -1797,7 +1737,7 @@ hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh
         const int32_t* xrow = desc_array(c.desc, offsetof(SegDesc, xrow), r0);
         if (c.dtype == EE_BF16 && c.att_part != nullptr) {
             // input still lies as attention split partials: only the few-rows variant can merge them
-            const size_t sm = a_lds_bytes(c.T, c.K);
+            const size_t sm = route::lds_rows_bytes(c.T, c.K);
             if (c.a_packed || cc.T > PASS_ROWS) return hipErrorInvalidValue;
             ResidArgs<__bf16> e{x, (__bf16*)xg, (__bf16*)xgh, xs_lo, ssq_out, c.ssq_stride, g_next, g_head, d, xrow, nullptr, 0, 0, {}};
             fill_rows(e, c, cc.T);
@@ -1832,7 +1772,7 @@ hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh
 
 hipError_t launch_gemm_swiglu(const GemmCommon& cc, void* act, size_t act_lo, int F, bool act_packed, hipStream_t s) {
     PartGeom pg;
-    if (cc.dtype == EE_BF16 && cut_pays(cc, &pg))
+    if (is_cut(cc, &pg))
         return launch_cut(cc, make_args(cc), RowsSwiglu{(__bf16*)act, act_lo, F, act_packed ? F / 32 : 0}, pg, s);
     for (int r0 = 0; r0 < cc.T; r0 += PASS_ROWS) {
         const GemmCommon c = pass_of(cc, r0);
@@ -1862,9 +1802,7 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t*
     GemmArgs a = make_args(c);
     HeadArgs e{partials, logits, c.N};
     int n_parts = c.N / 16;
-    if (c.dtype == EE_BF16 && c.a_packed && c.T > 32 && c.min_wgs <= 0 && c.ssq_stride == c.ssq_n && c.N >= 128 * 256) {
-        // (a vocabulary of at least half as many 256-column panels as there are CUs; 64 rows, 50304 words, 4096 wide: 128 ->
-        // 98 us)
+    if (c.dtype == EE_BF16 && c.a_packed && c.ssq_stride == c.ssq_n && route::head_panels(c.T, c.N, c.min_wgs)) {
         n_parts = (c.N + 255) / 256;
         const hipError_t err = launch_head64(c.W, c.A, (const char*)c.A + c.a_lo * 2, c.N, c.K, c.T, c.ssq, c.ssq_n, c.arow, c.inv_d, c.eps,
                                              partials, logits, s);

@@ -14,8 +14,6 @@
 // activation operand, of a K-cache row, or of a packed q row.
 #include "ee_internal.h"
 
-#include <algorithm>
-
 #include "ee_lanes.h"
 #include "ee_launch.h"
 #include "ee_part.h"
@@ -1253,72 +1251,18 @@ PfArgs pf_args(const PfGemm& g, int MTL) {
     return a;
 }
 
-// Rows per workgroup tile, 128 or 64.  A CU works through about ceil(workgroups / 256) tiles (whether one after
-// another or two side by side), each for a time proportional to its rows: take the cheaper, 128 on a tie
-// (half the activation traffic from L2).
-int pf_mtl(const PfGemm& g) {
-    const long n_wgN = (g.N + 255) / 256;
-    const long r8 = (n_wgN * ((g.M + 127) / 128) + 255) / 256 * 8;
-    const long r4 = (n_wgN * ((g.M + 63) / 64) + 255) / 256 * 4;
-    return r4 < r8 ? 4 : 8;
-}
-
 template <typename K>
 hipError_t pf_set_lds(K kernel, size_t bytes) {
     return hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
-constexpr int PF_CUS = 256, PF_PART_TILES = 256;
-
-
 template <int MTL>
-hipError_t pf_launch_part(const PfArgs& a, void* part, hipStream_t s) {
+hipError_t pf_launch_part(const PfArgs& a, int wgs, void* part, hipStream_t s) {
     constexpr size_t lds_b = pf_lds_bytes<MTL, 8, false>();
     static hipError_t once = pf_set_lds(pf_part_kernel<MTL>, lds_b);
     if (once != hipSuccess) return once;
-    const int wgs = (a.n_wgN * a.n_wgM * a.KT + a.unit - 1) / a.unit;
     EE_LAUNCH_SM(pf_part_kernel<MTL>, dim3((wgs + 7) / 8 * 8), dim3(512), lds_b, s, a, (f32x4*)part);
     return hipGetLastError();
-}
-
-int pf_part_mtl(int M) { return M <= 64 ? 4 : 8; }
-
-// Geometry of the cut of an N x K matrix over M rows: every workgroup an even share, but no fewer than eight k-tiles (a
-// part costs its writing and reading) and no more parts than fit `bytes`.  False: it cannot be cut so.
-bool pf_part_geom(int N, int K, int M, size_t bytes, PartGeom* g) {
-    g->mtl = pf_part_mtl(M);
-    g->KT = K / 32;
-    g->n_tiles = N / 16;
-    g->n_wgN = (g->n_tiles + PF_NTL - 1) / PF_NTL;
-    g->n_wgM = (M + g->mtl * 16 - 1) / (g->mtl * 16);
-    g->m_tiles = (M + 15) / 16;
-    const long tiles = (long)g->n_wgN * g->n_wgM;
-    if (tiles > PF_PART_TILES || g->n_tiles % 2) return false;
-    const long wgs = std::min<long>(PF_CUS, (long)(bytes / ((size_t)PF_NTL * g->mtl * 1024)) - tiles);
-    if (wgs < 1) return false;
-    const long u = (tiles * g->KT + wgs - 1) / wgs;
-    if (u > g->KT) return false;
-    g->unit = (int)std::min<long>(std::max<long>(u, 8), g->KT);
-    return true;
-}
-
-// What the cut and its sum take, in microseconds: what a CU takes in bounds it, at 33 GB/s, then come writing one or two
-// parts, reading all of them back, and a second launch.
-float pf_cut_us(const PartGeom& g) {
-    const int tiles = g.n_wgN * g.n_wgM, wgs = (tiles * g.KT + g.unit - 1) / g.unit;
-    const float part_kb = 16.0f * g.mtl;
-    return g.unit * (16 + 2 * g.mtl) / 33.0f + part_kb * (1.0f + (float)tiles / wgs) / 60.0f + (wgs + tiles) * part_kb / 5000.0f + 5.0f;
-}
-
-// Is it faster than a workgroup per result tile?  Such a launch takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at 47
-// GB/s with 64-row tiles and 33 with 128-row tiles.  Both fitted to the times of all four GEMMs at 768 to 6656 wide, 40 to
-// 1024 rows (per layer, 7B widths, 99 rows, direct and cut: Q|K|V 65 -> 46 us, O 60 -> 25, gate|up 67 -> 58, down 135 ->
-// 38; 64 rows: 60 -> 33, 60 -> 21, 66 -> 42, 130 -> 30; 256 rows: gate|up 123 -> 103, down 140 -> 60, Q|K|V stays direct).
-bool pf_cut_pays(const PfGemm& g, int mtl_direct, PartGeom* pg) {
-    if (!pf_part_geom(g.N, g.K, g.M, g.part_bytes, pg)) return false;
-    const long direct_tiles = (long)pg->n_wgN * ((g.M + mtl_direct * 16 - 1) / (mtl_direct * 16));
-    const long rounds = (direct_tiles + PF_CUS - 1) / PF_CUS;
-    return pf_cut_us(*pg) < rounds * pg->KT * (16 + 2 * mtl_direct) / (mtl_direct == 4 ? 47.0f : 33.0f) + 2.0f;
 }
 
 // The partial sums of g (see pf_part_kernel), cut as pg says.
@@ -1326,18 +1270,15 @@ hipError_t pf_part(const PfGemm& g, const PartGeom& pg, hipStream_t s) {
     PfArgs a = pf_args(g, pg.mtl);
     a.unit = pg.unit;
     a.ssq = nullptr;
-    return pg.mtl == 8 ? pf_launch_part<8>(a, g.part, s) : pf_launch_part<4>(a, g.part, s);
+    const int wgs = route::part_wgs(pg);
+    return pg.mtl == 8 ? pf_launch_part<8>(a, wgs, g.part, s) : pf_launch_part<4>(a, wgs, g.part, s);
 }
 
 }  // namespace
 
 size_t pf_part_bytes(int max_rows, int max_N) {
-    const int tiles = std::min(PF_PART_TILES, (max_N + 255) / 256 * ((max_rows + 63) / 64));
-    return (size_t)(PF_CUS + tiles + 8) * (PF_NTL * 8) * 1024;
-}
-
-bool cut_pays_over(int N, int K, int M, size_t bytes, float other_us, PartGeom* pg) {
-    return pf_part_geom(N, K, M, bytes, pg) && pf_cut_us(*pg) < other_us;
+    const int tiles = std::min(route::PART_TILES, (max_N + 255) / 256 * ((max_rows + 63) / 64));
+    return (size_t)(route::CUS + tiles + 8) * (PF_NTL * 8) * 1024;
 }
 
 hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N, int K, int M, void* part, const PartGeom& pg, hipStream_t s) {
@@ -1354,7 +1295,7 @@ hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N,
 
 #define PF_DISPATCH(KERNEL, WIDE, ...)                                                                        \
     do {                                                                                                  \
-        if (pf_mtl(g) == 8) {                                                                             \
+        if (route::prompt_row_tiles(g.N, g.M) == 8) {                                                                             \
             PfArgs a = pf_args(g, 8);                                                                     \
             constexpr size_t lds_b = pf_lds_bytes<8, 8, WIDE>();                                              \
             static hipError_t once = pf_set_lds(KERNEL<8, 8>, lds_b);                                     \
@@ -1376,7 +1317,7 @@ hipError_t launch_pf_qkv(const PfGemm& g, void* q_hi, void* q_lo, const float* r
     PfQkv e{(__bf16*)q_hi, (__bf16*)q_lo, d, kv.H, kv.hd, (const float2*)rope_cs, (__bf16*)kv.pool + (size_t)layer * kv.layer_stride,
             kv.blk_stride, kv.BT, bt, p0};
     PartGeom pg;
-    if (pf_cut_pays(g, pf_mtl(g), &pg)) {
+    if (route::prompt_cut(EE_K_QKV, g.N, g.K, g.M, g.part_bytes, &pg)) {
         const PfArgs a = pf_args(g, pg.mtl);
         const hipError_t err = pf_part(g, pg, s);
         if (err != hipSuccess) return err;
@@ -1389,11 +1330,8 @@ hipError_t launch_pf_qkv(const PfGemm& g, void* q_hi, void* q_lo, const float* r
 hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, void* xgh_hi, void* xgh_lo, const float* g_next,
                            const float* g_head, float* ssq_out, int ssq_n_out, hipStream_t s) {
     PfResid e{x, (__bf16*)xg_hi, (__bf16*)xg_lo, (__bf16*)xgh_hi, (__bf16*)xgh_lo, g_next, g_head, ssq_out, ssq_n_out, g.N};
-    // (With more than four row tiles of a few column panels the ranges of one panel's row tiles no longer run side by side,
-    // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 4 us for O and 9 us for down.)
-    const int cut_tiles = (g.N + 255) / 256 * ((g.M + 127) / 128);
     PartGeom pg;
-    if (cut_tiles <= 64 && pf_cut_pays(g, pf_mtl(g), &pg)) {
+    if (route::prompt_cut(EE_K_DOWN, g.N, g.K, g.M, g.part_bytes, &pg)) {
         const PfArgs a = pf_args(g, pg.mtl);
         const hipError_t err = pf_part(g, pg, s);
         if (err != hipSuccess) return err;
@@ -1403,7 +1341,7 @@ hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, 
     // Two workgroups per CU (four waves per SIMD) once the grid has more workgroups than CUs (30B widths at 2048
     // rows: O 359 -> 332 us, down 922 -> 840 us); a grid of one workgroup per CU keeps the deeper ring and the
     // second operand set.
-    const int mtl = pf_mtl(g);
+    const int mtl = route::prompt_row_tiles(g.N, g.M);
     const long n_wgs = (long)((g.N + 255) / 256) * ((g.M + mtl * 16 - 1) / (mtl * 16));
     const bool wide = n_wgs > 256;
     if (wide) {
@@ -1437,7 +1375,7 @@ hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, 
 
 hipError_t launch_pf_swiglu(const PfGemm& g, void* act_hi, void* act_lo, int F, hipStream_t s) {
     PartGeom pg;
-    if (pf_cut_pays(g, pf_mtl(g), &pg)) {
+    if (route::prompt_cut(EE_K_SWIGLU, g.N, g.K, g.M, g.part_bytes, &pg)) {
         const PfArgs a = pf_args(g, pg.mtl);
         const hipError_t err = pf_part(g, pg, s);
         if (err != hipSuccess) return err;

@@ -1,0 +1,157 @@
+// Which kernel a GEMM of the bf16 model runs in, by its sizes and rows: host arithmetic only, free of any device state, so
+// that a machine without a GPU can check what a shape takes (ee_debug_gemm_route).
+#pragma once
+#include <algorithm>
+#include <cstddef>
+
+#include "ee.h"
+
+namespace ee {
+
+// A GEMM cut along its contraction (pf_part_kernel in ee_prefill.hip): the k-tiles of all result tiles (256 columns x mtl
+// row tiles) stand behind each other and every workgroup takes `unit` of them.
+struct PartGeom {
+    int n_tiles, n_wgN, n_wgM, m_tiles, KT, unit, mtl;
+};
+
+namespace route {
+
+constexpr int CUS = 256;
+constexpr int PANEL = 16;  // 16-column weight tiles per result tile of the prompt phase's GEMMs and of the cut (256 columns)
+
+// ---- decode steps, few rows: the rows are staged in LDS
+
+constexpr int lds_row_stride(int K) { return 2 * K + 32; }  // elements; +64 B staggers the banks of two rows
+inline size_t lds_rows_bytes(int T, int K) { return (size_t)T * lds_row_stride(K) * 2; }
+
+// Waves per workgroup of a decode GEMM (bf16); merges: its input is merged from attention partials while being staged;
+// packed: its rows come in operand order.
+inline int step_waves(int T, int K, int N, bool packed, bool merges) {
+    const int kt = K / 32;
+    // (a residual GEMM of one workgroup or less per CU: more waves, shorter chains; 48 workgroups of 64 k-tiles 5.7 -> 5.2 us)
+    if (kt >= 32 && kt <= 64 && T <= 3 && N / 16 <= CUS && !merges && !packed) return 8;
+    if (kt <= 64 || T > 32) return 4;   // (from 33 rows on: one wave per SIMD with all the registers)
+    if (kt <= 128 || T > 16) return 8;  // (16 waves of 1024 threads leave 128 registers each: one row tile only)
+    return 16;
+}
+
+// Which rows are staged.  Every workgroup stages all of them for its one column tile, so what a second and third row cost
+// grows with their bytes and with the rounds of workgroups: two or three rows of up to 36 KB (2 rows at K = 4096), or
+// of all the LDS where the launch is a single round (the down projection).  Us per step, staged / rows_kernel: 7B widths,
+// 4 layers, 2 sequences 456 / 489, 3 (48 KB) 503 / 497, 4 526 / 502; 1.3B widths, 8 layers, 3 sequences 451 / 482, 4 503 /
+// 488, 8 647 / 521; 30B widths, 4 layers, 2 sequences (53 KB) 988 / 962, 3 1061 / 966; 768 wide, 12 layers, 4 sequences
+// 474 / 405, 16 624 / 407.
+constexpr size_t LDS_MAX_BYTES = 72 * 1024;      // one row, workgroups of up to 8 waves
+constexpr size_t LDS_MAX_BYTES_16 = 140 * 1024;  // 16 waves have the CU to themselves whatever their LDS use
+constexpr size_t LDS_FEW_BYTES = 36 * 1024;
+
+inline bool rows_staged(int T, int K, int N) {
+    if (T > 3) return false;
+    const size_t b = lds_rows_bytes(T, K), all = step_waves(T, K, N, false, false) == 16 ? LDS_MAX_BYTES_16 : LDS_MAX_BYTES;
+    if (T == 1 || N / 16 <= CUS) return b <= all;
+    return b <= LDS_FEW_BYTES;
+}
+
+// ---- decode steps, many rows: rows_kernel, in passes of up to 64 rows
+
+constexpr int PASS_ROWS = 64;  // the largest row tile count rows_kernel is built for
+
+inline int row_tiles(int T) { return T <= 16 ? 1 : (T <= 32 ? 2 : 4); }
+
+// Column tiles per workgroup of a launch of many rows.  One workgroup is resident per CU, so the launch runs in rounds of
+// 256 workgroups (fewer where the test hook ee_config::gemm_min_workgroups asks for it), and per k-tile a workgroup takes
+// in its G weight tiles and the rows' operands in two terms: rounds x (G + 2 mt) is what the launch costs (64 rows at the
+// 7B width: Q|K|V, 768 tiles, 3 tiles per workgroup; gate|up, 1376 tiles, 6).
+inline int tiles_per_wg(int mt, int n_tiles, int min_wgs) {
+    const int cus = min_wgs < 1 || min_wgs >= 512 ? CUS : (min_wgs / 2 > 0 ? min_wgs / 2 : 1);
+    int best = 1;
+    long cost = -1;
+    for (int g = 1; g <= 6; ++g) {
+        const long c = (long)((n_tiles + g - 1) / g + cus - 1) / cus * (g + 2 * mt);
+        if (cost < 0 || c < cost) cost = c, best = g;
+    }
+    return best;
+}
+
+// ---- GEMMs cut along their contraction
+
+constexpr int PART_TILES = 256;
+
+// Geometry of the cut of an N x K matrix over M rows: every workgroup an even share, but no fewer than eight k-tiles (a
+// part costs its writing and reading) and no more parts than fit `bytes`.  False: it cannot be cut so.
+inline bool part_geom(int N, int K, int M, size_t bytes, PartGeom* g) {
+    g->mtl = M <= 64 ? 4 : 8;
+    g->KT = K / 32;
+    g->n_tiles = N / 16;
+    g->n_wgN = (g->n_tiles + PANEL - 1) / PANEL;
+    g->n_wgM = (M + g->mtl * 16 - 1) / (g->mtl * 16);
+    g->m_tiles = (M + 15) / 16;
+    const long tiles = (long)g->n_wgN * g->n_wgM;
+    if (tiles > PART_TILES || g->n_tiles % 2) return false;
+    const long wgs = std::min<long>(CUS, (long)(bytes / ((size_t)PANEL * g->mtl * 1024)) - tiles);
+    if (wgs < 1) return false;
+    const long u = (tiles * g->KT + wgs - 1) / wgs;
+    if (u > g->KT) return false;
+    g->unit = (int)std::min<long>(std::max<long>(u, 8), g->KT);
+    return true;
+}
+
+inline int part_wgs(const PartGeom& g) { return (g.n_wgN * g.n_wgM * g.KT + g.unit - 1) / g.unit; }
+
+// What the cut and its sum take, in microseconds: what a CU takes in bounds it, at 33 GB/s, then come writing one or two
+// parts, reading all of them back, and a second launch.
+inline float cut_us(const PartGeom& g) {
+    const int tiles = g.n_wgN * g.n_wgM, wgs = part_wgs(g);
+    const float part_kb = 16.0f * g.mtl;
+    return g.unit * (16 + 2 * g.mtl) / 33.0f + part_kb * (1.0f + (float)tiles / wgs) / 60.0f + (wgs + tiles) * part_kb / 5000.0f + 5.0f;
+}
+
+// Decode steps: what rows_kernel takes, in microseconds, and whether the cut beats it: per pass of 64 rows, G / 23 GB/s of
+// weights and 2 mt / 70 GB/s of rows per k-tile and round (fitted to all five projections at 64 rows of the 7B widths).  64
+// rows, rows_kernel and cut with its sum: down 51 -> 30 us, Q|K|V 42 -> 33, gate|up 52 -> 42; O stays (23 and 21).  Up to 32
+// rows rows_kernel takes in less and needs no second launch.
+inline bool step_cut(int N, int K, int T, int min_wgs, size_t bytes, PartGeom* g) {
+    if (T <= 32 || min_wgs > 0) return false;
+    float us = 0.f;
+    for (int r0 = 0; r0 < T; r0 += PASS_ROWS) {
+        const int mt = row_tiles(std::min(T - r0, PASS_ROWS)), G = tiles_per_wg(mt, N / 16, 0);
+        const int rounds = ((N / 16 + G - 1) / G + CUS - 1) / CUS;
+        us += rounds * (K / 32) * (G / 23.0f + 2 * mt / 70.0f) + 6.0f;
+    }
+    return part_geom(N, K, T, bytes, g) && cut_us(*g) < us;
+}
+
+// The head of 33 to 64 rows in panels of 256 columns (a vocabulary of at least half as many panels as there are CUs; 64 rows,
+// 50304 words, 4096 wide: 128 -> 98 us).
+inline bool head_panels(int T, int V, int min_wgs) { return T > 32 && T <= PASS_ROWS && min_wgs <= 0 && V >= 128 * 256; }
+
+// ---- prompt phase
+
+// Row tiles per workgroup of a GEMM that is not cut, 8 or 4.  A CU works through about ceil(workgroups / 256) tiles
+// (whether one after another or two side by side), each for a time proportional to its rows: take the cheaper, 128 rows on
+// a tie (half the activation traffic from L2).
+inline int prompt_row_tiles(int N, int M) {
+    const long n_wgN = (N + 255) / 256;
+    const long r8 = (n_wgN * ((M + 127) / 128) + CUS - 1) / CUS * 8;
+    const long r4 = (n_wgN * ((M + 63) / 64) + CUS - 1) / CUS * 4;
+    return r4 < r8 ? 4 : 8;
+}
+
+// Is the cut faster than a workgroup per result tile?  Such a launch takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at 47
+// GB/s with 64-row tiles and 33 with 128-row tiles.  Both fitted to the times of all four GEMMs at 768 to 6656 wide, 40 to
+// 1024 rows (per layer, 7B widths, 99 rows, direct and cut: Q|K|V 65 -> 46 us, O 60 -> 25, gate|up 67 -> 58, down 135 ->
+// 38; 64 rows: 60 -> 33, 60 -> 21, 66 -> 42, 130 -> 30; 256 rows: gate|up 123 -> 103, down 140 -> 60, Q|K|V stays direct).
+inline bool prompt_cut(int kernel, int N, int K, int M, size_t bytes, PartGeom* g) {
+    const bool resid = kernel == EE_K_OPROJ || kernel == EE_K_DOWN;
+    // (With more than four row tiles of a few column panels the ranges of one panel's row tiles no longer run side by side,
+    // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 4 us for O and 9 us for down.)
+    if (resid && (N + 255) / 256 * ((M + 127) / 128) > 64) return false;
+    if (!part_geom(N, K, M, bytes, g)) return false;
+    const int mtl = prompt_row_tiles(N, M);
+    const long direct_tiles = (long)g->n_wgN * ((M + mtl * 16 - 1) / (mtl * 16));
+    const long rounds = (direct_tiles + CUS - 1) / CUS;
+    return cut_us(*g) < rounds * g->KT * (16 + 2 * mtl) / (mtl == 4 ? 47.0f : 33.0f) + 2.0f;
+}
+
+}  // namespace route
+}  // namespace ee

@@ -1,0 +1,44 @@
+"""Which kernels a GEMM takes by its sizes (host arithmetic, no GPU): the rules' boundaries, and the routes that the GPU tests
+rely on."""
+import ctypes as C
+
+import paper_2312_04916_amd as ee
+from workload import CONFIGS
+
+from common import ee_config_of
+
+GEMMS = (ee.EE_K_QKV, ee.EE_K_OPROJ, ee.EE_K_SWIGLU, ee.EE_K_DOWN)
+
+
+def config(d, F, vocab=1056, **tuning):
+    hd = 128 if d % 128 == 0 else 64 if d % 64 == 0 else 32
+    return ee.make_config(2, d, d // hd, hd, F, vocab, (1,), "bf16", 4096, **tuning)
+
+
+def test_arguments_are_checked():
+    r, L = C.c_int32(), ee.lib()
+    bf, f32 = config(1024, 2816), ee_config_of(CONFIGS["C1"].shape, 256)
+    call = lambda cfg, *a: L.ee_debug_gemm_route(C.byref(cfg), *a, C.byref(r))  # noqa: E731
+    assert call(bf, 64, 4, ee.EE_K_QKV, 64, 0) == 0
+    assert call(f32, 64, 4, ee.EE_K_QKV, 64, 0) == -1
+    assert call(bf, 64, 4, ee.EE_K_ATTN, 64, 0) == -7
+    assert call(bf, 64, 4, ee.EE_K_QKV, 65, 0) == -7   # more rows than max_rows
+    assert call(bf, 64, 4, ee.EE_K_HEAD, 5, 0) == -7   # more sequences than max_seqs
+    assert call(bf, 64, 4, ee.EE_K_HEAD, 4, 1) == -7   # heads of the prompt phase have one route
+    assert call(bf, 64, 4, ee.EE_K_QKV, 2048, 1) == 0 and call(bf, 64, 4, ee.EE_K_QKV, 2049, 1) == -7
+    assert L.ee_debug_gemm_route(None, 64, 4, ee.EE_K_QKV, 1, 0, C.byref(r)) == -7
+
+
+def test_few_rows_are_staged_in_lds():
+    """One row always; two or three of up to 36 KB, or of all the LDS where the launch is a single round of workgroups."""
+    cfg = config(4096, 11008)
+    for k in GEMMS:
+        assert ee.gemm_route(cfg, k, 1) == ee.EE_ROUTE_STAGED
+        assert ee.gemm_route(cfg, k, 2) == ee.EE_ROUTE_STAGED
+        assert ee.gemm_route(cfg, k, 3) == (ee.EE_ROUTE_STAGED if k == ee.EE_K_DOWN else ee.EE_ROUTE_ROWS)
+        assert ee.gemm_route(cfg, k, 4) == ee.EE_ROUTE_ROWS and ee.gemm_route(cfg, k, 32) == ee.EE_ROUTE_ROWS
+
+
+def test_head_panels_from_33_rows_and_32768_words_on():
+    for vocab, n, want in ((32768, 33, ee.EE_ROUTE_PANELS), (32768, 64, ee.EE_ROUTE_PANELS), (32768, 32, ee.EE_ROUTE_ROWS), (32736, 64, ee.EE_ROUTE_ROWS)):
+        assert ee.gemm_route(config(1024, 2816, vocab), ee.EE_K_HEAD, n) == want
