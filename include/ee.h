@@ -93,9 +93,9 @@ typedef struct {
     int32_t prefill_rows;        /* rows per pass of the prompt-phase GEMM path: 0 = 2048, n > 0 = min(n, 8192) rounded to
                                     128 (at least 128), n < 0 = path off (prompts then go through the decode kernels) */
     int32_t gemm_min_workgroups; /* a decode GEMM over many rows gives a workgroup several 16-column tiles so that a launch
-                                    takes few rounds of half this many workgroups: 0 = 512; tests lower it so that small
-                                    models reach those kernel variants (any value but 0 also keeps such GEMMs from
-                                    being cut along their contraction) */
+                                    takes few rounds of half this many workgroups: 0 = 512, more than 512 changes nothing;
+                                    tests lower it so that small models reach those kernel variants (values below 512
+                                    also keep such GEMMs from being cut along their contraction and heads out of panels) */
     int32_t scored_head_terms;   /* bf16 terms of the activations in the heads that ee_prefill_scored evaluates on
                                     every position: 0 or 1 = the leading term only (half the matrix-core work; the
                                     logits then carry the rounding of the head's input to bf16, about 1e-3 of their

@@ -54,6 +54,9 @@ inline bool rows_staged(int T, int K, int N) {
 
 // ---- decode steps, many rows: rows_kernel, in passes of up to 64 rows
 
+// ee_config::gemm_min_workgroups: 0 stands for 512, and from there on it changes nothing
+inline bool default_min_wgs(int min_wgs) { return min_wgs < 1 || min_wgs >= 512; }
+
 constexpr int PASS_ROWS = 64;  // the largest row tile count rows_kernel is built for
 
 inline int row_tiles(int T) { return T <= 16 ? 1 : (T <= 32 ? 2 : 4); }
@@ -63,7 +66,7 @@ inline int row_tiles(int T) { return T <= 16 ? 1 : (T <= 32 ? 2 : 4); }
 // in its G weight tiles and the rows' operands in two terms: rounds x (G + 2 mt) is what the launch costs (64 rows at the
 // 7B width: Q|K|V, 768 tiles, 3 tiles per workgroup; gate|up, 1376 tiles, 6).
 inline int tiles_per_wg(int mt, int n_tiles, int min_wgs) {
-    const int cus = min_wgs < 1 || min_wgs >= 512 ? CUS : (min_wgs / 2 > 0 ? min_wgs / 2 : 1);
+    const int cus = default_min_wgs(min_wgs) ? CUS : (min_wgs / 2 > 0 ? min_wgs / 2 : 1);
     int best = 1;
     long cost = -1;
     for (int g = 1; g <= 6; ++g) {
@@ -111,7 +114,7 @@ inline float cut_us(const PartGeom& g) {
 // rows, rows_kernel and cut with its sum: down 51 -> 30 us, Q|K|V 42 -> 33, gate|up 52 -> 42; O stays (23 and 21).  Up to 32
 // rows rows_kernel takes in less and needs no second launch.
 inline bool step_cut(int N, int K, int T, int min_wgs, size_t bytes, PartGeom* g) {
-    if (T <= 32 || min_wgs > 0) return false;
+    if (T <= 32 || !default_min_wgs(min_wgs)) return false;
     float us = 0.f;
     for (int r0 = 0; r0 < T; r0 += PASS_ROWS) {
         const int mt = row_tiles(std::min(T - r0, PASS_ROWS)), G = tiles_per_wg(mt, N / 16, 0);
@@ -123,7 +126,7 @@ inline bool step_cut(int N, int K, int T, int min_wgs, size_t bytes, PartGeom* g
 
 // The head of 33 to 64 rows in panels of 256 columns (a vocabulary of at least half as many panels as there are CUs; 64 rows,
 // 50304 words, 4096 wide: 128 -> 98 us).
-inline bool head_panels(int T, int V, int min_wgs) { return T > 32 && T <= PASS_ROWS && min_wgs <= 0 && V >= 128 * 256; }
+inline bool head_panels(int T, int V, int min_wgs) { return T > 32 && T <= PASS_ROWS && default_min_wgs(min_wgs) && V >= 128 * 256; }
 
 // ---- prompt phase
 

@@ -42,3 +42,10 @@ def test_few_rows_are_staged_in_lds():
 def test_head_panels_from_33_rows_and_32768_words_on():
     for vocab, n, want in ((32768, 33, ee.EE_ROUTE_PANELS), (32768, 64, ee.EE_ROUTE_PANELS), (32768, 32, ee.EE_ROUTE_ROWS), (32736, 64, ee.EE_ROUTE_ROWS)):
         assert ee.gemm_route(config(1024, 2816, vocab), ee.EE_K_HEAD, n) == want
+
+
+def test_the_documented_default_of_gemm_min_workgroups_equals_zero():
+    for value, cut in ((0, True), (512, True), (100000, True), (511, False), (1, False)):
+        cfg = config(4096, 11008, 32768, gemm_min_workgroups=value)
+        assert ee.gemm_route(cfg, ee.EE_K_DOWN, 64) == (ee.EE_ROUTE_CUT if cut else ee.EE_ROUTE_ROWS)
+        assert ee.gemm_route(cfg, ee.EE_K_HEAD, 64) == (ee.EE_ROUTE_PANELS if cut else ee.EE_ROUTE_ROWS)
