@@ -144,7 +144,9 @@ int ee_last_hip_error(void);
 
 /* Sizes of the two device buffers a model needs.  weight_bytes holds the packed weights and the
  * rotary table; workspace_bytes holds per-step activations for up to max_rows rows
- * (1 <= max_rows <= EE_MAX_ROWS) and max_seqs sequences per step (1 <= max_seqs <= EE_MAX_SEQS). */
+ * (1 <= max_rows <= EE_MAX_ROWS) and max_seqs sequences per step (1 <= max_seqs <= EE_MAX_SEQS).  The end of
+ * the workspace is scratch that short prompts run faster with (partial sums of GEMMs that are cut along their
+ * contraction, up to 66 MB): ee_model_create and ee_model_load accept a workspace that is smaller by any part of it. */
 int ee_model_bytes(const ee_config* cfg, int max_rows, int max_seqs, size_t* weight_bytes,
                    size_t* workspace_bytes);
 
@@ -286,7 +288,8 @@ int ee_kv_cache_free(ee_kv_cache* c);
  * always finds the K and V of every earlier token.  The caller's lists stay empty: each sequence passes exactly
  * one row (its current token) per step, ee_kv_cache_pending reports 0 and no step is ever forced.
  *   dev_workspace   a second step workspace on the model's device, 256-byte aligned; workspace_bytes as reported by
- *                   ee_model_bytes is always enough (EE_ERR_NOMEM if too small).  NULL switches the mode off again.
+ *                   ee_model_bytes is always enough (EE_ERR_NOMEM if too small), with prefill_rows = -1 in the config
+ *                   it is what the fills need.  NULL switches the mode off again.
  *   fill_stream     a HIP stream of the same priority as the one the steps are given, not the same stream.
  * Every token still passes every layer (on one stream or the other), so on one GPU this trades no work for the
  * early emission of tokens; ee_kv_cache_flush waits until the fill stream has caught up, and the read-backs and

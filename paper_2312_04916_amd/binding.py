@@ -276,10 +276,14 @@ class KvCache:
             _chk(lib().ee_kv_cache_set_pipeline(self.model.h, self.h, None, 0, None), "ee_kv_cache_set_pipeline")
             self._fill_ws = self._fill_stream = None
             return
-        self._fill_ws = torch.zeros(self.model.workspace_bytes, dtype=torch.uint8, device=self.model.device)
+        cfg = ee_config.from_buffer_copy(self.model.cfg)
+        cfg.prefill_rows = -1  # (the fills need the decode steps' part of a workspace only)
+        sb = C.c_size_t()
+        _chk(lib().ee_model_bytes(C.byref(cfg), self.model.max_rows, self.model.max_seqs, None, C.byref(sb)), "ee_model_bytes")
+        self._fill_ws = torch.zeros(sb.value, dtype=torch.uint8, device=self.model.device)
         self._fill_stream = torch.cuda.Stream(device=self.model.device)
         torch.cuda.synchronize()
-        _chk(lib().ee_kv_cache_set_pipeline(self.model.h, self.h, self._fill_ws.data_ptr(), self.model.workspace_bytes,
+        _chk(lib().ee_kv_cache_set_pipeline(self.model.h, self.h, self._fill_ws.data_ptr(), sb.value,
                                             C.c_void_p(self._fill_stream.cuda_stream)), "ee_kv_cache_set_pipeline")
 
     def filled(self, seq: int, layer: int) -> int:

@@ -171,7 +171,7 @@ WorkspaceLayout workspace_layout(const ee_config& c, int max_rows, int max_seqs)
         w.pf_tgt = take(Mp * 4);   // per row: the next token of the prompt (scoring its log-likelihood)
         w.pf_zt = take(Mp * 4);    // its logit
         w.pf_nll = take(Mp * 4);
-        w.pf_part = take(pf_part_bytes((int)Mp, (int)std::max(3 * d, 2 * F)));
+        w.pf_part = take(route::prompt_part_bytes((int)d, (int)F, (int)Mp));  // (last: see ee_model_create)
     }
     w.total = off;
     return w;
@@ -184,6 +184,7 @@ struct ee_model {
     int max_rows, max_seqs;
     char* wbase;
     char* ws;
+    size_t pf_part_bytes;  // what the caller's workspace holds of the scratch behind wsl.pf_part
     WeightLayout wl;
     WorkspaceLayout wsl;
     std::vector<uint8_t> have;  // per tensor: set?
@@ -996,7 +997,7 @@ int prefill_large(ee_model* m, ee_kv_cache* c, int seq, const int32_t* tokens, i
     const int32_t* bt = m->dev_btab();
     PfGemm g{};
     g.part = ws + w.pf_part;
-    g.part_bytes = w.total - w.pf_part;
+    g.part_bytes = m->pf_part_bytes;
     g.inv_d = 1.0f / (float)d;
     g.eps = cf.rms_eps;
     g.ssq_n = ssq_n;
@@ -1177,9 +1178,12 @@ int ee_model_create(const ee_config* cfg, void* dev_weights, size_t weight_bytes
                     size_t workspace_bytes, int max_rows, int max_seqs, void* stream, ee_model** out) {
     if (!cfg || !dev_weights || !dev_workspace || !out) return EE_ERR_ARG;
     if (((uintptr_t)dev_weights | (uintptr_t)dev_workspace) & 255) return EE_ERR_ARG;
-    size_t wb, sb;
-    EECHK(ee_model_bytes(cfg, max_rows, max_seqs, &wb, &sb));
-    if (weight_bytes < wb || workspace_bytes < sb) return EE_ERR_NOMEM;
+    size_t wb;
+    EECHK(ee_model_bytes(cfg, max_rows, max_seqs, &wb, nullptr));
+    // (without the scratch for partial sums the prompt phase takes its other kernels)
+    const WorkspaceLayout wsl = workspace_layout(*cfg, max_rows, max_seqs);
+    const size_t least = wsl.pf_rows ? wsl.pf_part : wsl.total;
+    if (weight_bytes < wb || workspace_bytes < least) return EE_ERR_NOMEM;
     ee_model* m = new (std::nothrow) ee_model();
     if (!m) return EE_ERR_NOMEM;
     m->cfg = *cfg;
@@ -1188,7 +1192,8 @@ int ee_model_create(const ee_config* cfg, void* dev_weights, size_t weight_bytes
     m->wbase = (char*)dev_weights;
     m->ws = (char*)dev_workspace;
     m->wl = weight_layout(*cfg);
-    m->wsl = workspace_layout(*cfg, max_rows, max_seqs);
+    m->wsl = wsl;
+    m->pf_part_bytes = wsl.pf_rows ? std::min(workspace_bytes, wsl.total) - wsl.pf_part : 0;
     m->have.assign(m->n_tensors(), 0);
     m->n_missing = m->n_tensors();
     for (int kind = 0; kind < EE_T_KINDS; ++kind)
@@ -1216,7 +1221,7 @@ int ee_model_create(const ee_config* cfg, void* dev_weights, size_t weight_bytes
         if ((e = hipEventCreateWithFlags(&m->spec_ev, hipEventDisableTiming)) != hipSuccess) break;  // (no step creates anything)
         if ((e = hipMemsetAsync(m->ws + m->wsl.counters, 0, 256 * 4, st)) != hipSuccess) break;
         if ((e = launch_fill_f32((float*)(m->wbase + m->wl.ones), 1.0f, (size_t)cfg->d_model, st)) != hipSuccess) break;
-        if (m->wsl.pf_rows && (e = hipMemsetAsync(m->ws + m->wsl.pf_begin, 0, m->wsl.total - m->wsl.pf_begin, st)) != hipSuccess) break;
+        if (m->wsl.pf_rows && (e = hipMemsetAsync(m->ws + m->wsl.pf_begin, 0, m->wsl.pf_part - m->wsl.pf_begin, st)) != hipSuccess) break;
         e = launch_rope_table((float*)(m->wbase + m->wl.rope), cfg->max_positions, cfg->head_dim, cfg->rope_base, st);
     } while (0);
     if (e != hipSuccess) {

@@ -144,7 +144,6 @@ struct PfGemm {
     void* part;       // scratch for partial sums where the contraction is cut over workgroups
     size_t part_bytes;
 };
-size_t pf_part_bytes(int max_rows, int max_N);
 hipError_t launch_pf_embed(const void* embed, const int32_t* dev_tokens, int M, int d, const float* g_next, float* x, void* xg_hi,
                            void* xg_lo, float* ssq, int ssq_n, hipStream_t s);
 hipError_t launch_pf_qkv(const PfGemm& g, void* q_hi, void* q_lo, const float* rope_cs, const KvGeom& kv, int layer, const int32_t* bt,

@@ -1276,11 +1276,6 @@ hipError_t pf_part(const PfGemm& g, const PartGeom& pg, hipStream_t s) {
 
 }  // namespace
 
-size_t pf_part_bytes(int max_rows, int max_N) {
-    const int tiles = std::min(route::PART_TILES, (max_N + 255) / 256 * ((max_rows + 63) / 64));
-    return (size_t)(route::CUS + tiles + 8) * (PF_NTL * 8) * 1024;
-}
-
 hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N, int K, int M, void* part, const PartGeom& pg, hipStream_t s) {
     PfGemm g{};
     g.W = W;

@@ -156,5 +156,19 @@ inline bool prompt_cut(int kernel, int N, int K, int M, size_t bytes, PartGeom* 
     return cut_us(*g) < rounds * g->KT * (16 + 2 * mtl) / (mtl == 4 ? 47.0f : 33.0f) + 2.0f;
 }
 
+// Scratch that the cuts of a prompt phase of up to `max_rows` rows per pass can use.  (What is cut, and how, changes with
+// the number of 64-row tiles.)
+inline size_t prompt_part_bytes(int d, int F, int max_rows) {
+    const int N[4] = {3 * d, d, 2 * F, d}, K[4] = {d, d, d, F}, kernel[4] = {EE_K_QKV, EE_K_OPROJ, EE_K_SWIGLU, EE_K_DOWN};
+    size_t need = 0;
+    for (int i = 0; i < 4; ++i)
+        for (int M = 1; M <= max_rows; M += 64) {
+            PartGeom g;
+            if (prompt_cut(kernel[i], N[i], K[i], M, (size_t)1 << 40, &g))
+                need = std::max(need, (size_t)(part_wgs(g) + g.n_wgN * g.n_wgM) * PANEL * g.mtl * 1024);
+        }
+    return need;
+}
+
 }  // namespace route
 }  // namespace ee

@@ -1,15 +1,17 @@
 """GPU parity of decode steps by the number of rows they carry, against the CPU oracle's cache-free forward: every row
 count at which the projections change kernel, row tile or pass (3 | 4 staged / packed rows, 16 | 17, 32 | 33, 64 | 66
 rows), on widths that leave ragged column groups, with one and with several column tiles per workgroup."""
+import ctypes as C
+
 import numpy as np
 import pytest
 import torch
 
 import paper_2312_04916_amd as ee
 from oracle.from_workload import build_model
-from workload import ModelShape, prompt_tokens
+from workload import ModelShape, model_tensor, model_tensor_list, prompt_tokens
 
-from common import TOL, kv_check, load_gpu_model, rel_err
+from common import TOL, ee_config_of, kv_check, load_gpu_model, rel_err
 from test_gpu_prefill import check_prefill
 
 pytestmark = pytest.mark.gpu
@@ -138,4 +140,44 @@ def test_head_whose_logits_are_all_minus_infinity():
             assert list(nt) == [0] * n
             seqs.update(list(range(n)), nt, ex)
         cache.close()
+    gm.close()
+
+
+@pytest.mark.parametrize("missing", ["none", "some", "all"])
+def test_workspace_without_scratch_for_partial_sums(missing):
+    """A workspace that lacks some or all of the scratch at its end (the size that the library asked for before it cut GEMMs
+    along K) is accepted, one byte less is not, and a prompt gives the same K and V."""
+    shape = ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5)
+    without = 18149376  # of this model with 64 rows and one sequence
+    cfg = ee_config_of(shape, 256)
+    full = C.c_size_t()
+    assert ee.lib().ee_model_bytes(C.byref(cfg), 64, 1, None, C.byref(full)) == 0 and full.value > without
+    n_bytes = {"none": full.value, "some": (without + full.value) // 2, "all": without}[missing]
+    print(f"case: workspace of {n_bytes} of {full.value} bytes", flush=True)
+    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=256)
+    # the same tensors in a model over a workspace of n_bytes, whose prompts are compared
+    weights, workspace = torch.empty_like(gm.weights), torch.empty(n_bytes, dtype=torch.uint8, device="cuda:0")
+    create = lambda n, h: ee.lib().ee_model_create(  # noqa: E731
+        C.byref(cfg), weights.data_ptr(), gm.weight_bytes, workspace.data_ptr(), n, 64, 1, None, C.byref(h))
+    if missing == "all":
+        assert create(without - 1, C.c_void_p()) == -2
+    h = C.c_void_p()
+    assert create(n_bytes, h) == 0
+    ee.lib().ee_model_free(gm.h)
+    gm.h, gm.weights, gm.workspace = h, weights, workspace
+    for kind, idx in model_tensor_list(shape):
+        gm.set_tensor(int(kind), idx, model_tensor(shape, kind, idx, 5, "cuda:0", 0.1).contiguous())
+    torch.cuda.synchronize()
+    om = build_model(shape, 5, gain_jitter=0.1)
+    cache = ee.KvCache(gm, 1, 256, 32, 4)
+    for n in (33, 100, 200):
+        cache.reset(0)
+        prompt = prompt_tokens(shape.vocab, n, 3).numpy().astype(np.int32)
+        ee.prefill(gm, cache, 0, prompt, 1.0)
+        hid, ko, vo = om.forward_sequence(prompt)
+        assert rel_err(cache.read_hidden(0), hid[shape.n_layers][n - 1]) <= TOL["bf16"]
+        for l in range(shape.n_layers):
+            k, v = cache.read(0, l, 0, n)
+            kv_check(k, ko[l], "bf16", "K", l), kv_check(v, vo[l], "bf16", "V", l)
+    cache.close()
     gm.close()

@@ -49,3 +49,18 @@ def test_the_documented_default_of_gemm_min_workgroups_equals_zero():
         cfg = config(4096, 11008, 32768, gemm_min_workgroups=value)
         assert ee.gemm_route(cfg, ee.EE_K_DOWN, 64) == (ee.EE_ROUTE_CUT if cut else ee.EE_ROUTE_ROWS)
         assert ee.gemm_route(cfg, ee.EE_K_HEAD, 64) == (ee.EE_ROUTE_PANELS if cut else ee.EE_ROUTE_ROWS)
+
+
+def test_scratch_of_the_prompt_phase_is_what_its_cuts_can_use():
+    """workspace_bytes against that of the same model without scratch (measured before there was any): nothing more for a
+    model whose GEMMs are never cut, and no more than 256 workgroups and 256 result tiles can fill for the widest."""
+    for d, F, vocab, max_pos, seqs, without in ((128, 352, 1056, 4096, 4, 11030528), (1024, 2080, 544, 256, 1, 18149376),
+                                                (2048, 5504, 50304, 2048, 1, 151994624), (4096, 11008, 50304, 2048, 1, 294174976),
+                                                (6656, 17920, 50304, 4096, 4, 472172544)):
+        cfg = ee.make_config(2, d, d // (128 if d > 128 else 32), 128 if d > 128 else 32, F, vocab, (1,), "bf16", max_pos)
+        sb = C.c_size_t()
+        assert ee.lib().ee_model_bytes(C.byref(cfg), 64, seqs, None, C.byref(sb)) == 0
+        scratch = sb.value - without
+        assert 0 <= scratch <= 512 * 128 * 1024 and (scratch == 0) == (d == 128)
+        if d == 1024:
+            assert scratch <= 16 << 20
