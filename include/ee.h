@@ -194,9 +194,12 @@ int ee_debug_plan(int n_segments, int32_t* filled, int position, int max_pending
  *   EE_ROUTE_STAGED  few rows, staged in LDS
  *   EE_ROUTE_ROWS    many rows in operand order (prompt phase: one workgroup per result tile)
  *   EE_ROUTE_CUT     cut along the contraction, the parts added up by a second kernel
- *   EE_ROUTE_PANELS  a head in panels of 256 columns */
+ *   EE_ROUTE_PANELS  a head in panels of 256 columns
+ * waves (may be NULL): of a workgroup where the rows are staged (the O projection: where its input is not merged from the
+ * parts of a split KV range), else 0. */
 enum { EE_ROUTE_STAGED = 0, EE_ROUTE_ROWS = 1, EE_ROUTE_CUT = 2, EE_ROUTE_PANELS = 3 };
-int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route);
+int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route,
+                        int32_t* waves);
 /* Measurement hook: the confidence every head reported in the latest ee_decode_step, conf[n_seqs][n_exits+1] (host;
  * row b = the b-th sequence of that call, column i = exit i, last column = final head); -1 where the head was not
  * evaluated for that sequence in that step (the token had left at a shallower exit, exits disabled or step forced).

@@ -74,7 +74,7 @@ def lib():
         L.ee_debug_set_logits.argtypes = [vp, vp, C.c_int]
         L.ee_debug_step_confidences.argtypes = [vp, C.c_int, fp]
         L.ee_debug_plan.argtypes = [C.c_int, i32p, C.c_int, C.c_int, C.c_int, C.c_int, i32p, i32p, i32p]
-        L.ee_debug_gemm_route.argtypes = [C.POINTER(ee_config), C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i32p]
+        L.ee_debug_gemm_route.argtypes = [C.POINTER(ee_config), C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i32p, i32p]
         L.ee_profile_begin.argtypes = [vp, C.c_int, C.c_int]
         L.ee_profile_end.argtypes = [vp, i32p, fp]
         L.ee_profile_every.argtypes = [vp, C.c_int]
@@ -337,11 +337,11 @@ def plan(filled: Sequence[int], position: int, max_pending: int, refeed: bool = 
     return bool(forced.value), [(lo[i], hi[i]) for i in range(n)], [f[i] for i in range(n)]
 
 
-def gemm_route(cfg: ee_config, kernel: int, rows: int, prompt: bool = False, max_rows: int = EE_MAX_ROWS, max_seqs: int = EE_MAX_SEQS) -> int:
-    """ee_debug_gemm_route (host only) -> EE_ROUTE_*."""
-    r = C.c_int32()
-    _chk(lib().ee_debug_gemm_route(C.byref(cfg), max_rows, max_seqs, kernel, rows, int(prompt), C.byref(r)), "ee_debug_gemm_route")
-    return r.value
+def gemm_route(cfg: ee_config, kernel: int, rows: int, prompt: bool = False, max_rows: int = EE_MAX_ROWS, max_seqs: int = EE_MAX_SEQS) -> Tuple[int, int]:
+    """ee_debug_gemm_route (host only) -> (EE_ROUTE_*, waves of a workgroup that stages its rows)."""
+    r, w = C.c_int32(), C.c_int32()
+    _chk(lib().ee_debug_gemm_route(C.byref(cfg), max_rows, max_seqs, kernel, rows, int(prompt), C.byref(r), C.byref(w)), "ee_debug_gemm_route")
+    return r.value, w.value
 
 
 def prefill(model: Model, cache: KvCache, seq: int, tokens: Sequence[int], threshold: float, stream=None):

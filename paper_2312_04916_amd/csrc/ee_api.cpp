@@ -1487,7 +1487,8 @@ int ee_debug_plan(int n_segments, int32_t* filled, int position, int max_pending
     return EE_OK;
 }
 
-int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route) {
+int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route,
+                        int32_t* waves) {
     if (!cfg || !route) return EE_ERR_ARG;
     EECHK(ee_model_bytes(cfg, max_rows, max_seqs, nullptr, nullptr));
     if (cfg->dtype != EE_BF16) return EE_ERR_CONFIG;
@@ -1513,6 +1514,7 @@ int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int ke
         *route = route::head_panels(rows, N, cfg->gemm_min_workgroups) ? EE_ROUTE_PANELS : EE_ROUTE_ROWS;
     else
         *route = route::step_cut(N, K, rows, cfg->gemm_min_workgroups, w.stage - w.partials, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
+    if (waves) *waves = *route == EE_ROUTE_STAGED ? route::step_waves(rows, K, N, false, false) : 0;
     return EE_OK;
 }
 

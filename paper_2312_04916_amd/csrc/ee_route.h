@@ -28,8 +28,12 @@ inline size_t lds_rows_bytes(int T, int K) { return (size_t)T * lds_row_stride(K
 // packed: its rows come in operand order.
 inline int step_waves(int T, int K, int N, bool packed, bool merges) {
     const int kt = K / 32;
-    // (a residual GEMM of one workgroup or less per CU: more waves, shorter chains; 48 workgroups of 64 k-tiles 5.7 -> 5.2 us)
-    if (kt >= 32 && kt <= 64 && T <= 3 && N / 16 <= CUS && !merges && !packed) return 8;
+    // One workgroup or less per CU: more waves, shorter chains, where the chains are long enough.  Us with 4 and 8 waves (event
+    // pairs, which add about 3 us; spread 0.5), 1, 2 and 3 rows: 64 k-tiles, 64 workgroups (down) 7.3 / 6.6, 9.1 / 8.2, 9.4 /
+    // 8.9; 128 (O, KV range unsplit) 8.5 / 8.2, 8.5 / 7.8, 9.2 / 8.8; 256 (gate|up) 8.7 / 8.6, 8.5 / 8.1, 9.1 / 8.6.  48
+    // k-tiles: 96 workgroups (down) 8.0 / 8.2, 7.6 / 7.8, 8.3 / 8.4.  32 to 40 k-tiles lose with one row: Q|K|V, 192
+    // workgroups 7.2 / 7.6, 8.1 / 8.2, 8.2 / 8.2, 240 7.6 / 8.0; gate|up, 128 7.1 / 7.4; O, 64 7.4 / 7.7, 8.3 / 8.6.
+    if (kt > 48 && kt <= 64 && T <= 3 && N / 16 <= CUS && !merges && !packed) return 8;
     if (kt <= 64 || T > 32) return 4;   // (from 33 rows on: one wave per SIMD with all the registers)
     if (kt <= 128 || T > 16) return 8;  // (16 waves of 1024 threads leave 128 registers each: one row tile only)
     return 16;
