@@ -1513,7 +1513,7 @@ int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int ke
     else if (head)
         *route = route::head_panels(rows, N, cfg->gemm_min_workgroups) ? EE_ROUTE_PANELS : EE_ROUTE_ROWS;
     else
-        *route = route::step_cut(N, K, rows, cfg->gemm_min_workgroups, w.stage - w.partials, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
+        *route = route::step_cut(kernel, N, K, rows, cfg->gemm_min_workgroups, w.stage - w.partials, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
     if (waves) *waves = *route == EE_ROUTE_STAGED ? route::step_waves(rows, K, N, false, false) : 0;
     return EE_OK;
 }

@@ -1629,8 +1629,8 @@ static hipError_t launch_rows(const GemmCommon& c, const GemmArgs& a, const Epi&
     return ks == 4 ? launch_rows_g<4, 1>(a, e, g, s) : ks == 8 ? launch_rows_g<8, 1>(a, e, g, s) : launch_rows_g<16, 1>(a, e, g, s);
 }
 
-static bool is_cut(const GemmCommon& c, PartGeom* g) {
-    return c.dtype == EE_BF16 && c.a_packed && c.part != nullptr && route::step_cut(c.N, c.K, c.T, c.min_wgs, c.part_bytes, g);
+static bool is_cut(const GemmCommon& c, int kernel, PartGeom* g) {
+    return c.dtype == EE_BF16 && c.a_packed && c.part != nullptr && route::step_cut(kernel, c.N, c.K, c.T, c.min_wgs, c.part_bytes, g);
 }
 
 template <typename Epi>
@@ -1684,7 +1684,7 @@ static const int32_t* desc_array(const SegDesc* d, size_t field_offset, int r0) 
 hipError_t launch_gemm_qkv(const GemmCommon& cc, void* q, size_t q_lo, const float* rope_cs, const KvGeom& kv, int layer,
                            hipStream_t s) {
     PartGeom pg;
-    if (is_cut(cc, &pg)) {
+    if (is_cut(cc, EE_K_QKV, &pg)) {
         RowsQkv e{{(__bf16*)q, q_lo, cc.N / 3, (const float2*)rope_cs, (__bf16*)kv.pool + (size_t)layer * kv.layer_stride, kv.blk_stride, kv.H,
                    kv.hd, kv.BT, desc_array(cc.desc, offsetof(SegDesc, pos), 0), desc_array(cc.desc, offsetof(SegDesc, kvblk), 0), 0, 0}};
         return launch_cut(cc, make_args(cc), e, pg, s);
@@ -1726,7 +1726,7 @@ static void fill_rows(ResidArgs<ST>& e, const GemmCommon& c, int T_all) {
 hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh, size_t xs_lo, float* ssq_out,
                              const float* g_next, const float* g_head, int d, void* xg_pk, size_t xg_pk_lo, hipStream_t s) {
     PartGeom pg;
-    if (is_cut(cc, &pg)) {
+    if (is_cut(cc, EE_K_DOWN, &pg)) {
         RowsResid e{{x, (__bf16*)xg, (__bf16*)xgh, xs_lo, ssq_out, cc.ssq_stride, g_next, g_head, d,
                      desc_array(cc.desc, offsetof(SegDesc, xrow), 0), (__bf16*)xg_pk, xg_pk_lo, 0, {}}};
         return launch_cut(cc, make_args(cc), e, pg, s);
@@ -1772,7 +1772,7 @@ hipError_t launch_gemm_resid(const GemmCommon& cc, float* x, void* xg, void* xgh
 
 hipError_t launch_gemm_swiglu(const GemmCommon& cc, void* act, size_t act_lo, int F, bool act_packed, hipStream_t s) {
     PartGeom pg;
-    if (is_cut(cc, &pg))
+    if (is_cut(cc, EE_K_SWIGLU, &pg))
         return launch_cut(cc, make_args(cc), RowsSwiglu{(__bf16*)act, act_lo, F, act_packed ? F / 32 : 0}, pg, s);
     for (int r0 = 0; r0 < cc.T; r0 += PASS_ROWS) {
         const GemmCommon c = pass_of(cc, r0);

@@ -85,7 +85,8 @@ inline int tiles_per_wg(int mt, int n_tiles, int min_wgs) {
 constexpr int PART_TILES = 256;
 
 // Geometry of the cut of an N x K matrix over M rows: every workgroup an even share, but no fewer than eight k-tiles (a
-// part costs its writing and reading) and no more parts than fit `bytes`.  False: it cannot be cut so.
+// part costs its writing and reading) and no more parts than fit `bytes`.  False: it cannot be cut so (a share of the whole
+// contraction is no cut).
 inline bool part_geom(int N, int K, int M, size_t bytes, PartGeom* g) {
     g->mtl = M <= 64 ? 4 : 8;
     g->KT = K / 32;
@@ -98,34 +99,41 @@ inline bool part_geom(int N, int K, int M, size_t bytes, PartGeom* g) {
     const long wgs = std::min<long>(CUS, (long)(bytes / ((size_t)PANEL * g->mtl * 1024)) - tiles);
     if (wgs < 1) return false;
     const long u = (tiles * g->KT + wgs - 1) / wgs;
-    if (u > g->KT) return false;
-    g->unit = (int)std::min<long>(std::max<long>(u, 8), g->KT);
-    return true;
+    g->unit = (int)std::max<long>(u, 8);
+    return g->unit < g->KT;
 }
 
 inline int part_wgs(const PartGeom& g) { return (g.n_wgN * g.n_wgM * g.KT + g.unit - 1) / g.unit; }
 
-// What the cut and its sum take, in microseconds: what a CU takes in bounds it, at 33 GB/s, then come writing one or two
-// parts, reading all of them back, and a second launch.
-inline float cut_us(const PartGeom& g) {
-    const int tiles = g.n_wgN * g.n_wgM, wgs = part_wgs(g);
-    const float part_kb = 16.0f * g.mtl;
-    return g.unit * (16 + 2 * g.mtl) / 33.0f + part_kb * (1.0f + (float)tiles / wgs) / 60.0f + (wgs + tiles) * part_kb / 5000.0f + 5.0f;
+// What the cut and its sum take, in microseconds, next to a launch without it: what a CU takes in at 54 GB/s (64-row tiles)
+// or 50 (128-row tiles) bounds the cut; the sum reads all parts back and writes M x N values, those of Q|K|V at 340 a
+// nanosecond (it writes V one 2-byte element at a time, as the cache keeps V transposed), others at 560.  Constants common to
+// both ways to launch are left out, so those of the two rules below are differences.  All fitted to the times of whole
+// prompts and steps with each of the four GEMMs cut and not, in all combinations (profiles/cut_rule.md).
+inline float cut_us(int kernel, const PartGeom& g, int M) {
+    const int parts = part_wgs(g) + g.n_wgN * g.n_wgM;
+    return g.unit * (16 + 2 * g.mtl) / (g.mtl == 4 ? 54.0f : 50.0f) + parts * 16 * g.mtl / 5300.0f +
+           (float)M * (g.n_tiles * 16) / (kernel == EE_K_QKV ? 340e3f : 560e3f);
 }
 
-// Decode steps: what rows_kernel takes, in microseconds, and whether the cut beats it: per pass of 64 rows, G / 23 GB/s of
-// weights and 2 mt / 70 GB/s of rows per k-tile and round (fitted to all five projections at 64 rows of the 7B widths).  64
-// rows, rows_kernel and cut with its sum: down 51 -> 30 us, Q|K|V 42 -> 33, gate|up 52 -> 42; O stays (23 and 21).  Up to 32
-// rows rows_kernel takes in less and needs no second launch.
-inline bool step_cut(int N, int K, int T, int min_wgs, size_t bytes, PartGeom* g) {
+// Decode steps: does the cut beat rows_kernel, which takes, per k-tile and round, G KB of weights at 50 GB/s and the rows at
+// 105, and for each further pass of up to 64 rows 6.5 us more (with RMS scales in front 10.4, 8.4 if it has up to 16 rows)?  Up
+// to 32 rows rows_kernel takes in less and needs no second launch.  Us that cutting one GEMM adds to a layer at 33 | 64 rows:
+// 4096 wide Q|K|V 0 | +2, O -3 | -3, gate|up +1 | +1, down -18 | -17; 2048 wide 0 | 0, 0 | 0, +3 | +3, -9 | -9; 6656 wide
+// +4 | +6, -7 | -6, -13 | -12, -33 | -30; 1024 wide all but down (0 | -1) lose.  From 66 rows on rows_kernel streams the
+// weights twice, and what wins at 1024 wide are Q|K|V (-1), gate|up (-1) and down (-7), from 2048 wide on all four.
+inline bool step_cut(int kernel, int N, int K, int T, int min_wgs, size_t bytes, PartGeom* g) {
     if (T <= 32 || !default_min_wgs(min_wgs)) return false;
-    float us = 0.f;
+    const bool resid = kernel == EE_K_OPROJ || kernel == EE_K_DOWN;
+    float us = kernel == EE_K_QKV ? -2.4f : resid ? -2.7f : -0.9f;
+    if (T > 64) us -= 3.5f;  // (128-row tiles: a longer start)
     for (int r0 = 0; r0 < T; r0 += PASS_ROWS) {
         const int mt = row_tiles(std::min(T - r0, PASS_ROWS)), G = tiles_per_wg(mt, N / 16, 0);
         const int rounds = ((N / 16 + G - 1) / G + CUS - 1) / CUS;
-        us += rounds * (K / 32) * (G / 23.0f + 2 * mt / 70.0f) + 6.0f;
+        us += rounds * (K / 32) * (G / 50.0f + 2 * mt / 105.0f);
+        if (r0) us += resid ? 6.5f : mt == 1 ? 8.4f : 10.4f;
     }
-    return part_geom(N, K, T, bytes, g) && cut_us(*g) < us;
+    return part_geom(N, K, T, bytes, g) && cut_us(kernel, *g, T) < us;
 }
 
 // The head of 33 to 64 rows in panels of 256 columns (a vocabulary of at least half as many panels as there are CUs; 64 rows,
@@ -144,20 +152,24 @@ inline int prompt_row_tiles(int N, int M) {
     return r4 < r8 ? 4 : 8;
 }
 
-// Is the cut faster than a workgroup per result tile?  Such a launch takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at 47
-// GB/s with 64-row tiles and 33 with 128-row tiles.  Both fitted to the times of all four GEMMs at 768 to 6656 wide, 40 to
-// 1024 rows (per layer, 7B widths, 99 rows, direct and cut: Q|K|V 65 -> 46 us, O 60 -> 25, gate|up 67 -> 58, down 135 ->
-// 38; 64 rows: 60 -> 33, 60 -> 21, 66 -> 42, 130 -> 30; 256 rows: gate|up 123 -> 103, down 140 -> 60, Q|K|V stays direct).
+// Prompt phase: is the cut faster than a workgroup per result tile, which takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at
+// 77 GB/s with 64-row tiles and 55 with 128-row tiles, and 1/70 us per 64-row tile or 15 us with 128-row tiles (0.3 us per
+// k-tile on short contractions)?  Us that cutting one GEMM adds to a layer: 4096 wide, 64 | 99 | 256 | 512 rows: Q|K|V -31 |
+// -19 | +6 | -7, O -40 | -30 | -26 | -15, gate|up -17 | -2 | -19 | +1, down -115 | -94 | -90 | -59; 2048 wide, 65 | 384 | 640
+// rows: -13 | +3 | +18, -14 | -10 | -4, -4 | -9 | +18, -44 | -41 | -28.
 inline bool prompt_cut(int kernel, int N, int K, int M, size_t bytes, PartGeom* g) {
     const bool resid = kernel == EE_K_OPROJ || kernel == EE_K_DOWN;
     // (With more than four row tiles of a few column panels the ranges of one panel's row tiles no longer run side by side,
-    // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 4 us for O and 9 us for down.)
+    // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 16 us for O and for down.)
     if (resid && (N + 255) / 256 * ((M + 127) / 128) > 64) return false;
-    if (!part_geom(N, K, M, bytes, g)) return false;
+    // (Short contractions: with 128-row tiles 16 and 20 k-tiles gain 1 or lose up to 6 us by it, with 64-row tiles 12 lose 0 to
+    // 3 and 16 to 22 gain 0 to 3.)
+    if (K < (M <= 64 ? 16 : 24) * 32 || !part_geom(N, K, M, bytes, g)) return false;
     const int mtl = prompt_row_tiles(N, M);
     const long direct_tiles = (long)g->n_wgN * ((M + mtl * 16 - 1) / (mtl * 16));
     const long rounds = (direct_tiles + CUS - 1) / CUS;
-    return cut_us(*g) < rounds * g->KT * (16 + 2 * mtl) / (mtl == 4 ? 47.0f : 33.0f) + 2.0f;
+    const float us = rounds * g->KT * (16 + 2 * mtl) / (mtl == 4 ? 77.0f : 55.0f) + (mtl == 4 ? direct_tiles / 70.0f : std::min(15.0f, 0.3f * g->KT));
+    return cut_us(kernel, *g, M) < us + (kernel == EE_K_QKV ? 2.0f : resid ? 1.0f : -1.0f);
 }
 
 // Scratch that the cuts of a prompt phase of up to `max_rows` rows per pass can use.  (What is cut, and how, changes with

@@ -2,6 +2,8 @@
 rely on."""
 import ctypes as C
 
+import pytest
+
 import paper_2312_04916_amd as ee
 from workload import CONFIGS
 
@@ -80,3 +82,39 @@ def test_eight_waves_on_short_contractions_only_where_they_were_measured_to_win(
     assert waves(wide, ee.EE_K_OPROJ) == waves(wide, ee.EE_K_SWIGLU) == 8 and waves(wide, ee.EE_K_QKV) == 4  # 128, 256 | 384 workgroups
     assert waves(config(2048, 2080), ee.EE_K_SWIGLU) == 4
     assert waves(config(4096, 11008), ee.EE_K_QKV) == 8 and waves(config(4096, 11008), ee.EE_K_DOWN) == 16
+
+
+# What cutting one projection (Q|K|V, O, gate|up, down) was measured to add to a layer, in us, where it is 2 us or more either way
+# (profiles/cut_rule.md); 0: less than that, either route will do.
+MEASURED_STEPS = {
+    (1024, 2816): {33: (2.5, 3, 0, 0), 64: (2.5, 3, 0, 0), 96: (-4, 0, -3, -9), 128: (-7, 0, -6, -14)},
+    (2048, 5504): {33: (0, 0, 3, -9), 64: (0, 0, 3, -9), 66: (-6, -5, -4, -19), 96: (-10, -6, -7, -23)},
+    (3072, 8192): {33: (0, 0, 0, -15), 66: (-9, -9, -13, -29)},
+    (4096, 11008): {33: (0, -3, 0, -18), 48: (0, -4, 0, -19), 64: (2, -3, 0, -17), 66: (-10, -12, -21, -39), 256: (-57, -44, -89, -140)},
+    (5120, 13824): {33: (0, -7, -13, -29), 64: (0, -6, -12, -27)},
+    (6656, 17920): {33: (4, -7, -13, -33), 64: (6, -6, -12, -30), 192: (-39, -53, 0, -151)},
+}
+MEASURED_PROMPTS = {
+    (384, 1024): {65: (3, 3, 6, -5), 300: (3, 4, 6, -5)},
+    (768, 2048): {33: (-4, -4, -2, -14), 128: (-3, -2, 0, -13), 640: (0, -3, 6, -11), 2048: (3, 0, 0, -5)},
+    (1024, 2816): {33: (-7, -6, -4, -21), 300: (0, -5, 8, -17), 777: (5, -4, 4, -12), 1300: (8, 0, 9, -10)},
+    (1536, 4096): {65: (-10, -10, -5, -33), 384: (0, -10, 8, -29)},
+    (2048, 5504): {65: (-13, -14, -4, -44), 129: (-6, -12, 2, -40), 256: (-3, -14, 8, -44), 384: (3, -10, -9, -41), 512: (12, -7, 0, -34),
+                   640: (18, -4, 18, -28), 777: (-4, 0, 0, -20), 1024: (8, -2.5, 0, -24)},
+    (4096, 11008): {64: (-31, -40, -17, -115), 99: (-19, -30, -2, -94), 200: (5, -22, -22, -78), 256: (6, -26, -19, -90), 300: (22, -15, 0, -52),
+                    384: (-26, -14, 0, -45), 512: (-7, -15, 0, -58)},
+    (5120, 13824): {33: (-31, -46, -13, -128), 129: (0, -27, -15, -72), 256: (26, -24, 32, -70)},
+    (6656, 17920): {33: (-34, -55, -7, -163), 128: (-19, -50, -50, -144), 129: (44, -24, 0, -77), 256: (-9, -22, 0, -72)},
+}
+
+
+@pytest.mark.parametrize("prompt", [False, True])
+def test_projections_are_cut_where_that_was_measured_to_win(prompt):
+    wrong = []
+    for (d, F), points in (MEASURED_PROMPTS if prompt else MEASURED_STEPS).items():
+        for rows, effects in points.items():
+            for k, us in zip(GEMMS, effects):
+                cut = route(config(d, F), k, rows, prompt) == ee.EE_ROUTE_CUT
+                if us and cut != (us < 0):
+                    wrong.append((d, rows, ee.KERNEL_NAMES[k], us, cut))
+    assert not wrong, wrong
