@@ -867,9 +867,7 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
             // first touched by the O projection, which waits for the decision.
             if (!is_final && ss.size() == 1 && !pp.on) {
                 const SegDesc* nd = m->host_desc(s + 1);
-                // (For long deferred lists the work that a leaving token throws away outweighs the idle time: 31 deferred
-                // rows at the 7B width, 10.3 against 9.8 ms for a list filled and worked off.)
-                if (nd->T > 0 && (m->cfg.dtype != EE_BF16 || (nd->T <= 16 && nd->T * m->cfg.d_model <= 17408))) {
+                if (nd->T > 0 && route::front_ahead(m->cfg.dtype, nd->T, m->cfg.d_model)) {
                     EECHK(run_layers(m, c, s + 1, nd->T, nd->n_qt, m->seg_begin(s + 1), m->seg_end(s + 1), max_ctx, st, BLOCK_FRONT, &spec_ns));
                     spec_seg = s + 1;
                     c->spec_used = true;

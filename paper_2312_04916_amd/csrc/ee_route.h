@@ -56,6 +56,16 @@ inline bool rows_staged(int T, int K, int N) {
     return b <= LDS_FEW_BYTES;
 }
 
+// ---- decode steps of one sequence: is the front of the next segment (packing, Q|K|V, attention) enqueued behind an exit's head,
+// before the decision is known?  A token that stays saves the host's round trip, about 6 us at any width and row count (2 to 9
+// from 2048 wide on, 2 to 15 at 768).  For one that leaves the front ran for nothing, and what of it outlasts the host's own
+// time delays the next step, by about, at 1 | 2 | 4 | 8 | 16 rows (contexts 300 and 1200): 768 wide 0 | 7 | 0 | 1 | 8 us; 2048
+// wide 8 | 3 | 13 | 16 | 22; 4096 wide 6 | 12 | 21 | 24 | 30; 6656 wide 38 | 43 | 50 | 50 | 58; 32 rows 9, 22, 37, 57.  The line (16
+// rows, 4 rows at 4096 wide) is where a front thrown away costs about three times what a kept one saves, so that it pays while
+// no more than one token in four leaves at the exit.  (6656 wide, 1 and 2 rows: one in seven.)
+constexpr int FRONT_MAX_ROWS = 16, FRONT_MAX_ELEMS = 4 * 4096 + 1024;
+inline bool front_ahead(int dtype, int T, int d) { return dtype != EE_BF16 || (T <= FRONT_MAX_ROWS && T * d <= FRONT_MAX_ELEMS); }
+
 // ---- decode steps, many rows: rows_kernel, in passes of up to 64 rows
 
 // ee_config::gemm_min_workgroups: 0 stands for 512, and from there on it changes nothing
