@@ -106,7 +106,7 @@ WeightLayout weight_layout(const ee_config& c) {
 struct WorkspaceLayout {
     size_t upload, upload_bytes;  // [descs][btab][tokens], one host-to-device copy per step
     size_t descs, btab, tokens;
-    size_t q, attn, act, xg_pk, head_pk, partials, counters, attn_part, stage, total;
+    size_t q, attn, act, xg_pk, head_pk, partials, attn_part, stage, total;
     int max_blocks_per_seq;
     // prompt phase (bf16 model): buffers for pf_rows positions at a time, activations in the packed operand layout
     int pf_rows;  // 0: the prompt phase runs through the decode kernels in chunks
@@ -149,7 +149,6 @@ WorkspaceLayout workspace_layout(const ee_config& c, int max_rows, int max_seqs)
     w.xg_pk = take(terms * rows * d * es);
     w.head_pk = take(terms * 64 * d * es);
     w.partials = take((size_t)(c.vocab / 16) * EE_MAX_SEQS * sizeof(HeadPartial));
-    w.counters = take(256 * 4);
     w.attn_part = take(attention_part_floats(max_rows, c.n_heads, c.head_dim) * 4);
     w.stage = take(2 * (size_t)max_rows * d * 4);
     w.pf_rows = pf_rows_of(c);
@@ -480,7 +479,7 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
         Timed t(m, EE_K_ATTN, st);
         HIPCHK(launch_attention(dt, m->ws + m->wsl.q, m->ws + m->wsl.attn, m->lo_rows(d), dd, g.desc_host, T, n_qt, m->dev_btab(), c->geom,
                                 kv_layer, d,
-                                (float*)(m->ws + m->wsl.attn_part), (int32_t*)(m->ws + m->wsl.counters) + 64, max_ctx,
+                                (float*)(m->ws + m->wsl.attn_part), max_ctx,
                                 (dt == EE_BF16 && !pk_d) ? &att_ns : nullptr, pk_d, st));
     }
     if (phase == BLOCK_FRONT) {
@@ -662,7 +661,7 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
     float* logits = (m->dbg_logits && n_head <= m->dbg_rows) ? m->dbg_logits : nullptr;
     Timed t(m, EE_K_HEAD, st);
     m->head_tag = m->head_tag == 0x7fffffff ? 1 : m->head_tag + 1;
-    HIPCHK(launch_gemm_head(g, (HeadPartial*)(m->ws + m->wsl.partials), (int32_t*)(m->ws + m->wsl.counters), logits, mode,
+    HIPCHK(launch_gemm_head(g, (HeadPartial*)(m->ws + m->wsl.partials), logits, mode,
                             threshold, m->results_dev, m->head_tag, st));
     return EE_OK;
 }
@@ -1217,7 +1216,6 @@ int ee_model_create(const ee_config* cfg, void* dev_weights, size_t weight_bytes
         if ((e = hipHostGetDevicePointer((void**)&m->results_dev, m->results, 0)) != hipSuccess) break;
         if ((e = hipHostGetDevicePointer((void**)&m->pinned_dev, m->pinned, 0)) != hipSuccess) break;
         if ((e = hipEventCreateWithFlags(&m->spec_ev, hipEventDisableTiming)) != hipSuccess) break;  // (no step creates anything)
-        if ((e = hipMemsetAsync(m->ws + m->wsl.counters, 0, 256 * 4, st)) != hipSuccess) break;
         if ((e = launch_fill_f32((float*)(m->wbase + m->wl.ones), 1.0f, (size_t)cfg->d_model, st)) != hipSuccess) break;
         if (m->wsl.pf_rows && (e = hipMemsetAsync(m->ws + m->wsl.pf_begin, 0, m->wsl.pf_part - m->wsl.pf_begin, st)) != hipSuccess) break;
         e = launch_rope_table((float*)(m->wbase + m->wl.rope), cfg->max_positions, cfg->head_dim, cfg->rope_base, st);

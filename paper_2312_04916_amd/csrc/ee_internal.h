@@ -113,12 +113,12 @@ hipError_t launch_gemm_swiglu(const GemmCommon& c, void* act, size_t act_lo, int
 // rows of a row-major two-term array (through an index list, or dense when NULL) -> packed array
 hipError_t launch_pack_rows(const void* src, size_t src_lo, int ld, const int32_t* rows, int T, int K, void* dst, size_t dst_lo,
                             hipStream_t s);
-hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t* counter, float* logits, int mode,
+hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, float* logits, int mode,
                             float threshold, HeadResult* results, int tag, hipStream_t s);
 
 hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, const SegDesc* desc, const SegDesc* desc_host, int T, int n_qt,
                             const int32_t* btab,
-                            const KvGeom& kv, int layer, int d, float* part, int32_t* counters, int max_ctx, int* defer_ns,
+                            const KvGeom& kv, int layer, int d, float* part, int max_ctx, int* defer_ns,
                             bool out_packed, hipStream_t s);
 // defer_ns != NULL: when the KV range was split, leave the partials unmerged and report the number of splits
 // (the O projection then merges them, see GemmCommon::att_part); 0 is reported when `out` is complete.

@@ -1794,9 +1794,8 @@ hipError_t launch_gemm_swiglu(const GemmCommon& cc, void* act, size_t act_lo, in
     return hipSuccess;
 }
 
-hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, int32_t* counter, float* logits, int mode,
+hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, float* logits, int mode,
                             float threshold, HeadResult* results, int tag, hipStream_t s) {
-    (void)counter;
     if (c.T <= 0) return hipSuccess;
     if (c.T > 64) return hipErrorInvalidValue;
     GemmArgs a = make_args(c);
@@ -2219,9 +2218,8 @@ static hipError_t launch_attention_mfma(const void* q, void* out, size_t io_lo, 
 
 hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, const SegDesc* desc, const SegDesc* desc_host, int T, int n_qt,
                             const int32_t* btab,
-                            const KvGeom& kv, int layer, int d, float* part, int32_t* counters, int max_ctx, int* defer_ns,
+                            const KvGeom& kv, int layer, int d, float* part, int max_ctx, int* defer_ns,
                             bool out_packed, hipStream_t s) {
-    (void)counters;
     if (defer_ns) *defer_ns = 0;
     if (T <= 0) return hipSuccess;
     if (dtype == EE_BF16) {
