@@ -32,6 +32,7 @@ namespace {
 
 constexpr int PF_NTL = 16;  // 16-column weight tiles per workgroup (256 output features)
 constexpr int PF_WNF = 4;   // weight tiles per wave
+constexpr int PF_WAVES = 8; // per workgroup
 
 // element index of (row m, feature k) in a packed activation array with KT = K/32 tiles per row group
 __device__ __forceinline__ size_t pk_index(int m, int k, int KT) {
@@ -96,7 +97,7 @@ struct PfTile {
     int kt0, nkt;  // k-tiles to work through
 };
 
-template <int MTL, int NWAVE>
+template <int MTL>
 __device__ __forceinline__ bool pf_tile_of(const PfArgs& a, PfTile<MTL>& t) {
     // Workgroups are dealt round-robin to the 8 XCDs: give each XCD whole column panels, all row tiles of
     // a panel back to back, so that a weight panel is fetched from HBM once and then served by that XCD's L2.
@@ -109,8 +110,8 @@ __device__ __forceinline__ bool pf_tile_of(const PfArgs& a, PfTile<MTL>& t) {
     t.nt0 = t.n_wg * PF_NTL;
     t.mt0 = m_wg * MTL;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    t.wn = wave % (NWAVE / 2);
-    t.wm = wave / (NWAVE / 2);
+    t.wn = wave % (PF_WAVES / 2);
+    t.wm = wave / (PF_WAVES / 2);
     return true;
 }
 
@@ -120,15 +121,10 @@ __device__ __forceinline__ bool pf_tile_of(const PfArgs& a, PfTile<MTL>& t) {
 //    for the 64-row tile, which also has room for a second operand set in registers);
 //  - otherwise one workgroup per CU with four stages and two operand sets (the residual epilogue needs the registers).
 // (LO = false: the activations' hi term only, 24 KB instead of 32 KB per stage of the 128-row tile, so three stages fit twice)
-template <int MTL, int NWAVE, bool WIDE, bool LO = true>
+template <int MTL, bool WIDE, bool LO = true>
 constexpr int pf_stages() {
     return WIDE ? (MTL == 8 && LO ? 2 : 3) : 4;
 }
-template <int MTL, int NWAVE, bool WIDE>
-constexpr bool pf_pipe() {  // (the residual epilogue overrides this for its two-workgroups-per-CU variant)
-    return false;
-}
-
 // The operand reads and the wait counts are written by hand: the compiler would make every LDS read wait
 // for ALL outstanding global->LDS copies (it cannot tell which buffer a copy targets), which would
 // serialise the stages.  vmcnt counts this wave's copies in issue order: stage kt has landed once at most
@@ -140,15 +136,15 @@ __device__ __forceinline__ void pf_wait_vm() {
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-template <int MTL, int NWAVE, bool WIDE, bool PIPE = pf_pipe<MTL, NWAVE, WIDE>(), bool LO = true>
+template <int MTL, bool WIDE, bool PIPE = false, bool LO = true>
 __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& t, u32x4* lds, float* rs,
                                             f32x4 (&acc)[PF_WNF][MTL / 2]) {
     constexpr int WNF = PF_WNF, NTL = PF_NTL;
     constexpr int NF = NTL + (LO ? 2 : 1) * MTL;     // fragments (1 KB each) per stage
-    constexpr int FPW = NF / NWAVE;                  // copied per wave
-    constexpr int NST = pf_stages<MTL, NWAVE, WIDE, LO>();
+    constexpr int FPW = NF / PF_WAVES;               // copied per wave
+    constexpr int NST = pf_stages<MTL, WIDE, LO>();
     static_assert(LO || !PIPE, "the single-term loop has one operand set");
-    static_assert(NF % NWAVE == 0, "fragments must divide over the waves");
+    static_assert(NF % PF_WAVES == 0, "fragments must divide over the waves");
     static_assert((NST - 2) * FPW < 64, "vmcnt range");
     constexpr int STAGE = NF * 64;        // u32x4 per stage
     constexpr int MW = MTL / 2;
@@ -176,10 +172,10 @@ __device__ __forceinline__ void pf_mainloop(const PfArgs& a, const PfTile<MTL>& 
             __builtin_amdgcn_global_load_lds(EE_GLB_PTR(src[i] + (size_t)kt * 64), EE_LDS_PTR(lds + st * STAGE + (wave * FPW + i) * 64), 16,
                                              0, 0);
     };
-    // r[m] = 1/sqrt(mean(x^2)+eps) of this tile's rows, from the producers' partial sums (fixed order): NWAVE * 4 / MTL
+    // r[m] = 1/sqrt(mean(x^2)+eps) of this tile's rows, from the producers' partial sums (fixed order): 4 or 8
     // neighbouring threads per row
     {
-        constexpr int TPR = NWAVE * 4 / MTL;
+        constexpr int TPR = PF_WAVES * 4 / MTL;
         static_assert(TPR == 4 || TPR == 8, "threads per row");
         const int ml = threadIdx.x / TPR, m = t.mt0 * 16 + ml;
         float r = 1.f;
@@ -405,14 +401,14 @@ __device__ __forceinline__ void pf_mainloop_k16(const PfArgs& a, const PfTile<4>
     __syncthreads();  // before the epilogue reuses the buffers
 }
 
-template <int MTL, int NWAVE, bool WIDE, bool LO = true>
+template <int MTL, bool WIDE, bool LO = true>
 constexpr size_t pf_lds_bytes() {  // the stages + rs[] + up to seven reduction rows
-    return pf_stages<MTL, NWAVE, WIDE, LO>() * (size_t)(PF_NTL + (LO ? 2 : 1) * MTL) * 1024 + (size_t)MTL * 16 * 4 * 8;
+    return pf_stages<MTL, WIDE, LO>() * (size_t)(PF_NTL + (LO ? 2 : 1) * MTL) * 1024 + (size_t)MTL * 16 * 4 * 8;
 }
 
-template <int MTL, int NWAVE, bool WIDE, bool LO = true>
+template <int MTL, bool WIDE, bool LO = true>
 __device__ __forceinline__ float* pf_rs_ptr(u32x4* lds) {
-    return (float*)(lds + pf_stages<MTL, NWAVE, WIDE, LO>() * (PF_NTL + (LO ? 2 : 1) * MTL) * 64);
+    return (float*)(lds + pf_stages<MTL, WIDE, LO>() * (PF_NTL + (LO ? 2 : 1) * MTL) * 64);
 }
 
 // ---- epilogue 1: RMS scale, rotary embedding, q (packed), k and v into the paged cache
@@ -485,15 +481,15 @@ __device__ __forceinline__ void pf_qkv_store(const PfQkv& e, const PfQkvRow& w, 
     }
 }
 
-template <int MTL, int NWAVE>
-__global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_qkv_kernel(PfArgs a, PfQkv e) {
+template <int MTL>
+__global__ __launch_bounds__(PF_WAVES * 64, 4) void pf_qkv_kernel(PfArgs a, PfQkv e) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
-    if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
+    if (!pf_tile_of<MTL>(a, t)) return;
     constexpr int MW = MTL / 2;
-    float* rs = pf_rs_ptr<MTL, NWAVE, true>(pf_lds);
+    float* rs = pf_rs_ptr<MTL, true>(pf_lds);
     f32x4 acc[PF_WNF][MW];
-    pf_mainloop<MTL, NWAVE, true, MTL == 4>(a, t, pf_lds, rs, acc);
+    pf_mainloop<MTL, true, MTL == 4>(a, t, pf_lds, rs, acc);
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     // (row tiles outside, weight tiles inside: a row's look-ups are made once)
 #pragma unroll
@@ -520,7 +516,7 @@ struct PfResid {
 };
 
 // (waves with active == false hold no sums: they only keep the barriers company)
-template <int MTL, int NWAVE>
+template <int MTL>
 __device__ __forceinline__ void pf_resid_epilogue(const PfArgs& a, const PfResid& e, const PfTile<MTL>& t, const float* rs, float* red,
                                                   const f32x4 (&acc)[PF_WNF][MTL / 2], bool active = true) {
     constexpr int WNF = PF_WNF;
@@ -574,29 +570,29 @@ __device__ __forceinline__ void pf_resid_epilogue(const PfArgs& a, const PfResid
         if (m < a.M) {
             float sum = red[ml];
 #pragma unroll
-            for (int wv = 1; wv < NWAVE / 2; ++wv) sum += red[wv * (MTL * 16) + ml];
+            for (int wv = 1; wv < PF_WAVES / 2; ++wv) sum += red[wv * (MTL * 16) + ml];
             e.ssq_out[(size_t)m * e.ssq_n_out + t.n_wg] = sum;
         }
     }
 }
 
-template <int MTL, int NWAVE, bool WIDE = false>
-__global__ __launch_bounds__(NWAVE * 64, WIDE ? 4 : 2) void pf_resid_kernel(PfArgs a, PfResid e) {
+template <int MTL, bool WIDE = false>
+__global__ __launch_bounds__(PF_WAVES * 64, WIDE ? 4 : 2) void pf_resid_kernel(PfArgs a, PfResid e) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
-    if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
-    float* rs = pf_rs_ptr<MTL, NWAVE, WIDE>(pf_lds);
-    float* red = rs + MTL * 16;  // [NWAVE/2][MTL*16]
+    if (!pf_tile_of<MTL>(a, t)) return;
+    float* rs = pf_rs_ptr<MTL, WIDE>(pf_lds);
+    float* red = rs + MTL * 16;  // [PF_WAVES/2][MTL*16]
     f32x4 acc[PF_WNF][MTL / 2];
-    pf_mainloop<MTL, NWAVE, WIDE, (!WIDE && MTL == 4)>(a, t, pf_lds, rs, acc);  // (two operand sets need 152 registers here)
-    pf_resid_epilogue<MTL, NWAVE>(a, e, t, rs, red, acc);
+    pf_mainloop<MTL, WIDE, (!WIDE && MTL == 4)>(a, t, pf_lds, rs, acc);  // (two operand sets need 152 registers here)
+    pf_resid_epilogue<MTL>(a, e, t, rs, red, acc);
 }
 
 // 64-row tile, one workgroup of 16 waves per CU, the contraction split over two wave groups
 __global__ __launch_bounds__(1024, 4) void pf_resid_k16_kernel(PfArgs a, PfResid e) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<4> t;
-    if (!pf_tile_of<4, 8>(a, t)) return;
+    if (!pf_tile_of<4>(a, t)) return;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int kh = wave >> 3;
     t.wn = (wave & 7) % 4;
@@ -605,7 +601,7 @@ __global__ __launch_bounds__(1024, 4) void pf_resid_k16_kernel(PfArgs a, PfResid
     float* red = rs + 64;
     f32x4 acc[4][2];
     pf_mainloop_k16(a, t, kh, pf_lds, rs, acc);
-    pf_resid_epilogue<4, 8>(a, e, t, rs, red, acc, kh == 0);
+    pf_resid_epilogue<4>(a, e, t, rs, red, acc, kh == 0);
 }
 
 // SwiGLU of tile T of the packed gate|up matrix.  The gate features sit in the lower 32 lanes, their up partners in the
@@ -655,7 +651,7 @@ __global__ __launch_bounds__(512, 2) void pf_part_kernel(PfArgs a, f32x4* __rest
         t.kt0 = at - p * a.KT;
         t.nkt = (end - at < a.KT - t.kt0) ? end - at : a.KT - t.kt0;
         f32x4 acc[PF_WNF][MW];
-        pf_mainloop<MTL, 8, false, MTL == 4>(a, t, pf_lds, pf_rs_ptr<MTL, 8, false>(pf_lds), acc);  // (a.ssq is NULL)
+        pf_mainloop<MTL, false, MTL == 4>(a, t, pf_lds, pf_rs_ptr<MTL, false>(pf_lds), acc);  // (a.ssq is NULL)
         f32x4* o = part + ((size_t)(w + p) * (PF_NTL * MTL) + t.wn * (PF_WNF * MTL) + t.wm * MW) * 64 + lane;
 #pragma unroll
         for (int i = 0; i < PF_WNF; ++i)
@@ -757,18 +753,18 @@ __global__ __launch_bounds__(256) void pf_swiglu_sum_kernel(PfArgs a, __bf16* ac
 }
 
 // ---- epilogue 3: SwiGLU.  Tile j of the packed gate|up matrix: rows 0-7 gate features 8j.., rows 8-15 the up features
-template <int MTL, int NWAVE>
-__global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_swiglu_kernel(PfArgs a, __bf16* act_hi, __bf16* act_lo, int F) {
+template <int MTL>
+__global__ __launch_bounds__(PF_WAVES * 64, 4) void pf_swiglu_kernel(PfArgs a, __bf16* act_hi, __bf16* act_lo, int F) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
-    if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
+    if (!pf_tile_of<MTL>(a, t)) return;
     constexpr int MW = MTL / 2;
-    float* rs = pf_rs_ptr<MTL, NWAVE, true>(pf_lds);
+    float* rs = pf_rs_ptr<MTL, true>(pf_lds);
     f32x4 acc[PF_WNF][MW];
     // One operand set for both tiles: with two, the 64-row tile's epilogue put 24 registers of the main loop into scratch
     // at the 128 that two workgroups per CU leave (2422 us at 2048 rows of the 7B widths; 76 registers now.  Prompts, 7B
     // widths: 5000 tokens through 4 layers 30.6 -> 16.3 ms, 99 tokens through 8 layers 4.79 -> 3.03 ms).
-    pf_mainloop<MTL, NWAVE, true>(a, t, pf_lds, rs, acc);
+    pf_mainloop<MTL, true>(a, t, pf_lds, rs, acc);
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
 #pragma unroll
     for (int i = 0; i < PF_WNF; ++i) {
@@ -811,18 +807,18 @@ __device__ __forceinline__ void pf_merge(float& m, float& s, int& i, float m2, f
     }
 }
 
-template <int MTL, int NWAVE, bool LO>
-__global__ __launch_bounds__(NWAVE * 64, NWAVE == 8 ? 4 : 2) void pf_head_kernel(PfArgs a, PfHead e) {
+template <int MTL, bool LO>
+__global__ __launch_bounds__(PF_WAVES * 64, 4) void pf_head_kernel(PfArgs a, PfHead e) {
     extern __shared__ u32x4 pf_lds[];
     PfTile<MTL> t;
-    if (!pf_tile_of<MTL, NWAVE>(a, t)) return;
+    if (!pf_tile_of<MTL>(a, t)) return;
     constexpr int WNF = PF_WNF;
     constexpr int MW = MTL / 2;
-    float* rs = pf_rs_ptr<MTL, NWAVE, (NWAVE == 8), LO>(pf_lds);
-    constexpr int WN = NWAVE / 2;        // waves along the features
+    float* rs = pf_rs_ptr<MTL, true, LO>(pf_lds);
+    constexpr int WN = PF_WAVES / 2;     // waves along the features
     float* red = rs + MTL * 16;          // waves wn > 0 hand (max, sum) over here: [2 * (wn - 1) + {0, 1}][MTL * 16]
     f32x4 acc[WNF][MW];
-    pf_mainloop<MTL, NWAVE, (NWAVE == 8), false, LO>(a, t, pf_lds, rs, acc);
+    pf_mainloop<MTL, true, false, LO>(a, t, pf_lds, rs, acc);
     int* redi = (int*)pf_lds;            // ... and the index here (the stage buffers are free now): [wn - 1][MTL * 16]
     const int lane = threadIdx.x & 63, li = lane & 15, rg = lane >> 4;
     float mxs[MW], sms[MW];
@@ -1258,7 +1254,7 @@ hipError_t pf_set_lds(K kernel, size_t bytes) {
 
 template <int MTL>
 hipError_t pf_launch_part(const PfArgs& a, int wgs, void* part, hipStream_t s) {
-    constexpr size_t lds_b = pf_lds_bytes<MTL, 8, false>();
+    constexpr size_t lds_b = pf_lds_bytes<MTL, false>();
     static hipError_t once = pf_set_lds(pf_part_kernel<MTL>, lds_b);
     if (once != hipSuccess) return once;
     EE_LAUNCH_SM(pf_part_kernel<MTL>, dim3((wgs + 7) / 8 * 8), dim3(512), lds_b, s, a, (f32x4*)part);
@@ -1292,16 +1288,16 @@ hipError_t launch_part(const void* W, const void* A_hi, const void* A_lo, int N,
     do {                                                                                                  \
         if (route::prompt_row_tiles(g.N, g.M) == 8) {                                                                             \
             PfArgs a = pf_args(g, 8);                                                                     \
-            constexpr size_t lds_b = pf_lds_bytes<8, 8, WIDE>();                                              \
-            static hipError_t once = pf_set_lds(KERNEL<8, 8>, lds_b);                                     \
+            constexpr size_t lds_b = pf_lds_bytes<8, WIDE>();                                              \
+            static hipError_t once = pf_set_lds(KERNEL<8>, lds_b);                                     \
             if (once != hipSuccess) return once;                                                          \
-            EE_LAUNCH_SM((KERNEL<8, 8>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, __VA_ARGS__);       \
+            EE_LAUNCH_SM((KERNEL<8>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, __VA_ARGS__);       \
         } else {                                                                                          \
             PfArgs a = pf_args(g, 4);                                                                     \
-            constexpr size_t lds_b = pf_lds_bytes<4, 8, WIDE>();                                              \
-            static hipError_t once = pf_set_lds(KERNEL<4, 8>, lds_b);                                     \
+            constexpr size_t lds_b = pf_lds_bytes<4, WIDE>();                                              \
+            static hipError_t once = pf_set_lds(KERNEL<4>, lds_b);                                     \
             if (once != hipSuccess) return once;                                                          \
-            EE_LAUNCH_SM((KERNEL<4, 8>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, __VA_ARGS__);       \
+            EE_LAUNCH_SM((KERNEL<4>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, __VA_ARGS__);       \
         }                                                                                                 \
         return hipGetLastError();                                                                         \
     } while (0)
@@ -1342,16 +1338,16 @@ hipError_t launch_pf_resid(const PfGemm& g, float* x, void* xg_hi, void* xg_lo, 
     if (wide) {
         if (mtl == 8) {
             PfArgs a = pf_args(g, 8);
-            constexpr size_t lds_b = pf_lds_bytes<8, 8, true>();
-            static hipError_t once = pf_set_lds(pf_resid_kernel<8, 8, true>, lds_b);
+            constexpr size_t lds_b = pf_lds_bytes<8, true>();
+            static hipError_t once = pf_set_lds(pf_resid_kernel<8, true>, lds_b);
             if (once != hipSuccess) return once;
-            EE_LAUNCH_SM((pf_resid_kernel<8, 8, true>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, e);
+            EE_LAUNCH_SM((pf_resid_kernel<8, true>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, e);
         } else {
             PfArgs a = pf_args(g, 4);
-            constexpr size_t lds_b = pf_lds_bytes<4, 8, true>();
-            static hipError_t once = pf_set_lds(pf_resid_kernel<4, 8, true>, lds_b);
+            constexpr size_t lds_b = pf_lds_bytes<4, true>();
+            static hipError_t once = pf_set_lds(pf_resid_kernel<4, true>, lds_b);
             if (once != hipSuccess) return once;
-            EE_LAUNCH_SM((pf_resid_kernel<4, 8, true>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, e);
+            EE_LAUNCH_SM((pf_resid_kernel<4, true>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, e);
         }
         return hipGetLastError();
     }
@@ -1389,16 +1385,16 @@ hipError_t launch_pf_head(const PfGemm& g, HeadPartial* partials, int32_t* tok, 
     if (two_terms) {
         // (8 waves, two workgroups per CU, two stages: 633 us at 1024 rows; 4 waves with two workgroups per CU measured
         // 672 us, 8 waves with one workgroup per CU and four stages 750 us)
-        constexpr size_t lds_b = pf_lds_bytes<8, 8, true>();
-        static hipError_t once = pf_set_lds(pf_head_kernel<8, 8, true>, lds_b);
+        constexpr size_t lds_b = pf_lds_bytes<8, true>();
+        static hipError_t once = pf_set_lds(pf_head_kernel<8, true>, lds_b);
         if (once != hipSuccess) return once;
-        EE_LAUNCH_SM((pf_head_kernel<8, 8, true>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, e);
+        EE_LAUNCH_SM((pf_head_kernel<8, true>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, e);
     } else {
         // the leading term of the activations only: half the MFMAs, 24 KB per stage, three stages
-        constexpr size_t lds_b = pf_lds_bytes<8, 8, true, false>();
-        static hipError_t once = pf_set_lds(pf_head_kernel<8, 8, false>, lds_b);
+        constexpr size_t lds_b = pf_lds_bytes<8, true, false>();
+        static hipError_t once = pf_set_lds(pf_head_kernel<8, false>, lds_b);
         if (once != hipSuccess) return once;
-        EE_LAUNCH_SM((pf_head_kernel<8, 8, false>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, e);
+        EE_LAUNCH_SM((pf_head_kernel<8, false>), dim3(pf_grid<8>(a)), dim3(512), lds_b, s, a, e);
     }
     {
         hipError_t err = hipGetLastError();
@@ -1426,10 +1422,10 @@ hipError_t launch_head64(const void* W, const void* A_hi, const void* A_lo, int 
     PfArgs a = pf_args(g, 4);
     a.arow = arow;
     PfHead e{partials, V, nullptr, nullptr, logits};
-    constexpr size_t lds_b = pf_lds_bytes<4, 8, true>();
-    static hipError_t once = pf_set_lds(pf_head_kernel<4, 8, true>, lds_b);
+    constexpr size_t lds_b = pf_lds_bytes<4, true>();
+    static hipError_t once = pf_set_lds(pf_head_kernel<4, true>, lds_b);
     if (once != hipSuccess) return once;
-    EE_LAUNCH_SM((pf_head_kernel<4, 8, true>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, e);
+    EE_LAUNCH_SM((pf_head_kernel<4, true>), dim3(pf_grid<4>(a)), dim3(512), lds_b, s, a, e);
     return hipGetLastError();
 }
 
