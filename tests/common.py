@@ -32,6 +32,12 @@ def load_gpu_model(shape: ModelShape, seed: int = 0, gain_jitter: float = 0.0, m
     return m
 
 
+def cut_projections(cfg: ee.ee_config, rows: int, prompt: bool, max_rows: int, max_seqs: int) -> str:
+    """Which projections of a layer are cut along K for so many rows: letters of QOGD (Q|K|V, O, gate|up, down)."""
+    kernels = (ee.EE_K_QKV, ee.EE_K_OPROJ, ee.EE_K_SWIGLU, ee.EE_K_DOWN)
+    return "".join(c for c, k in zip("QOGD", kernels) if ee.gemm_route(cfg, k, rows, prompt, max_rows, max_seqs)[0] == ee.EE_ROUTE_CUT)
+
+
 # Relative error allowed on hidden states, logits and confidences (error over the largest reference magnitude).
 # The stated bounds of the path are 1e-4 (fp32 model) and 2e-2 (bf16 model); the bf16 path keeps every activation
 # as two bf16 terms and reaches a few 1e-4, so the tests hold it to 2e-3: losing an activation's second term

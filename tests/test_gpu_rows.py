@@ -11,7 +11,7 @@ import paper_2312_04916_amd as ee
 from oracle.from_workload import build_model
 from workload import ModelShape, model_tensor, model_tensor_list, prompt_tokens
 
-from common import TOL, ee_config_of, kv_check, load_gpu_model, rel_err
+from common import TOL, cut_projections, ee_config_of, kv_check, load_gpu_model, rel_err
 from test_gpu_prefill import check_prefill
 
 pytestmark = pytest.mark.gpu
@@ -19,20 +19,38 @@ pytestmark = pytest.mark.gpu
 SHAPES = {
     "d128": ModelShape(3, 128, 4, 32, 352, 1056, (1,), "bf16", 0.02, 0.3),
     "d192": ModelShape(2, 192, 3, 64, 224, 544, (1,), "bf16", 0.02, 0.3),
-    # wide enough that from 33 rows on projections are cut over K (65 k-tiles, 17 panels of which the last holds one pair)
+    # wide enough that projections are cut over K (CUT_STEPS): 65 k-tiles and 17 panels of which the last holds one pair, 89
+    # k-tiles, 9 panels of which the last holds four tiles
     "d1024": ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5),
+    "d1024w": ModelShape(2, 1024, 8, 128, 2848, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5),
+    "d3072": ModelShape(2, 3072, 24, 128, 1056, 544, (1,), "bf16", 0.02, 0.3 / 24 ** 0.5),
 }
-ROWS = {"d1024": (33, 64, 66, 128, 129)}
+# The projections of a step that are cut, by rows (the rule is host arithmetic: test_routes.py checks this table without a
+# GPU): with 64-row tiles each of the four in one shape or another, with 128-row tiles one and two of those per panel.
+STEP_LIMITS = dict(max_rows=160, max_seqs=4)
+CUT_STEPS = {
+    "d1024": {33: "", 64: "", 66: "GD", 128: "QOGD", 129: "QOGD"},
+    "d1024w": {33: "D", 64: "D"},
+    "d3072": {33: "QOG", 64: "OG"},
+}
+PROMPT_SHAPES = {
+    "d1024": SHAPES["d1024"],
+    "d1536": ModelShape(2, 1536, 12, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 12 ** 0.5),
+}
+CUT_PROMPTS = {  # (tokens, prefill_rows): the projections that are cut in each pass
+    "d1024": {(33, 0): ["QOGD"], (64, 0): ["QOGD"], (65, 0): ["QOGD"], (128, 0): ["QOGD"], (129, 0): ["QOD"], (200, 128): ["QOGD", "QOGD"]},
+    "d1536": {(129, 0): ["QOGD"], (200, 0): ["QOGD"], (256, 0): ["QOGD"]},
+}
 
 
-@pytest.mark.parametrize("name,min_wgs", [("d128", 0), ("d192", 0), ("d128", 16), ("d192", 6), ("d1024", 0)])
+@pytest.mark.parametrize("name,min_wgs", [("d128", 0), ("d192", 0), ("d128", 16), ("d192", 6), ("d1024", 0), ("d1024w", 0), ("d3072", 0)])
 def test_full_depth_step_over_a_given_number_of_rows(name, min_wgs):
     shape = SHAPES[name]
     om = build_model(shape, 5, gain_jitter=0.1)
-    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=128, max_rows=160, max_seqs=4, gemm_min_workgroups=min_wgs)
+    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=128, gemm_min_workgroups=min_wgs, **STEP_LIMITS)
     n_seq, cap = 4, 40
     fed = [prompt_tokens(shape.vocab, 80, 60 + s).numpy().astype(np.int32) for s in range(n_seq)]
-    for rows in ROWS.get(name, (1, 2, 3, 4, 5, 16, 17, 32, 33, 64, 66, 80, 81)):
+    for rows in CUT_STEPS.get(name, (1, 2, 3, 4, 5, 16, 17, 32, 33, 64, 66, 80, 81)):
         print(f"case: {name} tiles {min_wgs} rows {rows}", flush=True)
         ids = list(range(min(n_seq, rows)))
         lens = [7 + 5 * s for s in ids]
@@ -66,13 +84,12 @@ def test_full_depth_step_over_a_given_number_of_rows(name, min_wgs):
     gm.close()
 
 
-@pytest.mark.parametrize("n,rows_env", [(33, 0), (64, 0), (65, 0), (128, 0), (129, 0), (200, 128)])
-def test_short_prompts_whose_gemms_are_cut_over_the_contraction(n, rows_env):
-    """Prompts around the row tiles of the prompt phase (64, 128 rows, one and two tiles, a second pass), on a width at
-    which all four GEMMs are cut over K: 32 and 65 k-tiles, 17 column panels of which the last holds a single pair."""
-    print(f"case: cut prompt n={n} rows_env={rows_env}", flush=True)
-    shape = ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5)
-    check_prefill(shape, n, 4, rows_env=rows_env, scored=False)
+@pytest.mark.parametrize("name,n,rows_env", [(name, *case) for name, cases in CUT_PROMPTS.items() for case in cases])
+def test_short_prompts_whose_gemms_are_cut_over_the_contraction(name, n, rows_env):
+    """Prompts around the row tiles of the prompt phase (64, 128 rows, one and two tiles, a second pass), at widths at which
+    the four GEMMs are cut over K as CUT_PROMPTS says: at 1024 wide all of them up to one row tile, at 1536 with two."""
+    print(f"case: cut prompt {name} n={n} rows_env={rows_env}", flush=True)
+    check_prefill(PROMPT_SHAPES[name], n, 4, rows_env=rows_env, scored=False)
 
 
 def test_head_over_more_than_half_a_batch_of_rows():
@@ -180,4 +197,110 @@ def test_workspace_without_scratch_for_partial_sums(missing):
             k, v = cache.read(0, l, 0, n)
             kv_check(k, ko[l], "bf16", "K", l), kv_check(v, vo[l], "bf16", "V", l)
     cache.close()
+    gm.close()
+
+
+def many_sequences(gm, cache, shape, n, fed, n_first):
+    seqs = ee.Sequences(shape.n_layers)
+    for s in range(n):
+        ee.prefill(gm, cache, s, fed[s][:n_first], 1.0)
+        seqs.start(s, fed[s][n_first])
+    return seqs
+
+
+def test_cut_projections_in_the_static_workspace():
+    """Steps of 40 sequences whose down projection is cut along K: the scratch lies in the step's workspace, so the library's
+    own static one gives the same bits."""
+    shape, n = SHAPES["d1024w"], 40
+    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=64, max_rows=64, max_seqs=n)
+    assert cut_projections(gm.cfg, n, False, 64, n) == "D"
+    fed = [prompt_tokens(shape.vocab, 16, 200 + s).numpy().astype(np.int32) for s in range(n)]
+    got = []
+    for static in (False, True):
+        print(f"case: 40 sequences, static workspace {static}", flush=True)
+        cache = ee.KvCache(gm, n, n * 64, 32, 4)
+        seqs = many_sequences(gm, cache, shape, n, fed, 5)
+        out = []
+        for k in range(3):
+            ro, tk, pm = seqs.rows(list(range(n)))
+            nt, ex, cf = ee.decode_step(gm, cache, list(range(n)), ro, tk, pm, 1.0, static_workspace=static)
+            out += [nt.copy(), cf.copy()]
+            seqs.update(list(range(n)), [f[6 + k] for f in fed], ex)
+        for s in (0, 17, n - 1):
+            out.append(cache.read_hidden(s))
+            out += [t for l in range(shape.n_layers) for t in cache.read(s, l, 0, 8)]
+        got.append(out)
+        cache.close()
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
+    gm.close()
+
+
+def test_cut_projections_in_a_pipeline_fill():
+    """Pipeline mode, 40 sequences, every token leaves at the first exit: its pass through the layers above runs on the fill
+    stream in that stream's workspace, with the down projections cut along K.  Their K and V against the oracle's (the K
+    and V of layer 2 are formed behind layer 1's down projection)."""
+    shape = ModelShape(3, 1024, 8, 128, 2848, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5)
+    n, steps = 40, 4
+    om = build_model(shape, 5, gain_jitter=0.1)
+    gm = load_gpu_model(shape, 5, gain_jitter=0.1, max_positions=64, max_rows=64, max_seqs=n)
+    assert cut_projections(gm.cfg, n, False, 64, n) == "D"
+    fed = [prompt_tokens(shape.vocab, 16, 300 + s).numpy().astype(np.int32) for s in range(n)]
+    print("case: pipeline fills of 40 rows", flush=True)
+    cache = ee.KvCache(gm, n, n * 64, 32, 15)
+    cache.set_pipeline(True)
+    seqs = many_sequences(gm, cache, shape, n, fed, 5)
+    seqs.pipeline = True
+    for k in range(steps):
+        ro, tk, pm = seqs.rows(list(range(n)))
+        _, ex, _ = ee.decode_step(gm, cache, list(range(n)), ro, tk, pm, 0.0)
+        assert list(ex) == [1] * n
+        seqs.update(list(range(n)), [f[6 + k] for f in fed], ex)
+    cache.flush(list(range(n)))
+    for s in (0, 17, n - 1):
+        _, ko, vo = om.forward_sequence(fed[s][: 5 + steps])
+        for l in range(shape.n_layers):
+            assert cache.filled(s, l) == 5 + steps
+            k, v = cache.read(s, l, 0, 5 + steps)
+            kv_check(k, ko[l], "bf16", "K", l), kv_check(v, vo[l], "bf16", "V", l)
+    cache.close()
+    gm.close()
+
+
+@pytest.mark.parametrize("structure", [dict(exit_norm=False), dict(tie_embeddings=True), dict(exit_mlp=True), dict(exit_layer=True)],
+                         ids=lambda s: next(iter(s)))
+def test_head_in_panels_behind_every_exit_structure(structure):
+    """The heads of 33 sequences in 256-column panels, at an exit of each structure and at the end: logits, arg max and
+    confidence as each sequence gets them in a step of its own."""
+    shape = ModelShape(2, 128, 4, 32, 352, 128 * 256 + 96, (1,), "bf16", 0.02, 0.3, **structure)
+    n = 33
+    gm = load_gpu_model(shape, 6, gain_jitter=0.1, max_positions=64, max_rows=64, max_seqs=n)
+    assert ee.gemm_route(gm.cfg, ee.EE_K_HEAD, n, False, 64, n)[0] == ee.EE_ROUTE_PANELS
+    logits = gm.enable_logits(n)
+    ids = list(range(n))
+    fed = [prompt_tokens(shape.vocab, 16, 400 + s).numpy().astype(np.int32) for s in ids]
+    for tau, leaves_at in ((0.0, 1), (1.0, 2)):
+        print(f"case: panels behind {structure}, threshold {tau}", flush=True)
+        got = []
+        for groups in ([ids], [[s] for s in ids]):
+            cache = ee.KvCache(gm, n, n * 64, 32, 4)
+            seqs = many_sequences(gm, cache, shape, n, fed, 5)
+            z, tok, cf = [], [], []
+            for g in groups:
+                ro, tk, pm = seqs.rows(g)
+                nt, ex, c = ee.decode_step(gm, cache, g, ro, tk, pm, tau)
+                assert list(ex) == [leaves_at] * len(g)
+                torch.cuda.synchronize()
+                z.append(logits[: len(g)].cpu().numpy().copy())
+                tok.extend(int(t) for t in nt)
+                cf.extend(float(v) for v in c)
+            cache.close()
+            got.append((np.concatenate(z), tok, cf))
+        (za, ta, ca), (zb, tb, cb) = got
+        assert rel_err(za, zb) <= TOL["bf16"]
+        for s in ids:
+            top = np.sort(zb[s])[-2:]
+            assert ta[s] == int(za[s].argmax()) and (ta[s] == tb[s] or top[1] - top[0] < 1e-2), s
+            want = 1.0 / np.exp(za[s].astype(np.float64) - za[s].max()).sum()
+            assert abs(ca[s] - want) <= 1e-5 * want, (s, ca[s], want)  # 32-bit exponentials and sums over 32864 terms
     gm.close()

@@ -7,7 +7,8 @@ import pytest
 import paper_2312_04916_amd as ee
 from workload import CONFIGS
 
-from common import ee_config_of
+from common import cut_projections, ee_config_of
+from test_gpu_rows import CUT_PROMPTS, CUT_STEPS, PROMPT_SHAPES, SHAPES, STEP_LIMITS
 
 GEMMS = (ee.EE_K_QKV, ee.EE_K_OPROJ, ee.EE_K_SWIGLU, ee.EE_K_DOWN)
 
@@ -118,3 +119,15 @@ def test_projections_are_cut_where_that_was_measured_to_win(prompt):
                 if us and cut != (us < 0):
                     wrong.append((d, rows, ee.KERNEL_NAMES[k], us, cut))
     assert not wrong, wrong
+
+
+def test_the_gpu_tests_run_the_routes_they_claim():
+    for name, by_rows in CUT_STEPS.items():
+        cfg = ee_config_of(SHAPES[name], 128)
+        assert {rows: cut_projections(cfg, rows, False, **STEP_LIMITS) for rows in by_rows} == by_rows, name
+    for name, cases in CUT_PROMPTS.items():
+        for (n, rows_env), passes in cases.items():
+            cfg = ee_config_of(PROMPT_SHAPES[name], 512, prefill_rows=rows_env)
+            step = rows_env or 512
+            got = [cut_projections(cfg, min(step, n - p), True, 64, 1) for p in range(0, n, step)]
+            assert got == passes, (name, n, rows_env)
