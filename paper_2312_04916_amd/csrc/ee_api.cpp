@@ -650,7 +650,7 @@ int run_head(ee_model* m, ee_kv_cache* c, int di, int hi, int n_head, int mode, 
     g.a_packed = 0;
     g.lda = d;
     g.arow = (const int32_t*)((char*)dd + offsetof(SegDesc, head_xrow));
-    if (dt == EE_BF16 && !route::rows_staged(n_head, d, 3 * d)) {  // many rows: packed operands
+    if (dt == EE_BF16 && !route::head_staged(n_head, d)) {  // many rows: packed operands
         char* hp = m->ws + m->wsl.head_pk;
         HIPCHK(launch_pack_rows(g.A, g.a_lo, d, g.arow, n_head, d, hp, (size_t)64 * d, st));
         g.A = hp;
@@ -1504,7 +1504,7 @@ int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int ke
     PartGeom g;
     if (prompt)
         *route = route::prompt_cut(kernel, N, K, rows, w.total - w.pf_part, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
-    else if (route::rows_staged(rows, K, kernel == EE_K_DOWN ? d : 3 * d))  // (the d wide GEMMs share their row operands)
+    else if (head ? route::head_staged(rows, K) : route::rows_staged(rows, K, kernel == EE_K_DOWN ? d : 3 * d))  // (the d wide GEMMs share their row operands)
         *route = EE_ROUTE_STAGED;
     else if (head)
         *route = route::head_panels(rows, N, cfg->gemm_min_workgroups) ? EE_ROUTE_PANELS : EE_ROUTE_ROWS;

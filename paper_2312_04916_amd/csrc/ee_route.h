@@ -56,6 +56,16 @@ inline bool rows_staged(int T, int K, int N) {
     return b <= LDS_FEW_BYTES;
 }
 
+// The rows of a head.  They are packed for this one launch, which a projection's rows are not (their producer writes them
+// so), so up to four stay staged, from 24 k-tiles on and with workgroups of up to 8 waves (K up to 4096).  What staging adds
+// to a head and its packing, us, vocabulary 32000 | 50304: 4 rows, 768 wide -0.8 | -2.3; 1024 -3.0 | -5.8; 1536 -3.5 | -7.5;
+// 2048 -3.8 | -8.1; 2560 -0.2 | -4.3; 3072 +2.5 | -0.7; 4096 -2.5 | -4.3; 3 rows, 3072 wide -0.5 | -7.0; 4096 -1.8 | -4.7.
+// Beyond: 4 rows, 256 and 512 wide +3, +4; 6 rows, 2048 wide +5.6 | +8.1; 5120 wide (16 waves), 2 rows +5.5 | +3.3.
+inline bool head_staged(int T, int K) {
+    if (rows_staged(T, K, 3 * K)) return true;
+    return T <= 4 && K >= 24 * 32 && step_waves(T, K, 3 * K, false, false) <= 8 && lds_rows_bytes(T, K) <= LDS_MAX_BYTES;
+}
+
 // ---- decode steps of one sequence: is the front of the next segment (packing, Q|K|V, attention) enqueued behind an exit's head,
 // before the decision is known?  A token that stays saves the host's round trip, about 6 us at any width and row count (2 to 9
 // from 2048 wide on, 2 to 15 at 768).  For one that leaves the front ran for nothing, and what of it outlasts the host's own

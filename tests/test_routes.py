@@ -46,6 +46,15 @@ def test_few_rows_are_staged_in_lds():
         assert route(cfg, k, 4) == ee.EE_ROUTE_ROWS and route(cfg, k, 32) == ee.EE_ROUTE_ROWS
 
 
+def test_heads_of_up_to_four_rows_are_staged():
+    for d in (768, 2048, 4096):
+        cfg = config(d, 32 * (d // 12), 50304)
+        assert [route(cfg, ee.EE_K_HEAD, n) for n in (1, 2, 3, 4)] == [ee.EE_ROUTE_STAGED] * 4
+        assert route(cfg, ee.EE_K_HEAD, 5) == ee.EE_ROUTE_ROWS
+    assert [route(config(736, 1376), ee.EE_K_HEAD, n) for n in (3, 4)] == [ee.EE_ROUTE_STAGED, ee.EE_ROUTE_ROWS]
+    assert [route(config(5120, 13824), ee.EE_K_HEAD, n) for n in (1, 2)] == [ee.EE_ROUTE_STAGED, ee.EE_ROUTE_ROWS]
+
+
 def test_head_panels_from_33_rows_and_32768_words_on():
     for vocab, n, want in ((32768, 33, ee.EE_ROUTE_PANELS), (32768, 64, ee.EE_ROUTE_PANELS), (32768, 32, ee.EE_ROUTE_ROWS), (32736, 64, ee.EE_ROUTE_ROWS)):
         assert route(config(1024, 2816, vocab), ee.EE_K_HEAD, n) == want
