@@ -182,9 +182,9 @@ inline bool prompt_cut(int kernel, int N, int K, int M, size_t bytes, PartGeom* 
     // (With more than four row tiles of a few column panels the ranges of one panel's row tiles no longer run side by side,
     // so its weights are fetched again: 640 rows at the 7B widths, 80 tiles, the cut loses by 16 us for O and for down.)
     if (resid && (N + 255) / 256 * ((M + 127) / 128) > 64) return false;
-    // (Short contractions: with 128-row tiles 16 and 20 k-tiles gain 1 or lose up to 6 us by it, with 64-row tiles 12 lose 0 to
-    // 3 and 16 to 22 gain 0 to 3.)
-    if (K < (M <= 64 ? 16 : 24) * 32 || !part_geom(N, K, M, bytes, g)) return false;
+    // (Short contractions: with 128-row tiles 16 and 20 k-tiles gain 1 or lose up to 6 us by it and 24 gain 2 to 3, with 64-row
+    // tiles 12 lose 0 to 3, 16 and 20 gain 0 to 2 and 24 gain 2 to 4.)
+    if (K < (M <= 64 ? 22 : 32) * 32 || !part_geom(N, K, M, bytes, g)) return false;
     const int mtl = prompt_row_tiles(N, M);
     const long direct_tiles = (long)g->n_wgN * ((M + mtl * 16 - 1) / (mtl * 16));
     const long rounds = (direct_tiles + CUS - 1) / CUS;
