@@ -129,7 +129,7 @@ inline int part_wgs(const PartGeom& g) { return (g.n_wgN * g.n_wgM * g.KT + g.un
 // or 50 (128-row tiles) bounds the cut; the sum reads all parts back and writes M x N values, those of Q|K|V at 340 a
 // nanosecond (it writes V one 2-byte element at a time, as the cache keeps V transposed), others at 560.  Constants common to
 // both ways to launch are left out, so those of the two rules below are differences.  All fitted to the times of whole
-// prompts and steps with each of the four GEMMs cut and not, in all combinations (profiles/cut_rule.md).
+// prompts and steps with each of the four GEMMs cut and not, in all combinations.
 inline float cut_us(int kernel, const PartGeom& g, int M) {
     const int parts = part_wgs(g) + g.n_wgN * g.n_wgM;
     return g.unit * (16 + 2 * g.mtl) / (g.mtl == 4 ? 54.0f : 50.0f) + parts * 16 * g.mtl / 5300.0f +

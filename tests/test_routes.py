@@ -94,8 +94,8 @@ def test_eight_waves_on_short_contractions_only_where_they_were_measured_to_win(
     assert waves(config(4096, 11008), ee.EE_K_QKV) == 8 and waves(config(4096, 11008), ee.EE_K_DOWN) == 16
 
 
-# What cutting one projection (Q|K|V, O, gate|up, down) was measured to add to a layer, in us, where it is 2 us or more either way
-# (profiles/cut_rule.md); 0: less than that, or 2 to 3 us gained on 24 k-tiles with 128-row tiles, which the rule leaves alone.
+# What cutting one projection (Q|K|V, O, gate|up, down) was measured to add to a layer, in us, where it is 2 us or more either
+# way; 0: less than that, or 2 to 3 us gained on 24 k-tiles with 128-row tiles, which the rule leaves alone.
 MEASURED_STEPS = {
     (1024, 2816): {33: (2.5, 3, 0, 0), 64: (2.5, 3, 0, 0), 96: (-4, 0, -3, -9), 128: (-7, 0, -6, -14)},
     (2048, 5504): {33: (0, 0, 3, -9), 64: (0, 0, 3, -9), 66: (-6, -5, -4, -19), 96: (-10, -6, -7, -23)},
