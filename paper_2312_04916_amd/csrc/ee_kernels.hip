@@ -1948,7 +1948,7 @@ struct AttTile0 {
     int32_t one, row0, nq, pos0, seq;
 };
 
-template <int HD, int NW>
+template <int HD, int NW, bool ONCE>
 __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const __bf16* __restrict__ q, size_t q_lo, __bf16* __restrict__ out,
                                                              size_t out_lo, int out_pk, const SegDesc* __restrict__ desc,
                                                              const int32_t* __restrict__ btab, KvGeom kv,
@@ -1979,7 +1979,9 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const __bf16* __rest
     // exactly the 16 bytes of a transposed-V row that the P.V product needs as its other operand.
     const int krow0 = (li >> 2) * 8 + (li & 3);
 
-    // K and V of one 32-position tile, loaded straight into MFMA operand order
+    // K and V of one 32-position tile, loaded straight into MFMA operand order (ONCE: and not kept in the caches, see
+    // the launch)
+    auto load = [](const __bf16* p) { return ONCE ? __builtin_nontemporal_load((const u32x4*)p) : *(const u32x4*)p; };
     struct TileRegs {
         u32x4 k[2 * KK];
         u32x4 v[CG];
@@ -1995,10 +1997,10 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const __bf16* __rest
         for (int sub = 0; sub < 2; ++sub) {
             const __bf16* kp = kbase + (size_t)(krow0 + sub * 4) * HD + lg * 8;  // one load: 16 rows x 64 contiguous bytes
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) r.k[sub * KK + kk] = *(const u32x4*)(kp + kk * 32);
+            for (int kk = 0; kk < KK; ++kk) r.k[sub * KK + kk] = load(kp + kk * 32);
         }
 #pragma unroll
-        for (int c = 0; c < CG; ++c) r.v[c] = *(const u32x4*)(vbase + (c * 16 + li) * 32 + lg * 8);
+        for (int c = 0; c < CG; ++c) r.v[c] = load(vbase + (c * 16 + li) * 32 + lg * 8);
     };
 
     bf16x8 qh[KK], ql[KK];
@@ -2193,12 +2195,19 @@ static hipError_t launch_attention_mfma(const void* q, void* out, size_t io_lo, 
     if (NS > by_len) NS = by_len;
     if (NS > ATT_MAX_SPLITS) NS = ATT_MAX_SPLITS;
     if (NS < 1) NS = 1;
-    if (few)
-        EE_LAUNCH((attn_mfma_kernel<HD, 8>), dim3(wgs * NS), dim3(8 * 64), s, (const __bf16*)q, io_lo, (__bf16*)out, io_lo, out_pk, desc,
-                  btab, kv, lb, d, NS, part, t0);
-    else
-        EE_LAUNCH((attn_mfma_kernel<HD, 4>), dim3(wgs * NS), dim3(4 * 64), s, (const __bf16*)q, io_lo, (__bf16*)out, io_lo, out_pk, desc,
-                  btab, kv, lb, d, NS, part, t0);
+    // K and V that a step reads once and that no cache holds until the next step (256 MB behind the L2s; this is one layer
+    // of many) are read past the caches: 64 sequences of the 7B widths (434 MB a layer) 89 -> 80 us a layer = 5.4 TB/s, a
+    // pass of two steps 4600 -> 4450 us; 16 (300 MB) 4896 -> 4828.  One sequence (17 MB) loses by it, 37020 -> 37150 us.
+    size_t positions = (size_t)n_qt * max_ctx;
+    if (desc_host != nullptr) {
+        positions = 0;
+        for (int i = 0; i < n_qt; ++i) positions += desc_host->qt_pos0[i] + desc_host->qt_nq[i];
+    }
+    const bool once = positions * d * 4 >= ((size_t)64 << 20);
+    const auto kernel = few ? (once ? attn_mfma_kernel<HD, 8, true> : attn_mfma_kernel<HD, 8, false>)
+                            : (once ? attn_mfma_kernel<HD, 4, true> : attn_mfma_kernel<HD, 4, false>);
+    EE_LAUNCH(kernel, dim3(wgs * NS), dim3((few ? 8 : 4) * 64), s, (const __bf16*)q, io_lo, (__bf16*)out, io_lo, out_pk, desc, btab, kv, lb, d,
+              NS, part, t0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || NS == 1) return e;
     if (defer_ns != nullptr) {  // the consumer merges the splits itself
