@@ -1304,24 +1304,51 @@ __global__ __launch_bounds__(KS * 64, KS / 4) void rows_kernel(GemmArgs a, Epi e
         if (u < n) fill(u, u);
     rms.finish(a, rs);
     const int full = n / D, rem = n - full * D;
-    for (int gI = 0; gI + 1 < full; ++gI) {  // steady state: every refill is in range
+    if constexpr (MT == 4) {
+        // A slot is refilled while the next one is multiplied, a load between every few of its MFMAs: a wave that has its
+        // SIMD to itself waits half of its time for the memory pipeline to take a load, and in a burst of G + 2 MT of them
+        // the matrix core waits too (64 rows, 7B widths, whole steps of 64 sequences: 4438 -> 4381 us a pass of two steps
+        // through 8 layers; with two waves per SIMD, up to 32 rows, nothing: 4828 and 4875 us at 16 sequences).
+        const int done = full > 1 ? (full - 1) * D : 0;
+        if (n > 0) use(0);
+        for (int t = 0; t < done; t += D) {  // steady state: every refill is in range
 #pragma unroll
-        for (int u = 0; u < D; ++u) {
-            use(u);
-            fill(u, (gI + 1) * D + u);
-            __builtin_amdgcn_sched_barrier(0);
+            for (int u = 0; u < D; ++u) {
+                fill(u, t + u + D);
+                use((u + 1) % D);
+#pragma unroll
+                for (int i = 0; i < G + 2 * MT; ++i) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 2 * G * MT / (G + 2 * MT) > 0 ? 2 * G * MT / (G + 2 * MT) : 1, 0);  // MFMAs
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);                                                             // load
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
         }
-    }
-    if (full > 0) {  // last full group: refill only the slots the remainder needs
 #pragma unroll
-        for (int u = 0; u < D; ++u) {
-            use(u);
-            if (u < rem) fill(u, full * D + u);
+        for (int u = 0; u < 2 * D - 1; ++u) {
+            if (done + u + D < n) fill(u % D, done + u + D);
+            if (done + u + 1 < n) use((u + 1) % D);
         }
-    }
+    } else {
+        for (int gI = 0; gI + 1 < full; ++gI) {  // steady state: every refill is in range
 #pragma unroll
-    for (int u = 0; u < D; ++u)
-        if (u < rem) use(u);
+            for (int u = 0; u < D; ++u) {
+                use(u);
+                fill(u, (gI + 1) * D + u);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        if (full > 0) {  // last full group: refill only the slots the remainder needs
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                use(u);
+                if (u < rem) fill(u, full * D + u);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < D; ++u)
+            if (u < rem) use(u);
+    }
     typename Epi::Ops ops[NF];
 #pragma unroll
     for (int i = 0; i < NF; ++i) {
