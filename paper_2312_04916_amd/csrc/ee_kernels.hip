@@ -1165,12 +1165,12 @@ __global__ __launch_bounds__(512) void head_merge_kernel(const HeadPartial* __re
 // G + 2 MT KB, of which G come from HBM.  Up to 16 rows HBM bounds it (gate|up at the 7B widths 35.7 -> 31.0 us = 5.8
 // TB/s, at the 30B widths 91.5 -> 77.1 us = 6.2 TB/s, 16 and 4 rows); at 64 rows the bytes that a CU can have outstanding
 // do (about 40 KB: 30 to 70 GB/s per CU, the less the more of them come from HBM; neither a deeper ring nor another
-// order of the k-tiles moves it).  Hence as many tiles per workgroup as leave one workgroup per CU, one wave per SIMD
-// with all 512 registers from 33 rows on, and an epilogue that runs on registers behind a single barrier: the product is
+// order of the k-tiles moves it; the counters show 70 to 97 lines of 128 bytes on their way per CU, whatever is asked for).  Hence as many tiles per workgroup as leave one workgroup per CU, one wave per SIMD
+// with all 512 registers for five and six of them from 33 rows on, and an epilogue that runs on registers behind a single barrier: the product is
 // formed transposed (weights as the A operand), so a lane holds four consecutive features of one row, and everything it
 // needs from memory is requested before the barrier.  64 rows, 7B widths, before (8 waves, at most two tiles, epilogue
 // through LDS with one dependent look-up per element and pass) and now: Q|K|V 79.4 -> 41.8 us, gate|up 86.8 -> 52.1, head
-// 194 -> 128; 32 rows: gate|up 41.4 -> 33.1, Q|K|V 29.2 -> 23.7.
+// 194 -> 128; 32 rows: gate|up 41.4 -> 33.1, Q|K|V 29.2 -> 23.7.  (The loop for 33 and more rows has changed since, see there.)
 // ------------------------------------------------------------------------------------------------
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -1306,7 +1306,7 @@ __global__ __launch_bounds__(KS * 64, KS / 4) void rows_kernel(GemmArgs a, Epi e
     const int full = n / D, rem = n - full * D;
     if constexpr (MT == 4) {
         // A slot is refilled while the next one is multiplied, a load between every few of its MFMAs: a wave that has its
-        // SIMD to itself waits half of its time for the memory pipeline to take a load, and in a burst of G + 2 MT of them
+        // SIMD to itself waited half of its time for the memory pipeline to take a load, and in a burst of G + 2 MT of them
         // the matrix core waits too (64 rows, 7B widths, whole steps of 64 sequences: 4438 -> 4381 us a pass of two steps
         // through 8 layers; with two waves per SIMD, up to 32 rows, nothing: 4828 and 4875 us at 16 sequences).
         const int done = full > 1 ? (full - 1) * D : 0;
@@ -1634,11 +1634,16 @@ static hipError_t launch_rows_g(const GemmArgs& a, const Epi& e, int g, hipStrea
     if constexpr (KS == 16) {
         return g >= 2 ? launch_rows_as<KS, MT, 2>(a, e, s) : launch_rows_as<KS, MT, 1>(a, e, s);
     } else {
+        // Four row tiles: two waves per SIMD cover each other's waits for the memory pipeline.  Us a pass of two steps, 4 and
+        // 8 waves: 64 sequences, 768 wide, 12 layers 1519 / 1377; 2048 wide, 8 layers 1809 / 1675, 40 sequences 1672 / 1533;
+        // 4096 wide (Q|K|V, three tiles), 8 layers 4397 / 4343.  Five and six tiles keep one wave per SIMD: at the 256
+        // registers of two, six tiles spill 34 (4096 wide 4456), and 8 partial sums of five fill the LDS.
+        constexpr int K4 = MT == 4 ? 8 : KS;
         switch (g) {
-            case 1: return launch_rows_as<KS, MT, 1>(a, e, s);
-            case 2: return launch_rows_as<KS, MT, 2>(a, e, s);
-            case 3: return launch_rows_as<KS, MT, 3>(a, e, s);
-            case 4: return launch_rows_as<KS, MT, 4>(a, e, s);
+            case 1: return launch_rows_as<K4, MT, 1>(a, e, s);
+            case 2: return launch_rows_as<K4, MT, 2>(a, e, s);
+            case 3: return launch_rows_as<K4, MT, 3>(a, e, s);
+            case 4: return launch_rows_as<K4, MT, 4>(a, e, s);
             case 5: return launch_rows_as<KS, MT, 5>(a, e, s);
             default: return launch_rows_as<KS, MT, 6>(a, e, s);
         }

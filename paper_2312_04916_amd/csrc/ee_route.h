@@ -34,7 +34,7 @@ inline int step_waves(int T, int K, int N, bool packed, bool merges) {
     // k-tiles: 96 workgroups (down) 8.0 / 8.2, 7.6 / 7.8, 8.3 / 8.4.  32 to 40 k-tiles lose with one row: Q|K|V, 192
     // workgroups 7.2 / 7.6, 8.1 / 8.2, 8.2 / 8.2, 240 7.6 / 8.0; gate|up, 128 7.1 / 7.4; O, 64 7.4 / 7.7, 8.3 / 8.6.
     if (kt > 48 && kt <= 64 && T <= 3 && N / 16 <= CUS && !merges && !packed) return 8;
-    if (kt <= 64 || T > 32) return 4;   // (from 33 rows on: one wave per SIMD with all the registers)
+    if (kt <= 64 || T > 32) return 4;   // (from 33 rows on the column tiles per workgroup decide: launch_rows_g)
     if (kt <= 128 || T > 16) return 8;  // (16 waves of 1024 threads leave 128 registers each: one row tile only)
     return 16;
 }
