@@ -200,6 +200,11 @@ int ee_debug_plan(int n_segments, int32_t* filled, int position, int max_pending
 enum { EE_ROUTE_STAGED = 0, EE_ROUTE_ROWS = 1, EE_ROUTE_CUT = 2, EE_ROUTE_PANELS = 3 };
 int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route,
                         int32_t* waves);
+/* Test hook, host only: the launch of a GEMM of a decode step whose route is EE_ROUTE_ROWS (EE_ERR_ARG if it is another), of
+ * its first pass where it needs several: shape[0] = 16-column tiles per workgroup, [1] = waves of a workgroup (each takes
+ * every [1]th of the 32-element steps of the contraction), [2] = slots of a wave's operand ring, [3] = 1 if a slot is
+ * refilled between the matrix instructions of the next one, 0 if behind its own. */
+int ee_debug_rows_launch(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int32_t shape[4]);
 /* Measurement hook: the confidence every head reported in the latest ee_decode_step, conf[n_seqs][n_exits+1] (host;
  * row b = the b-th sequence of that call, column i = exit i, last column = final head); -1 where the head was not
  * evaluated for that sequence in that step (the token had left at a shallower exit, exits disabled or step forced).

@@ -1483,23 +1483,29 @@ int ee_debug_plan(int n_segments, int32_t* filled, int position, int max_pending
     return EE_OK;
 }
 
+// Output features and reduction length of a GEMM of the model; false: `kernel` names none.
+static bool gemm_sizes(const ee_config& c, int kernel, int* N, int* K) {
+    *K = kernel == EE_K_DOWN ? c.d_ff : c.d_model;
+    switch (kernel) {
+        case EE_K_QKV: *N = 3 * c.d_model; return true;
+        case EE_K_OPROJ:
+        case EE_K_DOWN: *N = c.d_model; return true;
+        case EE_K_SWIGLU: *N = 2 * c.d_ff; return true;
+        case EE_K_HEAD: *N = c.vocab; return true;
+        default: return false;
+    }
+}
+
 int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int prompt, int32_t* route,
                         int32_t* waves) {
     if (!cfg || !route) return EE_ERR_ARG;
     EECHK(ee_model_bytes(cfg, max_rows, max_seqs, nullptr, nullptr));
     if (cfg->dtype != EE_BF16) return EE_ERR_CONFIG;
     const WorkspaceLayout w = workspace_layout(*cfg, max_rows, max_seqs);
-    const int d = cfg->d_model, F = cfg->d_ff;
+    const int d = cfg->d_model;
     const bool head = kernel == EE_K_HEAD;
-    int N, K = d;
-    switch (kernel) {
-        case EE_K_QKV: N = 3 * d; break;
-        case EE_K_OPROJ: N = d; break;
-        case EE_K_SWIGLU: N = 2 * F; break;
-        case EE_K_DOWN: N = d, K = F; break;
-        case EE_K_HEAD: N = cfg->vocab; break;
-        default: return EE_ERR_ARG;
-    }
+    int N, K;
+    if (!gemm_sizes(*cfg, kernel, &N, &K)) return EE_ERR_ARG;
     if (rows < 1 || rows > (prompt ? w.pf_rows : head ? max_seqs : max_rows) || (prompt && head)) return EE_ERR_ARG;
     PartGeom g;
     if (prompt)
@@ -1511,6 +1517,20 @@ int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int ke
     else
         *route = route::step_cut(kernel, N, K, rows, cfg->gemm_min_workgroups, w.stage - w.partials, &g) ? EE_ROUTE_CUT : EE_ROUTE_ROWS;
     if (waves) *waves = *route == EE_ROUTE_STAGED ? route::step_waves(rows, K, N, false, false) : 0;
+    return EE_OK;
+}
+
+int ee_debug_rows_launch(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int32_t shape[4]) {
+    int32_t r;
+    int N, K;
+    if (!shape) return EE_ERR_ARG;
+    EECHK(ee_debug_gemm_route(cfg, max_rows, max_seqs, kernel, rows, 0, &r, nullptr));
+    if (r != EE_ROUTE_ROWS || !gemm_sizes(*cfg, kernel, &N, &K)) return EE_ERR_ARG;
+    const route::RowsShape s = route::rows_shape(std::min(rows, route::PASS_ROWS), K, N, cfg->gemm_min_workgroups);
+    shape[0] = s.tiles;
+    shape[1] = s.waves;
+    shape[2] = route::rows_ring(s.waves, s.mt, s.tiles);
+    shape[3] = route::rows_loads_between(s.waves, s.mt);
     return EE_OK;
 }
 

@@ -1232,18 +1232,10 @@ struct RmsRows {
     }
 };
 
-// Ring slots per wave: as many as the registers hold next to the accumulators (512 per lane with one wave per SIMD, 256
-// with two, 128 with four).
-template <int KS, int MT, int G>
-constexpr int rows_depth() {
-    const int d = ((KS == 4 ? 290 : KS == 8 ? 190 : 84) - 4 * G * MT) / (4 * (G + 2 * MT));
-    return d < 2 ? 2 : d > 8 ? 8 : d;
-}
-
 template <int KS, int MT, int G, typename Epi>
 __global__ __launch_bounds__(KS * 64, KS / 4) void rows_kernel(GemmArgs a, Epi e) {
     static_assert(KS % MT == 0, "the epilogue gives a wave one row tile");
-    constexpr int D = rows_depth<KS, MT, G>();
+    constexpr int D = route::rows_ring(KS, MT, G);
     constexpr int NF = (G * MT + KS - 1) / KS;  // result tiles per wave in the epilogue
     extern __shared__ f32x4 rows_lds[];         // [KS][G * MT][64]
     __shared__ float rs[MT * 16];
@@ -1304,11 +1296,7 @@ __global__ __launch_bounds__(KS * 64, KS / 4) void rows_kernel(GemmArgs a, Epi e
         if (u < n) fill(u, u);
     rms.finish(a, rs);
     const int full = n / D, rem = n - full * D;
-    if constexpr (MT == 4) {
-        // A slot is refilled while the next one is multiplied, a load between every few of its MFMAs: a wave that has its
-        // SIMD to itself waited half of its time for the memory pipeline to take a load, and in a burst of G + 2 MT of them
-        // the matrix core waits too (64 rows, 7B widths, whole steps of 64 sequences: 4438 -> 4381 us a pass of two steps
-        // through 8 layers; with two waves per SIMD, up to 32 rows, nothing: 4828 and 4875 us at 16 sequences).
+    if constexpr (route::rows_loads_between(KS, MT)) {  // a slot is refilled while the next one is multiplied
         const int done = full > 1 ? (full - 1) * D : 0;
         if (n > 0) use(0);
         for (int t = 0; t < done; t += D) {  // steady state: every refill is in range
@@ -1629,36 +1617,28 @@ static hipError_t launch_rows_as(const GemmArgs& a, const Epi& e, hipStream_t s)
     return hipGetLastError();
 }
 
-template <int KS, int MT, typename Epi>
-static hipError_t launch_rows_g(const GemmArgs& a, const Epi& e, int g, hipStream_t s) {
-    if constexpr (KS == 16) {
-        return g >= 2 ? launch_rows_as<KS, MT, 2>(a, e, s) : launch_rows_as<KS, MT, 1>(a, e, s);
-    } else {
-        // Four row tiles: two waves per SIMD cover each other's waits for the memory pipeline.  Us a pass of two steps, 4 and
-        // 8 waves: 64 sequences, 768 wide, 12 layers 1519 / 1377; 2048 wide, 8 layers 1809 / 1675, 40 sequences 1672 / 1533;
-        // 4096 wide (Q|K|V, three tiles), 8 layers 4397 / 4343.  Five and six tiles keep one wave per SIMD: at the 256
-        // registers of two, six tiles spill 34 (4096 wide 4456), and 8 partial sums of five fill the LDS.
-        constexpr int K4 = MT == 4 ? 8 : KS;
-        switch (g) {
-            case 1: return launch_rows_as<K4, MT, 1>(a, e, s);
-            case 2: return launch_rows_as<K4, MT, 2>(a, e, s);
-            case 3: return launch_rows_as<K4, MT, 3>(a, e, s);
-            case 4: return launch_rows_as<K4, MT, 4>(a, e, s);
-            case 5: return launch_rows_as<KS, MT, 5>(a, e, s);
-            default: return launch_rows_as<KS, MT, 6>(a, e, s);
-        }
-    }
-}
-
-// a launch of many rows (A in operand order)
+// a launch of up to 64 rows (A in operand order), see route::rows_shape
 template <typename Epi>
 static hipError_t launch_rows(const GemmCommon& c, const GemmArgs& a, const Epi& e, hipStream_t s) {
-    int ks = ks_of(c);
-    const int mt = route::row_tiles(c.T), g = route::tiles_per_wg(mt, a.n_tiles, c.min_wgs);
-    if (ks == 16 && g >= 3) ks = 8;  // (1024 threads leave 128 registers per lane: two tiles at most)
-    if (mt == 4) return launch_rows_g<4, 4>(a, e, g, s);
-    if (mt == 2) return ks == 4 ? launch_rows_g<4, 2>(a, e, g, s) : launch_rows_g<8, 2>(a, e, g, s);
-    return ks == 4 ? launch_rows_g<4, 1>(a, e, g, s) : ks == 8 ? launch_rows_g<8, 1>(a, e, g, s) : launch_rows_g<16, 1>(a, e, g, s);
+    const route::RowsShape r = route::rows_shape(c.T, c.K, c.N, c.min_wgs);
+#define EE_ROWS(KS, MT, G) \
+    if (r.waves == KS && r.mt == MT && r.tiles == G) return launch_rows_as<KS, MT, G>(a, e, s)
+#define EE_ROWS_6(KS, MT) EE_ROWS(KS, MT, 1); EE_ROWS(KS, MT, 2); EE_ROWS(KS, MT, 3); EE_ROWS(KS, MT, 4); EE_ROWS(KS, MT, 5); EE_ROWS(KS, MT, 6)
+    EE_ROWS_6(4, 1);
+    EE_ROWS_6(8, 1);
+    EE_ROWS(16, 1, 1);
+    EE_ROWS(16, 1, 2);
+    EE_ROWS_6(4, 2);
+    EE_ROWS_6(8, 2);
+    EE_ROWS(8, 4, 1);
+    EE_ROWS(8, 4, 2);
+    EE_ROWS(8, 4, 3);
+    EE_ROWS(8, 4, 4);
+    EE_ROWS(4, 4, 5);
+    EE_ROWS(4, 4, 6);
+#undef EE_ROWS_6
+#undef EE_ROWS
+    return hipErrorInvalidValue;
 }
 
 static bool is_cut(const GemmCommon& c, int kernel, PartGeom* g) {

@@ -34,7 +34,7 @@ inline int step_waves(int T, int K, int N, bool packed, bool merges) {
     // k-tiles: 96 workgroups (down) 8.0 / 8.2, 7.6 / 7.8, 8.3 / 8.4.  32 to 40 k-tiles lose with one row: Q|K|V, 192
     // workgroups 7.2 / 7.6, 8.1 / 8.2, 8.2 / 8.2, 240 7.6 / 8.0; gate|up, 128 7.1 / 7.4; O, 64 7.4 / 7.7, 8.3 / 8.6.
     if (kt > 48 && kt <= 64 && T <= 3 && N / 16 <= CUS && !merges && !packed) return 8;
-    if (kt <= 64 || T > 32) return 4;   // (from 33 rows on the column tiles per workgroup decide: launch_rows_g)
+    if (kt <= 64 || T > 32) return 4;   // (packed rows: rows_shape has the last word)
     if (kt <= 128 || T > 16) return 8;  // (16 waves of 1024 threads leave 128 registers each: one row tile only)
     return 16;
 }
@@ -98,6 +98,39 @@ inline int tiles_per_wg(int mt, int n_tiles, int min_wgs) {
         if (cost < 0 || c < cost) cost = c, best = g;
     }
     return best;
+}
+
+// Ring slots per wave of rows_kernel: as many as the registers hold next to the accumulators (512 per lane with one wave per
+// SIMD, 256 with two, 128 with four).
+constexpr int rows_ring(int waves, int mt, int tiles) {
+    const int d = ((waves == 4 ? 290 : waves == 8 ? 190 : 84) - 4 * tiles * mt) / (4 * (tiles + 2 * mt));
+    return d < 2 ? 2 : d > 8 ? 8 : d;
+}
+
+// Does rows_kernel refill a ring slot between the MFMAs of the next one (or in a burst behind its own)?  Four row tiles with
+// one wave per SIMD only: that wave waits half of its time for the memory pipeline to take a load, and in a burst of G + 2 MT
+// of them its matrix core waits too.  Us a full-depth step, burst / between: 4 waves (gate|up at 4096 wide, Q|K|V and gate|up
+// at 6656), 33 | 48 | 64 rows: 4096 wide, 8 layers 1376 / 1351 | 1443 / 1418 | 1524 / 1504 (gate|up 51.8 / 48.5 us), 6656 wide,
+// 6 layers 2039 / 2032 | 2090 / 2082 | 2207 / 2199.  8 waves cover each other's waits and lose by it: 2048 wide, 8 layers 700 /
+// 707 | 724 / 729 | 761 / 769, 3072 wide 998 / 1001 | 1016 / 1021 | 1066 / 1072, 5120 wide, 4 layers 1118 / 1135 | 1176 / 1189
+// | 1203 / 1219.
+constexpr bool rows_loads_between(int waves, int mt) { return mt == 4 && waves == 4; }
+
+// The launch of up to 64 packed rows.
+struct RowsShape {
+    int mt, tiles, waves;  // row tiles, column tiles per workgroup, waves
+};
+
+inline RowsShape rows_shape(int T, int K, int N, int min_wgs) {
+    RowsShape r{row_tiles(T), 0, step_waves(T, K, N, true, false)};
+    r.tiles = tiles_per_wg(r.mt, N / 16, min_wgs);
+    if (r.waves == 16 && r.tiles >= 3) r.waves = 8;  // (1024 threads leave 128 registers per lane: two tiles at most)
+    // Four row tiles: two waves per SIMD cover each other's waits for the memory pipeline.  Us a pass of two steps, 4 and 8
+    // waves: 64 sequences, 768 wide, 12 layers 1519 / 1377; 2048 wide, 8 layers 1809 / 1675, 40 sequences 1672 / 1533; 4096
+    // wide (Q|K|V, three tiles), 8 layers 4397 / 4343.  Five and six tiles keep one wave per SIMD: at the 256 registers of
+    // two, six tiles spill 34 (4096 wide 4456), and 8 partial sums of five fill the LDS.
+    if (r.mt == 4) r.waves = r.tiles <= 4 ? 8 : 4;
+    return r;
 }
 
 // ---- GEMMs cut along their contraction

@@ -94,6 +94,32 @@ def test_eight_waves_on_short_contractions_only_where_they_were_measured_to_win(
     assert waves(config(4096, 11008), ee.EE_K_QKV) == 8 and waves(config(4096, 11008), ee.EE_K_DOWN) == 16
 
 
+def test_ring_refills_go_between_the_mfmas_where_a_wave_has_its_simd_to_itself():
+    """33 and more rows: up to four column tiles run 8 waves, two per SIMD, and refill a slot in a burst; five and six run 4, one
+    per SIMD, and refill between the MFMAs, which 8 waves were measured to lose by.  Up to 32 rows: in a burst."""
+    seen = set()
+    for d, F in ((768, 2048), (1024, 2816), (2048, 5504), (3072, 8192), (4096, 11008), (5120, 13824), (6656, 17920)):
+        for min_wgs in (0, 511, 200, 64, 16):
+            cfg = config(d, F, 50304, gemm_min_workgroups=min_wgs)
+            for k in (*GEMMS, ee.EE_K_HEAD):
+                for rows in (4, 16, 17, 32, 33, 48, 64):
+                    if route(cfg, k, rows) != ee.EE_ROUTE_ROWS:
+                        continue
+                    tiles, waves, ring, between = ee.rows_launch(cfg, k, rows)
+                    assert 1 <= tiles <= 6 and 2 <= ring <= 8
+                    if rows > 32:
+                        assert (waves, between) == ((8, 0) if tiles <= 4 else (4, 1)), (d, k, rows)
+                        seen.add(tiles)
+                    else:
+                        assert waves in (4, 8, 16) and between == 0, (d, k, rows)
+    assert seen == {1, 2, 3, 4, 5, 6}
+    r, L = (C.c_int32 * 4)(), ee.lib()
+    assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_QKV, 1, r) == -7   # staged
+    assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_DOWN, 64, r) == -7  # cut
+    assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_QKV, 65, r) == -7   # more rows than max_rows
+    assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_QKV, 64, None) == -7
+
+
 # What cutting one projection (Q|K|V, O, gate|up, down) was measured to add to a layer, in us, where it is 2 us or more either
 # way; 0: less than that, or 2 to 3 us gained on 24 k-tiles with 128-row tiles, which the rule leaves alone.
 MEASURED_STEPS = {
