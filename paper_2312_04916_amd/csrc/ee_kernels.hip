@@ -1313,8 +1313,8 @@ __global__ __launch_bounds__(KS * 64, KS / 4) void rows_kernel(GemmArgs a, Epi e
             }
         }
 #pragma unroll
-        for (int u = 0; u < 2 * D - 1; ++u) {
-            if (done + u + D < n) fill(u % D, done + u + D);
+        for (int u = 0; u < 2 * D - 1; ++u) {  // (fewer than 2 D k-tiles are left, of which the ring holds D)
+            if (u < D - 1 && done + u + D < n) fill(u, done + u + D);
             if (done + u + 1 < n) use((u + 1) % D);
         }
     } else {

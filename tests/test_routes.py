@@ -9,6 +9,7 @@ from workload import CONFIGS
 
 from common import cut_projections, ee_config_of
 from test_gpu_rows import CUT_PROMPTS, CUT_STEPS, PROMPT_SHAPES, SHAPES, STEP_LIMITS
+from test_gpu_rows_tiles import DOWN_MIN_WGS
 
 GEMMS = (ee.EE_K_QKV, ee.EE_K_OPROJ, ee.EE_K_SWIGLU, ee.EE_K_DOWN)
 
@@ -166,3 +167,16 @@ def test_the_gpu_tests_run_the_routes_they_claim():
             step = rows_env or 512
             got = [cut_projections(cfg, min(step, n - p), True, 64, 1) for p in range(0, n, step)]
             assert got == passes, (name, n, rows_env)
+
+
+def test_the_gpu_tests_of_column_tiles_fill_every_ring_twice():
+    shape, seen = SHAPES["d1024"], set()
+    for tiles, min_wgs in DOWN_MIN_WGS.items():
+        cfg = ee_config_of(shape, 128, gemm_min_workgroups=min_wgs)
+        for rows in CUT_STEPS["d1024"]:
+            got, waves, ring, between = ee.rows_launch(cfg, ee.EE_K_DOWN, rows, **STEP_LIMITS)
+            assert (got, waves, between) == (tiles, *((8, 0) if tiles <= 4 else (4, 1)))
+            per_wave = [(shape.d_ff // 32 - w + waves - 1) // waves for w in range(waves)]
+            assert min(per_wave) >= 2 * ring and any(n % ring for n in per_wave)
+            seen.add((tiles, waves))
+    assert len(seen) == 6
