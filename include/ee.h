@@ -205,6 +205,10 @@ int ee_debug_gemm_route(const ee_config* cfg, int max_rows, int max_seqs, int ke
  * every [1]th of the 32-element steps of the contraction), [2] = slots of a wave's operand ring, [3] = 1 if a slot is
  * refilled between the matrix instructions of the next one, 0 if behind its own. */
 int ee_debug_rows_launch(const ee_config* cfg, int max_rows, int max_seqs, int kernel, int rows, int32_t shape[4]);
+/* Test hook, host only: *past = 1 if the decode attention of a bf16 model (EE_ERR_CONFIG for fp32) reads K and V without
+ * keeping them in the caches.  contexts[i]: positions of sequence i, its rows of the step included; rows[i]: those rows (the
+ * deferred and the current one); layers: the step's, with exits on those up to the end of the launch's segment. */
+int ee_debug_kv_past_caches(const ee_config* cfg, int n_seqs, const int32_t* contexts, const int32_t* rows, int layers, int32_t* past);
 /* Measurement hook: the confidence every head reported in the latest ee_decode_step, conf[n_seqs][n_exits+1] (host;
  * row b = the b-th sequence of that call, column i = exit i, last column = final head); -1 where the head was not
  * evaluated for that sequence in that step (the token had left at a shallower exit, exits disabled or step forced).

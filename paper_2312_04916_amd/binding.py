@@ -19,7 +19,7 @@ KERNEL_NAMES = ["qkv", "attention", "oproj", "swiglu", "down", "head"]
  EE_T_EXIT_NORM, EE_T_EXIT_HEAD, EE_T_FINAL_NORM, EE_T_FINAL_HEAD) = range(14)
 
 EXPORTS = ["ee_strerror", "ee_last_hip_error", "ee_model_bytes", "ee_model_create", "ee_model_set_tensor",
-           "ee_model_load", "ee_model_free", "ee_debug_set_logits", "ee_debug_step_confidences", "ee_debug_plan", "ee_debug_gemm_route", "ee_debug_rows_launch", "ee_profile_begin", "ee_profile_end", "ee_profile_every", "ee_measure_stream_read", "ee_debug_lane_reductions", "ee_kv_cache_bytes", "ee_kv_cache_create",
+           "ee_model_load", "ee_model_free", "ee_debug_set_logits", "ee_debug_step_confidences", "ee_debug_plan", "ee_debug_gemm_route", "ee_debug_rows_launch", "ee_debug_kv_past_caches", "ee_profile_begin", "ee_profile_end", "ee_profile_every", "ee_measure_stream_read", "ee_debug_lane_reductions", "ee_kv_cache_bytes", "ee_kv_cache_create",
            "ee_kv_cache_set_refeed", "ee_kv_cache_set_pipeline", "ee_kv_cache_reset", "ee_kv_cache_filled", "ee_kv_cache_pending", "ee_kv_cache_read",
            "ee_kv_cache_flush", "ee_kv_cache_free", "ee_debug_read_hidden", "ee_prefill", "ee_prefill_scored",
            "ee_decode_step", "ee_decode_step_static"]
@@ -76,6 +76,7 @@ def lib():
         L.ee_debug_plan.argtypes = [C.c_int, i32p, C.c_int, C.c_int, C.c_int, C.c_int, i32p, i32p, i32p]
         L.ee_debug_gemm_route.argtypes = [C.POINTER(ee_config), C.c_int, C.c_int, C.c_int, C.c_int, C.c_int, i32p, i32p]
         L.ee_debug_rows_launch.argtypes = [C.POINTER(ee_config), C.c_int, C.c_int, C.c_int, C.c_int, i32p]
+        L.ee_debug_kv_past_caches.argtypes = [C.POINTER(ee_config), C.c_int, i32p, i32p, C.c_int, i32p]
         L.ee_profile_begin.argtypes = [vp, C.c_int, C.c_int]
         L.ee_profile_end.argtypes = [vp, i32p, fp]
         L.ee_profile_every.argtypes = [vp, C.c_int]
@@ -350,6 +351,13 @@ def rows_launch(cfg: ee_config, kernel: int, rows: int, max_rows: int = EE_MAX_R
     s = (C.c_int32 * 4)()
     _chk(lib().ee_debug_rows_launch(C.byref(cfg), max_rows, max_seqs, kernel, rows, s), "ee_debug_rows_launch")
     return tuple(s)
+
+
+def kv_past_caches(cfg: ee_config, contexts: Sequence[int], rows: Sequence[int], layers: int) -> bool:
+    """ee_debug_kv_past_caches (host only)."""
+    c, r, past = _i32(contexts), _i32(rows), C.c_int32()
+    _chk(lib().ee_debug_kv_past_caches(C.byref(cfg), len(c), _ip(c), _ip(r), layers, C.byref(past)), "ee_debug_kv_past_caches")
+    return bool(past.value)
 
 
 def prefill(model: Model, cache: KvCache, seq: int, tokens: Sequence[int], threshold: float, stream=None):

@@ -438,7 +438,7 @@ struct BlockW {
 enum { BLOCK_ALL = 0, BLOCK_FRONT = 1, BLOCK_REST = 2 };  // FRONT: the KV write and the attention; REST: what follows them
 
 int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer, const BlockW& w, void* a_first, bool kv_only,
-              const float* g_next, const float* g_head, bool pack_next, int max_ctx, hipStream_t st, int phase = BLOCK_ALL,
+              const float* g_next, const float* g_head, bool pack_next, int max_ctx, bool past_caches, hipStream_t st, int phase = BLOCK_ALL,
               int* att_ns_io = nullptr) {
     const ee_config& cf = m->cfg;
     const int d = cf.d_model, F = cf.d_ff, dt = cf.dtype;
@@ -479,7 +479,7 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
         Timed t(m, EE_K_ATTN, st);
         HIPCHK(launch_attention(dt, m->ws + m->wsl.q, m->ws + m->wsl.attn, m->lo_rows(d), dd, g.desc_host, T, n_qt, m->dev_btab(), c->geom,
                                 kv_layer, d,
-                                (float*)(m->ws + m->wsl.attn_part), max_ctx,
+                                (float*)(m->ws + m->wsl.attn_part), max_ctx, past_caches,
                                 (dt == EE_BF16 && !pk_d) ? &att_ns : nullptr, pk_d, st));
     }
     if (phase == BLOCK_FRONT) {
@@ -514,7 +514,7 @@ int run_block(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int kv_layer
 // ---- the per-layer launch sequence over the rows described by dev_desc(di)
 // first_phase: BLOCK_FRONT stops after the attention of layer l0 (nothing of the rows' residual stream has changed
 // then); BLOCK_REST takes the pass up from there.  *att_ns_io carries the attention's split count between the two.
-int run_layers(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int l0, int l1, int max_ctx, hipStream_t st,
+int run_layers(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int l0, int l1, int max_ctx, bool past_caches, hipStream_t st,
                int first_phase = BLOCK_ALL, int* att_ns_io = nullptr) {
     const ee_config& cf = m->cfg;
     const int d = cf.d_model, dt = cf.dtype;
@@ -533,7 +533,7 @@ int run_layers(ee_model* m, ee_kv_cache* c, int di, int T, int n_qt, int l0, int
         const float* g_head = nullptr;
         for (int i = 0; i < cf.n_exits; ++i)
             if (cf.exit_layers[i] == l + 1) g_head = m->exit_in_gain(i);
-        EECHK(run_block(m, c, di, T, n_qt, l, w, c->xg(), false, g_next, g_head, l + 1 < l1, max_ctx, st,
+        EECHK(run_block(m, c, di, T, n_qt, l, w, c->xg(), false, g_next, g_head, l + 1 < l1, max_ctx, past_caches, st,
                         l == l0 ? first_phase : BLOCK_ALL, att_ns_io));
         if (l == l0 && first_phase == BLOCK_FRONT) break;
     }
@@ -580,7 +580,8 @@ void fill_exit_layer_desc(const ee_model* m, const ee_kv_cache* c, int seg, cons
 // `src` (host_desc(mlp_desc(seg)) lists their copies): the rows' x, first operand and sum-of-squares partials are copied to the exit's slots, every copy leaves
 // its K and V in the exit's cache layer, and, with_head, the whole layer runs on the copies so that the head rows'
 // x'.g (g: the exit's norm gain, or 1) stands in the first operand store at the copies' slots.
-int run_exit_layer(ee_model* m, ee_kv_cache* c, int seg, const int32_t* src, bool with_head, int max_ctx, hipStream_t st) {
+int run_exit_layer(ee_model* m, ee_kv_cache* c, int seg, const int32_t* src, bool with_head, int max_ctx, bool past_caches,
+                   hipStream_t st) {
     const ee_config& cf = m->cfg;
     const int d = cf.d_model, dt = cf.dtype, me = m->mlp_desc(seg);
     const SegDesc* eh = m->host_desc(me);
@@ -593,7 +594,7 @@ int run_exit_layer(ee_model* m, ee_kv_cache* c, int seg, const int32_t* src, boo
     const BlockW w{m->wbase + m->wl.eqkv[seg], m->wbase + m->wl.ewo[seg], m->wbase + m->wl.egu[seg], m->wbase + m->wl.ewd[seg],
                    m->gain(m->wl.gm[seg])};
     return run_block(m, c, me, T, eh->n_qt, cf.n_layers + seg, w, c->xgh(), !with_head, m->exit_out_gain(seg), nullptr, false, max_ctx,
-                     st);
+                     past_caches, st);
 }
 
 // head `hi` (exit number, or n_exits for the final head) on the rows listed in dev_desc(di).head_*
@@ -746,8 +747,9 @@ struct StepSeq {
 
 // rows of the active sequences for segment `seg`: positions [filled[seg], last] of each
 void build_desc(const ee_model* m, const ee_kv_cache* c, SegDesc* d, const std::vector<StepSeq>& ss, int seg, bool with_head,
-                float threshold, int* rows_out) {
+                float threshold, int* rows_out, route::KvReads* reads) {
     int T = 0, nqt = 0, nh = 0;
+    *reads = {};
     for (size_t b = 0; b < ss.size(); ++b) {
         if (!ss[b].active) continue;
         const SeqState& s = c->seqs[ss[b].seq];
@@ -762,9 +764,10 @@ void build_desc(const ee_model* m, const ee_kv_cache* c, SegDesc* d, const std::
             d->kvblk[T] = s.blocks[pos / c->BT];
             d->rseq[T] = (int)b;
         }
-        for (int r = first; r < T; r += 16) {
+        reads->add(lo, T - first);
+        for (int r = first; r < T; r += route::ATT_ROWS) {
             d->qt_row0[nqt] = r;
-            d->qt_nq[nqt] = std::min(16, T - r);
+            d->qt_nq[nqt] = std::min(route::ATT_ROWS, T - r);
             d->qt_pos0[nqt] = d->pos[r];
             d->qt_seq[nqt] = (int)b;
             ++nqt;
@@ -823,9 +826,13 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
     for (size_t b = 0; b < ss.size(); ++b) put_btab(m, c, (int)b, c->seqs[ss[b].seq]);
     int max_ctx = max_ctx_of(c, ss);
     std::vector<int> rows(n_seg, 0);
+    std::vector<route::KvReads> reads(n_seg);
+    auto past_caches = [&](int s) {
+        return route::kv_past_caches(reads[s], m->cfg.d_model, decode && threshold < 1.0f ? m->seg_end(s) : m->cfg.n_layers);
+    };
     auto rebuild = [&](int from) -> int {
         for (int s = from; s < n_seg; ++s) {
-            build_desc(m, c, m->host_desc(s), ss, s, decode, threshold, &rows[s]);
+            build_desc(m, c, m->host_desc(s), ss, s, decode, threshold, &rows[s], &reads[s]);
             if (rows[s] > m->max_rows) return EE_ERR_NOMEM;
         }
         // (the first upload of a step also looks up the rows that start at the embedding)
@@ -842,11 +849,11 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
             // pipeline mode: the stage's previous token may still be on the other stream (segment 0 only ever runs here)
             if (pp.on && s > 0 && pp.last_ev[s] >= 0 && pp.last_stream[s] != st)
                 HIPCHK(hipStreamWaitEvent(st, pp.pool[pp.last_ev[s]], 0));
-            EECHK(run_layers(m, c, s, hd->T, hd->n_qt, m->seg_begin(s), m->seg_end(s), max_ctx, st, spec_seg == s ? BLOCK_REST : BLOCK_ALL,
-                             &spec_ns));
+            EECHK(run_layers(m, c, s, hd->T, hd->n_qt, m->seg_begin(s), m->seg_end(s), max_ctx, past_caches(s), st,
+                             spec_seg == s ? BLOCK_REST : BLOCK_ALL, &spec_ns));
             if (m->exit_layer() && s < m->cfg.n_exits)
                 EECHK(run_exit_layer(m, c, s, (const int32_t*)((char*)m->dev_desc(s) + offsetof(SegDesc, xrow)), decode && hd->n_head > 0,
-                                     max_ctx, st));
+                                     max_ctx, past_caches(s), st));
             if (pp.on && s > 0) {
                 const int e = pp.next_ev++ % Pipeline::POOL;
                 HIPCHK(hipEventRecord(pp.pool[e], st));
@@ -867,7 +874,8 @@ int run_step(ee_model* m, ee_kv_cache* c, std::vector<StepSeq>& ss, float thresh
             if (!is_final && ss.size() == 1 && !pp.on) {
                 const SegDesc* nd = m->host_desc(s + 1);
                 if (nd->T > 0 && route::front_ahead(m->cfg.dtype, nd->T, m->cfg.d_model)) {
-                    EECHK(run_layers(m, c, s + 1, nd->T, nd->n_qt, m->seg_begin(s + 1), m->seg_end(s + 1), max_ctx, st, BLOCK_FRONT, &spec_ns));
+                    EECHK(run_layers(m, c, s + 1, nd->T, nd->n_qt, m->seg_begin(s + 1), m->seg_end(s + 1), max_ctx, past_caches(s + 1), st,
+                                     BLOCK_FRONT, &spec_ns));
                     spec_seg = s + 1;
                     c->spec_used = true;
                 }
@@ -991,6 +999,9 @@ int prefill_large(ee_model* m, ee_kv_cache* c, int seq, const int32_t* tokens, i
         }
     }
     EECHK(upload(m, st));
+    route::KvReads reads;  // of an exit's layer, which runs on the last position
+    reads.add(n_tokens - 1, 1);
+    const bool past_caches = route::kv_past_caches(reads, d, cf.n_layers);
     const int32_t* bt = m->dev_btab();
     PfGemm g{};
     g.part = ws + w.pf_part;
@@ -1133,7 +1144,7 @@ int prefill_large(ee_model* m, ee_kv_cache* c, int seq, const int32_t* tokens, i
                                             c->ssq() + (size_t)slot * c->ssq_stride, c->ssq_stride, st));
                 if (!fin && m->exit_layer())
                     EECHK(run_exit_layer(m, c, sgi, (const int32_t*)((char*)m->dev_desc(sgi) + offsetof(SegDesc, head_xrow)), true,
-                                         n_tokens, st));
+                                         n_tokens, past_caches, st));
                 EECHK(run_head(m, c, sgi, sgi, 1, fin ? HEAD_EMIT : HEAD_RULE, threshold, st));
             }
         }
@@ -1534,6 +1545,20 @@ int ee_debug_rows_launch(const ee_config* cfg, int max_rows, int max_seqs, int k
     return EE_OK;
 }
 
+int ee_debug_kv_past_caches(const ee_config* cfg, int n_seqs, const int32_t* contexts, const int32_t* rows, int layers, int32_t* past) {
+    if (!cfg || !contexts || !rows || !past || n_seqs < 1 || n_seqs > EE_MAX_SEQS) return EE_ERR_ARG;
+    EECHK(ee_model_bytes(cfg, 1, 1, nullptr, nullptr));
+    if (cfg->dtype != EE_BF16) return EE_ERR_CONFIG;
+    if (layers < 1 || layers > cfg->n_layers) return EE_ERR_ARG;
+    route::KvReads r;
+    for (int i = 0; i < n_seqs; ++i) {
+        if (rows[i] < 1 || contexts[i] < rows[i]) return EE_ERR_ARG;
+        r.add(contexts[i] - rows[i], rows[i]);
+    }
+    *past = route::kv_past_caches(r, cfg->d_model, layers);
+    return EE_OK;
+}
+
 int ee_debug_step_confidences(const ee_model* m, int n_seqs, float* conf) {
     if (!m || !conf || n_seqs < 1 || n_seqs > EE_MAX_SEQS) return EE_ERR_ARG;
     const int n_seg = m->n_seg();
@@ -1797,12 +1822,15 @@ int prefill_impl(ee_model* m, ee_kv_cache* c, int seq, const int32_t* tokens, in
         EECHK(upload(m, st));
         HIPCHK(launch_embed(cf.dtype, m->wbase + m->wl.embed, m->dev_tokens(), m->dev_desc(0), n, cf.d_model, m->gain(m->wl.g1[0]),
                             c->x(), c->xg(), c->xs_lo, c->ssq(), c->ssq_stride, st));
+        route::KvReads reads;
+        reads.add(p0, n);
+        const bool past_caches = route::kv_past_caches(reads, cf.d_model, cf.n_layers);
         for (int sgi = 0; sgi < n_seg; ++sgi) {
-            EECHK(run_layers(m, c, 0, n, d->n_qt, m->seg_begin(sgi), m->seg_end(sgi), p0 + n, st));
+            EECHK(run_layers(m, c, 0, n, d->n_qt, m->seg_begin(sgi), m->seg_end(sgi), p0 + n, past_caches, st));
             bool fin = sgi == n_seg - 1;
             if (!fin && m->exit_layer())
                 EECHK(run_exit_layer(m, c, sgi, (const int32_t*)((char*)m->dev_desc(0) + offsetof(SegDesc, xrow)),
-                                     last && threshold < 1.0f, p0 + n, st));
+                                     last && threshold < 1.0f, p0 + n, past_caches, st));
             if (last && (fin || threshold < 1.0f)) EECHK(run_head(m, c, sgi, sgi, 1, fin ? HEAD_EMIT : HEAD_RULE, threshold, st));
         }
         HIPCHK(hipStreamSynchronize(st));  // the pinned staging is rewritten by the next chunk

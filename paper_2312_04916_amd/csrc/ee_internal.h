@@ -118,8 +118,9 @@ hipError_t launch_gemm_head(const GemmCommon& c, HeadPartial* partials, float* l
 
 hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, const SegDesc* desc, const SegDesc* desc_host, int T, int n_qt,
                             const int32_t* btab,
-                            const KvGeom& kv, int layer, int d, float* part, int max_ctx, int* defer_ns,
+                            const KvGeom& kv, int layer, int d, float* part, int max_ctx, bool past_caches, int* defer_ns,
                             bool out_packed, hipStream_t s);
+// past_caches: K and V are read without keeping them in the caches (route::kv_past_caches).
 // defer_ns != NULL: when the KV range was split, leave the partials unmerged and report the number of splits
 // (the O projection then merges them, see GemmCommon::att_part); 0 is reported when `out` is complete.
 hipError_t launch_kv_gather(int dtype, const KvGeom& kv, int layer, const int32_t* btab_seq, int pos0, int n,

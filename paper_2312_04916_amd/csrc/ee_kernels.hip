@@ -1960,7 +1960,7 @@ struct AttTile0 {
     int32_t one, row0, nq, pos0, seq;
 };
 
-template <int HD, int NW, bool ONCE>
+template <int HD, int NW, bool PAST>
 __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const __bf16* __restrict__ q, size_t q_lo, __bf16* __restrict__ out,
                                                              size_t out_lo, int out_pk, const SegDesc* __restrict__ desc,
                                                              const int32_t* __restrict__ btab, KvGeom kv,
@@ -1991,9 +1991,9 @@ __global__ __launch_bounds__(NW * 64) void attn_mfma_kernel(const __bf16* __rest
     // exactly the 16 bytes of a transposed-V row that the P.V product needs as its other operand.
     const int krow0 = (li >> 2) * 8 + (li & 3);
 
-    // K and V of one 32-position tile, loaded straight into MFMA operand order (ONCE: and not kept in the caches, see
-    // the launch)
-    auto load = [](const __bf16* p) { return ONCE ? __builtin_nontemporal_load((const u32x4*)p) : *(const u32x4*)p; };
+    // K and V of one 32-position tile, loaded straight into MFMA operand order (PAST: and not kept in the caches, see
+    // route::kv_past_caches)
+    auto load = [](const __bf16* p) { return PAST ? __builtin_nontemporal_load((const u32x4*)p) : *(const u32x4*)p; };
     struct TileRegs {
         u32x4 k[2 * KK];
         u32x4 v[CG];
@@ -2186,8 +2186,8 @@ size_t attention_part_floats(int max_rows, int H, int hd) {
 
 template <int HD>
 static hipError_t launch_attention_mfma(const void* q, void* out, size_t io_lo, const SegDesc* desc, const SegDesc* desc_host, int n_qt,
-                                        const int32_t* btab, const KvGeom& kv, int layer, int d, float* part, int max_ctx, int* defer_ns,
-                                        bool out_packed, hipStream_t s) {
+                                        const int32_t* btab, const KvGeom& kv, int layer, int d, float* part, int max_ctx, bool past_caches,
+                                        int* defer_ns, bool out_packed, hipStream_t s) {
     const int out_pk = out_packed ? d / 32 : 0;
     AttTile0 t0{0, 0, 0, 0, 0};
     if (n_qt == 1 && desc_host != nullptr) t0 = AttTile0{1, desc_host->qt_row0[0], desc_host->qt_nq[0], desc_host->qt_pos0[0], desc_host->qt_seq[0]};
@@ -2207,17 +2207,8 @@ static hipError_t launch_attention_mfma(const void* q, void* out, size_t io_lo, 
     if (NS > by_len) NS = by_len;
     if (NS > ATT_MAX_SPLITS) NS = ATT_MAX_SPLITS;
     if (NS < 1) NS = 1;
-    // K and V that a step reads once and that no cache holds until the next step (256 MB behind the L2s; this is one layer
-    // of many) are read past the caches: 64 sequences of the 7B widths (434 MB a layer) 89 -> 80 us a layer = 5.4 TB/s, a
-    // pass of two steps 4600 -> 4450 us; 16 (300 MB) 4896 -> 4828.  One sequence (17 MB) loses by it, 37020 -> 37150 us.
-    size_t positions = (size_t)n_qt * max_ctx;
-    if (desc_host != nullptr) {
-        positions = 0;
-        for (int i = 0; i < n_qt; ++i) positions += desc_host->qt_pos0[i] + desc_host->qt_nq[i];
-    }
-    const bool once = positions * d * 4 >= ((size_t)64 << 20);
-    const auto kernel = few ? (once ? attn_mfma_kernel<HD, 8, true> : attn_mfma_kernel<HD, 8, false>)
-                            : (once ? attn_mfma_kernel<HD, 4, true> : attn_mfma_kernel<HD, 4, false>);
+    const auto kernel = few ? (past_caches ? attn_mfma_kernel<HD, 8, true> : attn_mfma_kernel<HD, 8, false>)
+                            : (past_caches ? attn_mfma_kernel<HD, 4, true> : attn_mfma_kernel<HD, 4, false>);
     EE_LAUNCH(kernel, dim3(wgs * NS), dim3((few ? 8 : 4) * 64), s, (const __bf16*)q, io_lo, (__bf16*)out, io_lo, out_pk, desc, btab, kv, lb, d,
               NS, part, t0);
     hipError_t e = hipGetLastError();
@@ -2239,15 +2230,15 @@ static hipError_t launch_attention_mfma(const void* q, void* out, size_t io_lo, 
 
 hipError_t launch_attention(int dtype, const void* q, void* out, size_t io_lo, const SegDesc* desc, const SegDesc* desc_host, int T, int n_qt,
                             const int32_t* btab,
-                            const KvGeom& kv, int layer, int d, float* part, int max_ctx, int* defer_ns,
+                            const KvGeom& kv, int layer, int d, float* part, int max_ctx, bool past_caches, int* defer_ns,
                             bool out_packed, hipStream_t s) {
     if (defer_ns) *defer_ns = 0;
     if (T <= 0) return hipSuccess;
     if (dtype == EE_BF16) {
         switch (kv.hd) {
-            case 32: return launch_attention_mfma<32>(q, out, io_lo, desc, desc_host, n_qt, btab, kv, layer, d, part, max_ctx, defer_ns, out_packed, s);
-            case 64: return launch_attention_mfma<64>(q, out, io_lo, desc, desc_host, n_qt, btab, kv, layer, d, part, max_ctx, defer_ns, out_packed, s);
-            case 128: return launch_attention_mfma<128>(q, out, io_lo, desc, desc_host, n_qt, btab, kv, layer, d, part, max_ctx, defer_ns, out_packed, s);
+            case 32: return launch_attention_mfma<32>(q, out, io_lo, desc, desc_host, n_qt, btab, kv, layer, d, part, max_ctx, past_caches, defer_ns, out_packed, s);
+            case 64: return launch_attention_mfma<64>(q, out, io_lo, desc, desc_host, n_qt, btab, kv, layer, d, part, max_ctx, past_caches, defer_ns, out_packed, s);
+            case 128: return launch_attention_mfma<128>(q, out, io_lo, desc, desc_host, n_qt, btab, kv, layer, d, part, max_ctx, past_caches, defer_ns, out_packed, s);
             default: return hipErrorInvalidValue;
         }
     }

@@ -193,6 +193,36 @@ inline bool step_cut(int kernel, int N, int K, int T, int min_wgs, size_t bytes,
 // 50304 words, 4096 wide: 128 -> 98 us).
 inline bool head_panels(int T, int V, int min_wgs) { return T > 32 && T <= PASS_ROWS && default_min_wgs(min_wgs) && V >= 128 * 256; }
 
+// ---- decode attention
+
+constexpr int ATT_ROWS = 16;  // rows of a query tile: consecutive positions of one sequence
+
+// Positions of K and V behind a launch: those its sequences have, and those its query tiles read (each tile all up to its last row).
+struct KvReads {
+    size_t distinct = 0, read = 0;
+    void add(int first, int rows) {  // a sequence whose rows are the positions first .. first + rows - 1
+        for (int r = 0; r < rows; r += ATT_ROWS) read += first + std::min(r + ATT_ROWS, rows);
+        if (rows > 0) distinct += first + rows;
+    }
+};
+
+// Are K and V read past the caches?  The 256 MB behind the L2s hold them until they are read again where that comes soon enough:
+// what counts is their bytes over the `layers` that lie between (with exits on, those up to the end of this segment: a token may
+// leave there and the next one begins), not those of one layer.  % that reading them past the caches adds to a step, by
+// those bytes: 63 to 330 MB +0.2 to +2.8 (7B widths, 1 sequence, 32 layers, 306 MB +0.4; 8, first exit behind 2 layers, 253 MB
+// +2.8), 380 to 530 MB between -2.8 and +1.5, 20 of 26 points faster (16 sequences, 1.3B widths, first exit behind 6 layers, 384 MB
+// -2.6; 7B widths, behind 2, 506 MB -1.0; one, 32 layers, 518 MB 0.0 and +0.2), 750 MB and more 0 to -6 (7B widths, 16
+// sequences, 16 layers, 4.0 GB -2.7; 1.3B widths, 24 layers, 3.0 GB -4.2, 6.0 GB -6.0, first exit behind 6 of them, 1.5 GB -5.7; 30B
+// widths, 16, 4 layers, 3.3 GB -3.9; the worst, 64 contexts of 100, +0.5).
+// Query tiles of one sequence read the same positions at about the same time, and the caches serve the second, unless there is
+// too much between them as well.  read / distinct 1.1 to 1.5: -0.4 to -4.4.  2 (17 to 32 rows a sequence): 86 to 244 MB a layer
+// +0.5 to +3.6, one point of nine faster (-0.9); 250 to 500 MB between -5.1 and +1.8, ten of 14 faster.  3 (33 to 41 rows): +0.2
+// to +7.5 at 60 to 530 MB a layer.
+inline bool kv_past_caches(const KvReads& r, int d, int layers) {
+    const size_t layer = r.distinct * d * 4;
+    return 2 * r.read <= 3 * r.distinct ? layer * layers >= (size_t)384 << 20 : r.read <= 2 * r.distinct && layer >= (size_t)256 << 20;
+}
+
 // ---- prompt phase
 
 // Row tiles per workgroup of a GEMM that is not cut, 8 or 4.  A CU works through about ceil(workgroups / 256) tiles

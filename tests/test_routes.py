@@ -8,6 +8,7 @@ import paper_2312_04916_amd as ee
 from workload import CONFIGS
 
 from common import cut_projections, ee_config_of
+from test_gpu_long_batches import CASES as LONG_BATCHES, long_batch
 from test_gpu_rows import CUT_PROMPTS, CUT_STEPS, PROMPT_SHAPES, SHAPES, STEP_LIMITS
 from test_gpu_rows_tiles import DOWN_MIN_WGS
 
@@ -119,6 +120,11 @@ def test_ring_refills_go_between_the_mfmas_where_a_wave_has_its_simd_to_itself()
     assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_DOWN, 64, r) == -7  # cut
     assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_QKV, 65, r) == -7   # more rows than max_rows
     assert L.ee_debug_rows_launch(C.byref(config(4096, 11008)), 64, 4, ee.EE_K_QKV, 64, None) == -7
+    one, past = (C.c_int32 * 1)(1), C.c_int32()
+    call = lambda cfg, n, c, rows, layers: L.ee_debug_kv_past_caches(C.byref(cfg), n, c, rows, layers, C.byref(past))  # noqa: E731
+    assert call(config(4096, 11008), 1, one, one, 2) == 0 and past.value == 0
+    assert call(ee_config_of(CONFIGS["C1"].shape, 256), 1, one, one, 1) == -1
+    assert [call(config(4096, 11008), *a) for a in ((0, one, one, 1), (65, one, one, 1), (1, one, one, 3), (1, one, (C.c_int32 * 1)(2), 1), (1, None, one, 1))] == [-7] * 5
 
 
 # What cutting one projection (Q|K|V, O, gate|up, down) was measured to add to a layer, in us, where it is 2 us or more either
@@ -155,6 +161,69 @@ def test_projections_are_cut_where_that_was_measured_to_win(prompt):
                 if us and cut != (us < 0):
                     wrong.append((d, rows, ee.KERNEL_NAMES[k], us, cut))
     assert not wrong, wrong
+
+
+# What reading K and V past the caches was measured to add to a step, in percent, where it is a percent or more either way:
+# (width, layers up to the end of the segment or of the step, sequences, positions of each, rows of each): percent.  Left out: the one
+# slower point of a percent or more above 384 MB over those layers, (2048, 6, 64, 125, 1) with 1.5, and those within 2 % of a line.
+MEASURED_PAST_CACHES = {
+    (4096, 16, 1, 1000, 1): 1.1, (4096, 4, 1, 1000, 1): 1.4, (4096, 4, 4, 1000, 1): 1.4, (4096, 4, 8, 500, 1): 1.3, (4096, 2, 4, 1000, 1): 1.7,
+    (4096, 2, 8, 1000, 1): 2.8, (2048, 24, 1, 1500, 1): 1.9, (2048, 6, 1, 3000, 1): 1.2, (2048, 6, 4, 1000, 1): 1.1, (2048, 6, 16, 250, 1): 1.7,
+    (768, 6, 64, 125, 1): 1.3,
+    (2048, 6, 16, 500, 1): -2.6, (4096, 2, 64, 250, 1): -0.8, (4096, 4, 8, 1000, 1): -1.4, (4096, 2, 16, 1000, 1): -1.0,
+    (768, 3, 64, 768, 1): -2.8, (6656, 1, 12, 1500, 1): -2.6,
+    (4096, 16, 2, 1000, 1): -1.7, (4096, 16, 4, 1000, 1): -1.7, (4096, 16, 8, 500, 1): -1.7, (4096, 16, 8, 1000, 1): -1.6,
+    (4096, 16, 16, 500, 1): -1.8, (4096, 16, 16, 1000, 1): -2.7, (4096, 4, 16, 1000, 1): -2.0, (4096, 16, 64, 200, 1): -1.2, (4096, 4, 64, 200, 1): -2.8,
+    (4096, 32, 2, 600, 1): -1.0, (2048, 24, 1, 3000, 1): -1.7, (2048, 24, 2, 1400, 1): -1.2, (2048, 24, 4, 700, 1): -1.3, (2048, 24, 4, 1000, 1): -2.0,
+    (2048, 24, 8, 1000, 1): -3.2, (2048, 24, 16, 250, 1): -1.4, (2048, 24, 16, 500, 1): -2.4, (2048, 24, 16, 1000, 1): -4.2, (2048, 24, 16, 2000, 1): -6.0,
+    (2048, 6, 16, 1000, 1): -2.4, (2048, 6, 16, 2000, 1): -5.7, (2048, 24, 64, 250, 1): -1.4, (768, 24, 16, 1000, 1): -1.6, (768, 24, 16, 2000, 1): -1.7,
+    (768, 24, 64, 500, 1): -2.4, (768, 6, 64, 500, 1): -1.5, (6656, 4, 12, 1500, 1): -2.9, (6656, 4, 16, 2000, 1): -3.9, (6656, 1, 16, 2000, 1): -3.1,
+    # three query tiles per sequence: 33 to 41 rows (a step whose first exit is passed, eight layers)
+    (4096, 8, 1, 3000, 41): 1.6, (4096, 8, 2, 2500, 33): 2.4, (4096, 8, 4, 2000, 33): 4.0, (4096, 8, 4, 3000, 41): 3.5, (4096, 8, 5, 3000, 40): 2.6,
+    (2048, 8, 4, 3000, 33): 6.1, (4096, 8, 7, 3000, 36): 3.6, (4096, 8, 6, 3000, 40): 6.4, (4096, 8, 7, 4500, 36): 2.4, (2048, 8, 7, 6000, 36): 7.1,
+    # two: the exceptions, both at 280 to 310 MB a layer, are (4096, 10, 2000, 24) with 1.5 and (2048, 8, 4500, 31) with 1.8
+    (4096, 8, 4, 1000, 17): 1.7, (2048, 8, 8, 2000, 31): 2.2, (2048, 8, 8, 3000, 17): 3.6, (2048, 8, 12, 2500, 20): 2.8, (768, 12, 8, 3000, 31): 2.8,
+    (4096, 8, 8, 2500, 17): -4.9, (4096, 8, 8, 3000, 31): -4.9, (4096, 8, 8, 2500, 31): -3.6, (4096, 8, 14, 1500, 18): -2.0, (4096, 8, 14, 2000, 18): -3.8,
+    (4096, 8, 12, 2500, 20): -1.3, (2048, 8, 14, 3000, 18): -3.5, (2048, 8, 14, 4500, 18): -4.0,
+}
+
+
+def test_kv_goes_past_the_caches_where_that_was_measured_to_win():
+    wrong = []
+    for (d, layers, n, ctx, rows), percent in MEASURED_PAST_CACHES.items():
+        hd = 64 if d == 768 else 128
+        cfg = ee.make_config(32, d, d // hd, hd, 32 * (d // 12), 1056, (1,), "bf16", 4096)
+        if ee.kv_past_caches(cfg, [ctx + 12] * n, [rows] * n, layers) != (percent < 0):
+            wrong.append((d, layers, n, ctx, rows, percent))
+    assert not wrong, wrong
+
+
+def test_kv_past_the_caches_counts_a_context_once_whatever_reads_it():
+    cfg = config(4096, 11008)  # two layers, 32 KB a position over both
+    line = (384 << 20) // (32 << 10)
+    past = lambda contexts, rows, layers=2: ee.kv_past_caches(cfg, contexts, rows, layers)  # noqa: E731
+    assert past([line], [1]) and past([line], [16]) and not past([line - 1], [1])
+    assert not past([line], [1], layers=1) and past([2 * line], [1], layers=1)
+    # tiles that read a context again: 17 rows are two, for which the line is 256 MB a layer, 33 are three
+    two = (256 << 20) // (16 << 10)
+    assert past([two], [17], layers=1) and past([two], [32]) and not past([two - 1], [17]) and not past([8 * two], [33])
+    assert not past([two // 4] * 3, [17] * 3) and past([two // 4] * 4, [17] * 4)
+    # half of what the sequences have may be read twice (short of 256 MB a layer)
+    q = (line - 4) // 4
+    cfg = config(4096, 11008)
+    cfg.n_layers = 3
+    past3 = lambda rows: ee.kv_past_caches(cfg, [q] * 4, rows, 3)  # noqa: E731
+    assert past3([17, 1, 1, 1]) and past3([17, 17, 1, 1]) and not past3([17, 17, 17, 1])
+    assert past([64] * 3 + [line], [17, 20, 33, 1]) and not past([64] * 3 + [line - 193], [1, 1, 1, 17])
+
+
+def test_the_gpu_tests_of_kv_past_the_caches_lie_on_both_sides_of_the_line():
+    for name in LONG_BATCHES:
+        for over in (-1, 0):
+            shape, contexts, rows = long_batch(name, over)
+            cfg = ee_config_of(shape, 2048)
+            assert ee.kv_past_caches(cfg, contexts, rows, shape.n_layers) == (over == 0), name
+            assert ee.kv_past_caches(cfg, contexts[:1], rows[:1], shape.n_layers) is False
 
 
 def test_the_gpu_tests_run_the_routes_they_claim():
