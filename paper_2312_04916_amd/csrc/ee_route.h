@@ -158,35 +158,37 @@ inline bool part_geom(int N, int K, int M, size_t bytes, PartGeom* g) {
 
 inline int part_wgs(const PartGeom& g) { return (g.n_wgN * g.n_wgM * g.KT + g.unit - 1) / g.unit; }
 
-// What the cut and its sum take, in microseconds, next to a launch without it: what a CU takes in at 54 GB/s (64-row tiles)
-// or 50 (128-row tiles) bounds the cut; the sum reads all parts back and writes M x N values, those of Q|K|V at 340 a
+// What the cut and its sum take, in microseconds, next to a launch without it: what a CU takes in, at gbps64 (64-row tiles) or
+// gbps128 (128-row tiles) GB/s, bounds the cut; the sum reads all parts back and writes M x N values, those of Q|K|V at 340 a
 // nanosecond (it writes V one 2-byte element at a time, as the cache keeps V transposed), others at 560.  Constants common to
 // both ways to launch are left out, so those of the two rules below are differences.  All fitted to the times of whole
 // prompts and steps with each of the four GEMMs cut and not, in all combinations.
-inline float cut_us(int kernel, const PartGeom& g, int M) {
+inline float cut_us(int kernel, const PartGeom& g, int M, float gbps64, float gbps128) {
     const int parts = part_wgs(g) + g.n_wgN * g.n_wgM;
-    return g.unit * (16 + 2 * g.mtl) / (g.mtl == 4 ? 54.0f : 50.0f) + parts * 16 * g.mtl / 5300.0f +
+    return g.unit * (16 + 2 * g.mtl) / (g.mtl == 4 ? gbps64 : gbps128) + parts * 16 * g.mtl / 5300.0f +
            (float)M * (g.n_tiles * 16) / (kernel == EE_K_QKV ? 340e3f : 560e3f);
 }
 
-// Decode steps: does the cut beat rows_kernel, which takes, per k-tile and round, G KB of weights at 50 GB/s and the rows at
-// 105, and for each further pass of up to 64 rows 6.5 us more (with RMS scales in front 10.4, 8.4 if it has up to 16 rows)?  Up
-// to 32 rows rows_kernel takes in less and needs no second launch.  Us that cutting one GEMM adds to a layer at 33 | 64 rows:
-// 4096 wide Q|K|V 0 | +2, O -3 | -3, gate|up +1 | +1, down -18 | -17; 2048 wide 0 | 0, 0 | 0, +3 | +3, -9 | -9; 6656 wide
-// +4 | +6, -7 | -6, -13 | -12, -33 | -30; 1024 wide all but down (0 | -1) lose.  From 66 rows on rows_kernel streams the
-// weights twice, and what wins at 1024 wide are Q|K|V (-1), gate|up (-1) and down (-7), from 2048 wide on all four.
+// Decode steps: does the cut, at 60 and 100 GB/s, beat rows_kernel, which takes, per k-tile and round, G KB of weights and 2 mt KB
+// of rows, both at 92 GB/s with four row tiles and 8 waves, else the weights at 55 and the rows at 120, and for each further pass of
+// up to 64 rows 1 us more (with RMS scales in front 3)?  Up to 32 rows rows_kernel takes in less and needs no second launch.
+// Us that cutting one GEMM adds to a layer at 33 | 64 rows: 4096 wide Q|K|V +3 | +6, O -2 | -3, gate|up +2 | +4, down -16 | -15;
+// 2048 wide +4 | +5, +1 | +2, +7 | +7, -6 | -7; 6656 wide +4 | +6, -6 | -5, -10 | -7, -28 | -29; 1024 wide all but down (-2 |
+// -1) lose.  From 66 rows on rows_kernel streams the weights twice, and what wins at 1024 wide is down (-5), at 2048 wide all but
+// gate|up (-3, -3, +1, -15), from 3072 wide on all four; with the scratch of a model for just so many rows (fewer workgroups) less:
+// 66 | 96 rows, 2048 wide +5 | -4, -3 | -5, +21 | +5, -12 | -18; 4096 wide +1 | -9, -5 | -9, 0 | -12, -30 | -36.  Of 650
+// such points the rule is wrong by 1 us or more at nine, by 3 us at most.
 inline bool step_cut(int kernel, int N, int K, int T, int min_wgs, size_t bytes, PartGeom* g) {
     if (T <= 32 || !default_min_wgs(min_wgs)) return false;
     const bool resid = kernel == EE_K_OPROJ || kernel == EE_K_DOWN;
-    float us = kernel == EE_K_QKV ? -2.4f : resid ? -2.7f : -0.9f;
-    if (T > 64) us -= 3.5f;  // (128-row tiles: a longer start)
+    float us = -3.8f;
     for (int r0 = 0; r0 < T; r0 += PASS_ROWS) {
-        const int mt = row_tiles(std::min(T - r0, PASS_ROWS)), G = tiles_per_wg(mt, N / 16, 0);
-        const int rounds = ((N / 16 + G - 1) / G + CUS - 1) / CUS;
-        us += rounds * (K / 32) * (G / 50.0f + 2 * mt / 105.0f);
-        if (r0) us += resid ? 6.5f : mt == 1 ? 8.4f : 10.4f;
+        const RowsShape r = rows_shape(std::min(T - r0, PASS_ROWS), K, N, 0);
+        const int rounds = ((N / 16 + r.tiles - 1) / r.tiles + CUS - 1) / CUS;
+        us += rounds * (K / 32) * (r.mt == 4 && r.waves == 8 ? (r.tiles + 2 * r.mt) / 92.0f : r.tiles / 55.0f + 2 * r.mt / 120.0f);
+        if (r0) us += resid ? 1.0f : 3.0f;
     }
-    return part_geom(N, K, T, bytes, g) && cut_us(kernel, *g, T) < us;
+    return part_geom(N, K, T, bytes, g) && cut_us(kernel, *g, T, 60.0f, 100.0f) < us;
 }
 
 // The head of 33 to 64 rows in panels of 256 columns (a vocabulary of at least half as many panels as there are CUs; 64 rows,
@@ -235,7 +237,7 @@ inline int prompt_row_tiles(int N, int M) {
     return r4 < r8 ? 4 : 8;
 }
 
-// Prompt phase: is the cut faster than a workgroup per result tile, which takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at
+// Prompt phase: is the cut, at 54 and 50 GB/s, faster than a workgroup per result tile, which takes in `rounds` x KT x (16 + 2 mtl) KB per CU, at
 // 77 GB/s with 64-row tiles and 55 with 128-row tiles, and 1/70 us per 64-row tile or 15 us with 128-row tiles (0.3 us per
 // k-tile on short contractions)?  Us that cutting one GEMM adds to a layer: 4096 wide, 64 | 99 | 256 | 512 rows: Q|K|V -31 |
 // -19 | +6 | -7, O -40 | -30 | -26 | -15, gate|up -17 | -2 | -19 | +1, down -115 | -94 | -90 | -59; 2048 wide, 65 | 384 | 640
@@ -252,7 +254,7 @@ inline bool prompt_cut(int kernel, int N, int K, int M, size_t bytes, PartGeom* 
     const long direct_tiles = (long)g->n_wgN * ((M + mtl * 16 - 1) / (mtl * 16));
     const long rounds = (direct_tiles + CUS - 1) / CUS;
     const float us = rounds * g->KT * (16 + 2 * mtl) / (mtl == 4 ? 77.0f : 55.0f) + (mtl == 4 ? direct_tiles / 70.0f : std::min(15.0f, 0.3f * g->KT));
-    return cut_us(kernel, *g, M) < us + (kernel == EE_K_QKV ? 2.0f : resid ? 1.0f : -1.0f);
+    return cut_us(kernel, *g, M, 54.0f, 50.0f) < us + (kernel == EE_K_QKV ? 2.0f : resid ? 1.0f : -1.0f);
 }
 
 // Scratch that the cuts of a prompt phase of up to `max_rows` rows per pass can use.  (What is cut, and how, changes with

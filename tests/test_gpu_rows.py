@@ -24,14 +24,16 @@ SHAPES = {
     "d1024": ModelShape(2, 1024, 8, 128, 2080, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5),
     "d1024w": ModelShape(2, 1024, 8, 128, 2848, 544, (1,), "bf16", 0.02, 0.3 / 8 ** 0.5),
     "d3072": ModelShape(2, 3072, 24, 128, 1056, 544, (1,), "bf16", 0.02, 0.3 / 24 ** 0.5),
+    "d5632": ModelShape(2, 5632, 44, 128, 352, 544, (1,), "bf16", 0.02, 0.3 / 44 ** 0.5),
 }
 # The projections of a step that are cut, by rows (the rule is host arithmetic: test_routes.py checks this table without a
 # GPU): with 64-row tiles each of the four in one shape or another, with 128-row tiles one and two of those per panel.
 STEP_LIMITS = dict(max_rows=160, max_seqs=4)
 CUT_STEPS = {
-    "d1024": {33: "", 64: "", 66: "GD", 128: "QOGD", 129: "QOGD"},
+    "d1024": {33: "", 64: "", 66: "D", 128: "QOGD", 129: "QOGD"},
     "d1024w": {33: "D", 64: "D"},
-    "d3072": {33: "QOG", 64: "OG"},
+    "d3072": {33: "OG", 64: "OG"},
+    "d5632": {33: "QOG"},
 }
 PROMPT_SHAPES = {
     "d1024": SHAPES["d1024"],
@@ -43,7 +45,7 @@ CUT_PROMPTS = {  # (tokens, prefill_rows): the projections that are cut in each 
 }
 
 
-@pytest.mark.parametrize("name,min_wgs", [("d128", 0), ("d192", 0), ("d128", 16), ("d192", 6), ("d1024", 0), ("d1024w", 0), ("d3072", 0)])
+@pytest.mark.parametrize("name,min_wgs", [("d128", 0), ("d192", 0), ("d128", 16), ("d192", 6), ("d1024", 0), ("d1024w", 0), ("d3072", 0), ("d5632", 0)])
 def test_full_depth_step_over_a_given_number_of_rows(name, min_wgs):
     shape = SHAPES[name]
     om = build_model(shape, 5, gain_jitter=0.1)
