@@ -1165,12 +1165,13 @@ __global__ __launch_bounds__(512) void head_merge_kernel(const HeadPartial* __re
 // G + 2 MT KB, of which G come from HBM.  Up to 16 rows HBM bounds it (gate|up at the 7B widths 35.7 -> 31.0 us = 5.8
 // TB/s, at the 30B widths 91.5 -> 77.1 us = 6.2 TB/s, 16 and 4 rows); at 64 rows the bytes that a CU can have outstanding
 // do (about 40 KB: 30 to 70 GB/s per CU, the less the more of them come from HBM; neither a deeper ring nor another
-// order of the k-tiles moves it; the counters show 70 to 97 lines of 128 bytes on their way per CU, whatever is asked for).  Hence as many tiles per workgroup as leave one workgroup per CU, one wave per SIMD
-// with all 512 registers for five and six of them from 33 rows on, and an epilogue that runs on registers behind a single barrier: the product is
-// formed transposed (weights as the A operand), so a lane holds four consecutive features of one row, and everything it
-// needs from memory is requested before the barrier.  64 rows, 7B widths, before (8 waves, at most two tiles, epilogue
-// through LDS with one dependent look-up per element and pass) and now: Q|K|V 79.4 -> 41.8 us, gate|up 86.8 -> 52.1, head
-// 194 -> 128; 32 rows: gate|up 41.4 -> 33.1, Q|K|V 29.2 -> 23.7.  (The loop for 33 and more rows has changed since, see there.)
+// order of the k-tiles moves it; the counters show 70 to 97 lines of 128 bytes on their way per CU, whatever is asked
+// for).  Hence as many tiles per workgroup as leave one workgroup per CU, as many waves as their registers allow
+// (route::rows_shape), and an epilogue that runs on registers behind a single barrier: the product is formed transposed
+// (weights as the A operand), so a lane holds four consecutive features of one row, and everything it needs from memory is
+// requested before the barrier.  64 rows, 7B widths, with an epilogue through LDS (one dependent look-up per element and
+// pass) and at most two tiles, with this one, and with the loops and wave counts of 33 and more rows as they are now: Q|K|V
+// 79.4, 41.8, 37.4 us, gate|up 86.8, 52.1, 48.5; 32 rows: gate|up 41.4 -> 33.1, Q|K|V 29.2 -> 23.7.
 // ------------------------------------------------------------------------------------------------
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
@@ -1944,12 +1945,12 @@ __global__ __launch_bounds__(256) void attn_f32_kernel(const float* __restrict__
 
 // ------------------------------------------------------------------------------------------------
 // attention, bf16 model: ragged multi-query decode attention over the paged cache with MFMA.
-// One workgroup = (query tile of <= 16 consecutive rows of one sequence, head, KV split); its 4 waves
+// One workgroup = (query tile of <= 16 consecutive rows of one sequence, head, KV split); its 4 or 8 waves
 // take the split's 32-position tiles round-robin.  Per tile a wave computes S^T = K Q^T (K rows come
 // straight from the cache as MFMA A operands: a load covers 16 rows x 64 contiguous bytes), applies the causal mask
 // (only the last rows of the context differ between the queries of a tile), keeps an online soft-max
-// per query, stages the V tile through LDS (coalesced 16-byte loads in, transposed 2-byte reads out)
-// and accumulates O^T += V^T P^T, where P^T is already in B-operand layout in the S^T registers.
+// per query and accumulates O^T += V^T P^T, where P^T is already in B-operand layout in the S^T registers and V, which
+// the cache keeps transposed, comes straight from it as the A operand.
 // q and P are fed as two bf16 terms each (hi + lo), so only K and V carry bf16 rounding.
 // Partials of the KV splits are merged by attn_merge_kernel in a fixed order.
 // ------------------------------------------------------------------------------------------------
