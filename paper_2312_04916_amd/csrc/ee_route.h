@@ -211,8 +211,8 @@ struct KvReads {
 // Are K and V read past the caches?  The 256 MB behind the L2s hold them until they are read again where that comes soon enough:
 // what counts is their bytes over the `layers` that lie between (with exits on, those up to the end of this segment: a token may
 // leave there and the next one begins), not those of one layer.  % that reading them past the caches adds to a step, by
-// those bytes: 63 to 330 MB -0.7 to +2.8, nearly all slower (7B widths, 1 sequence, 32 layers, 306 MB +0.4; 8, first exit behind 2 layers, 253 MB
-// +2.8), 380 to 530 MB between -2.8 and +1.5, 20 of 26 points faster (16 sequences, 1.3B widths, first exit behind 6 layers, 384 MB
+// those bytes: 63 to 330 MB -0.7 to +2.8, nearly all slower (7B widths, 1 sequence, 32 layers, 306 MB +0.4; 8, first exit behind 2
+// layers, 253 MB +2.8), 380 to 530 MB between -2.8 and +1.5, 20 of 26 points faster (16 sequences, 1.3B widths, first exit behind 6 layers, 384 MB
 // -2.6; 7B widths, behind 2, 506 MB -1.0; one, 32 layers, 518 MB 0.0 and +0.2), 750 MB and more 0 to -6 (7B widths, 16
 // sequences, 16 layers, 4.0 GB -2.7; 1.3B widths, 24 layers, 3.0 GB -4.2, 6.0 GB -6.0, first exit behind 6 of them, 1.5 GB -5.7; 30B
 // widths, 16, 4 layers, 3.3 GB -3.9; the worst, 64 contexts of 100, +0.5).
